@@ -54,8 +54,8 @@ struct BatchWork {
   int cap = 0, m = 0;
   size_t ld = 0, ldc = 0;
   bool f32 = false, adj = false;
-  DBuf<double> t, rc, yc, ec, wz, wy, wt, text;                    // FP64 cycle
-  DBuf<float> t32, rc32, yc32, ec32, wz32, wy32, wt32, text32;     // FP32 cycle
+  DBuf<double> t, rc, yc, ec, wz, wy, wt, text, y;                 // FP64 cycle (y: level sweeps)
+  DBuf<float> t32, rc32, yc32, ec32, wz32, wy32, wt32, text32, y32;  // FP32 cycle
   DBuf<int> ncLc, ncUc, ncUct, ncLct;                              // tree node counters per column
   DBuf<double> abc, auc, aec, as, at;                              // adjoint cycle
   DBuf<double> r;                                                  // fine residuals before the restriction
@@ -776,9 +776,6 @@ static void build_sweep(Sweep& sw, int n, const std::vector<int>& dep_rp, const 
     else d2d(sw.dinv.p, dev_dinv, n, s);
     launch_cast_f32(sw.dinv.p, sw.dinv32.p, n, s);
   }
-  sw.ticket.alloc(1);
-  launch_fill_u32(sw.ticket.p, 0u, 1, s);
-  sw.ticket_base = 0;
   {
     // a few levels of look-ahead: more resident waves would only poll
     const double per_level = levels > 0 ? (double)sw.nchunks / levels : 1.0;
@@ -886,26 +883,34 @@ static void check_abort(Solver& S) {
 
 // One triangular sweep of a factor: the single-CU kernel when the factor has
 // one and it is enabled, else the synchronisation-free kernel over the
-// factor's level segments (one workgroup or the whole device each).
+// factor's level segments (one workgroup or the whole device each).  nb
+// columns (rhs and reset ldr, out ldo apart) share every launch, except those
+// of the single-CU kernel, whose staging holds one column.
 template <class T>
-static void run_tri(Solver& S, Sweep& sw, const void* rhs, bool rhs_f64, T* out, T* reset) {
+static void run_tri(Solver& S, Sweep& sw, const void* rhs, bool rhs_f64, T* out, T* reset, int nb = 1, size_t ldr = 0,
+                    size_t ldo = 0) {
   constexpr bool F32 = sizeof(T) == 4;
   if (sw.cu && (S.opt.sweep_kernel == 0 || S.opt.sweep_kernel == 3)) {
     CuSweep& c = *sw.cu;
-    launch_cu_sweep<T>(c, F32 ? (const T*)c.wval32.p : (const T*)c.wval.p,
-                       F32 ? (const T*)c.dinv_e32.p : (const T*)c.dinv_e.p, rhs, rhs_f64, out, reset,
-                       F32 ? (T*)S.cu_rhs32.p : (T*)S.cu_rhs.p, F32 ? (T*)S.cu_out32.p : (T*)S.cu_out.p, S.s);
+    for (int k = 0; k < nb; ++k) {
+      const void* rk = rhs_f64 ? (const void*)((const double*)rhs + k * ldr) : (const void*)((const T*)rhs + k * ldr);
+      launch_cu_sweep<T>(c, F32 ? (const T*)c.wval32.p : (const T*)c.wval.p,
+                         F32 ? (const T*)c.dinv_e32.p : (const T*)c.dinv_e.p, rk, rhs_f64, out + k * ldo,
+                         reset ? reset + k * ldr : nullptr, F32 ? (T*)S.cu_rhs32.p : (T*)S.cu_rhs.p,
+                         F32 ? (T*)S.cu_out32.p : (T*)S.cu_out.p, S.s);
+    }
     return;
   }
   const T* di = sw.has_diag ? (F32 ? (const T*)sw.dinv32.p : (const T*)sw.dinv.p) : nullptr;
   if (S.opt.sweep_kernel == 0 && sw.levels <= kLevelLaunchMax && (int)sw.lvl_c0.size() == sw.levels + 1) {
     // a few wide levels (colour classes): one plain launch per level
-    launch_sweep_levels<T>(sw, F32 ? (const T*)sw.dval32.p : (const T*)sw.dval.p, di, rhs, rhs_f64, out, reset, S.s);
+    launch_sweep_levels<T>(sw, F32 ? (const T*)sw.dval32.p : (const T*)sw.dval.p, di, rhs, rhs_f64, out, reset, S.s,
+                           nb, ldr, ldo);
     return;
   }
   const int waves = S.opt.sweep_waves > 0 ? S.opt.sweep_waves : sw.waves;
   launch_sweep<T>(sw, F32 ? (const T*)sw.dval32.p : (const T*)sw.dval.p, di, rhs, rhs_f64, out, reset, waves,
-                  S.opt.sweep_kernel == 1, S.abort_flag.p, S.s);
+                  S.opt.sweep_kernel == 1, S.abort_flag.p, S.s, nb, ldr, ldo);
 }
 
 static void reset_cycle_buffers(Solver& S) {
@@ -1589,6 +1594,10 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
       launch_fill_f64_bits(B.wy.p, kSent64, nw, s);
       launch_fill_f64_bits(B.wt.p, kSent64, nw, s);
     }
+    if (!S.wave && !S.fine_nd) {
+      B.y.alloc(nf);
+      launch_fill_f64_bits(B.y.p, kSent64, nf, s);
+    }
     auto counters = [&](DBuf<int>& c, const TreeSolve& t) {
       if (!t.ncount.p) return;
       c.alloc(t.ncount.n * B.cap);
@@ -1623,6 +1632,10 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
       launch_fill_f32_bits(B.wy32.p, kSent32, nw, s);
       launch_fill_f32_bits(B.wt32.p, kSent32, nw, s);
     }
+    if (!S.wave && !S.fine_nd) {
+      B.y32.alloc(nf);
+      launch_fill_f32_bits(B.y32.p, kSent32, nf, s);
+    }
     B.f32 = true;
   }
   if (adjoint && !B.adj) {
@@ -1652,9 +1665,9 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
 static void reset_batch_buffers(Solver& S) {
   BatchWork& B = S.bw;
   hipStream_t s = S.s;
-  for (DBuf<double>* b : {&B.t, &B.yc, &B.ec, &B.text, &B.wy, &B.wt, &B.auc, &B.aec, &B.at})
+  for (DBuf<double>* b : {&B.t, &B.yc, &B.ec, &B.text, &B.wy, &B.wt, &B.auc, &B.aec, &B.at, &B.y})
     if (b->p) launch_fill_f64_bits(b->p, kSent64, b->n, s);
-  for (DBuf<float>* b : {&B.t32, &B.yc32, &B.ec32, &B.text32, &B.wy32, &B.wt32})
+  for (DBuf<float>* b : {&B.t32, &B.yc32, &B.ec32, &B.text32, &B.wy32, &B.wt32, &B.y32})
     if (b->p) launch_fill_f32_bits(b->p, kSent32, b->n, s);
   for (DBuf<int>* c : {&B.ncLc, &B.ncUc, &B.ncUct, &B.ncLct})
     if (c->p) launch_fill_u32(reinterpret_cast<unsigned*>(c->p), 0u, c->n, s);
@@ -1676,8 +1689,18 @@ static void vcycle_batch(Solver& S, const double* z, size_t ldz, double* q, size
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.L0, sz, 8, false) + sweep_bytes(S.U0, sz, sz, true)));
     launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, true, F32 ? (T*)B.wz32.p : (T*)B.wz.p, F32 ? (T*)B.wy32.p : (T*)B.wy.p,
                         F32 ? (T*)B.wt32.p : (T*)B.wt.p, t, S.abort_flag.p, s, nb, ldz, ld);
-  } else {
+  } else if (S.fine_nd) {
     for (int c = 0; c < nb; ++c) smooth_apply<T>(S, z + c * ldz, t + c * ld);
+  } else {
+    T* y = F32 ? (T*)B.y32.p : (T*)B.y.p;
+    {
+      Prof p(S, PC_SWEEP_FINE, nb * sweep_bytes(S.L0, sz, 8, false));
+      run_tri<T>(S, S.L0, z, true, y, nullptr, nb, ldz, ld);
+    }
+    {
+      Prof p(S, PC_SWEEP_FINE, nb * sweep_bytes(S.U0, sz, sz, true));
+      run_tri<T>(S, S.U0, y, false, t, y, nb, ld, ld);
+    }
   }
   {
     // the residual over the column batch (A read once for every column),
@@ -1740,8 +1763,17 @@ static void vcycle_adjoint_batch(Solver& S, const double* z, size_t ldz, double*
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.U0t, 8, 8, false) + sweep_bytes(S.L0t, 8, 8, true)));
     launch_wave_pair<double>(S.wg, S.wU0t, S.wL0t, B.as.p, true, B.wz.p, B.wy.p, B.wt.p, B.at.p, S.abort_flag.p, s, nb,
                              ld, ld);
-  } else {
+  } else if (S.fine_nd) {
     for (int c = 0; c < nb; ++c) smooth_adjoint(S, B.as.p + c * ld, B.at.p + c * ld);
+  } else {
+    {
+      Prof p(S, PC_SWEEP_FINE, nb * sweep_bytes(S.U0t, 8, 8, false));
+      run_tri<double>(S, S.U0t, B.as.p, false, B.y.p, nullptr, nb, ld, ld);
+    }
+    {
+      Prof p(S, PC_SWEEP_FINE, nb * sweep_bytes(S.L0t, 8, 8, true));
+      run_tri<double>(S, S.L0t, B.y.p, false, B.at.p, B.y.p, nb, ld, ld);
+    }
   }
   {
     Prof p(S, PC_PROLONG, nb * ((double)S.n * 28 + (double)S.nc * 8));

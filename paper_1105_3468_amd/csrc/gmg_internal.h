@@ -132,8 +132,6 @@ struct Sweep {
   DBuf<int> chunk, rows, dp, dcol;
   DBuf<double> dval, dinv;
   DBuf<float> dval32, dinv32;
-  DBuf<unsigned> ticket;     // dynamic chunk counter
-  unsigned ticket_base = 0;  // host copy of the counter value at the next launch
   bool has_diag = false;
   int waves = 0;             // resident waves (a few dependency levels of look-ahead)
   // consecutive level ranges, one launch each: chunks [seg_c0[g], seg_c1[g])
@@ -289,10 +287,11 @@ void set_error_message(const std::string& msg);
 constexpr int kLevelLaunchMax = 16;
 template <class T>
 void launch_sweep_levels(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool rhs_is_f64, T* out,
-                         T* reset_rhs, hipStream_t s);
+                         T* reset_rhs, hipStream_t s, int nb = 1, size_t ldr = 0, size_t ldo = 0);
 template <class T>
 void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool rhs_is_f64,
-                  T* out, T* reset_rhs, int waves, bool whole, int* abort_flag, hipStream_t s);
+                  T* out, T* reset_rhs, int waves, bool whole, int* abort_flag, hipStream_t s, int nb = 1,
+                  size_t ldr = 0, size_t ldo = 0);
 // rows of a one-workgroup level range (its FP64 results fill 128 KiB of LDS)
 constexpr int kSweepLdsRows = 16384;
 template <class T>

@@ -7,9 +7,9 @@
 // a wave never holds two rows where one depends on the other.  A chunk gives
 // each of its rows G lanes (G a power of two chosen per level from the
 // longest row, so that a lane reads at most one batch of entries); the lanes'
-// partial sums meet in a shuffle reduction.  Waves take chunks from a global
-// ticket counter in schedule order, so every row a wave waits for belongs to
-// a chunk that an already-running wave holds: the sweep always makes
+// partial sums meet in a shuffle reduction.  Chunk t belongs to wave t of the
+// launch and workgroups start in order, so every row a wave waits for belongs
+// to a chunk that an already-running wave holds: the sweep always makes
 // progress.  A result is published with one relaxed agent-scope store
 // and doubles as its own ready flag: consumers poll with relaxed agent-scope
 // loads until the value differs from the NaN sentinel the buffer was reset to.
@@ -210,26 +210,32 @@ __device__ __forceinline__ bool chunk_rows(const Src& src, const int* __restrict
   return true;
 }
 
+// A wave per chunk, in schedule order.  500k-row graph, 24 levels, 15.6k
+// chunks: 80 us a sweep, against 190 us when persistent waves drew their
+// chunks from one counter (12 ns a ticket, all of them in turn).
+//
+// nb > 1 sweeps nb right-hand sides in one launch: workgroup g * nb + c runs
+// chunks 4 g .. 4 g + 3 for column c (rhs + c * ldr, out + c * ldo; reset_rhs
+// like rhs).
 template <class T, class TR, bool DIAG>
 __global__ __launch_bounds__(256) void k_sweep(const int* __restrict__ chunk, const int* __restrict__ rows,
                                                const int* __restrict__ dp, const int* __restrict__ dcol,
                                                const T* __restrict__ dval, const T* __restrict__ dinv,
-                                               const TR* rhs, T* out, TR* reset_rhs, unsigned nchunks,
-                                               unsigned* ticket, unsigned base, int* abort_flag, uint64_t limit) {
-  const int lane = threadIdx.x & 63;
+                                               const TR* rhs, T* out, TR* reset_rhs, unsigned nchunks, int nb,
+                                               size_t ldr, size_t ldo, int* abort_flag, uint64_t limit) {
+  const unsigned g = blockIdx.x / nb, col = blockIdx.x - g * nb;
+  const unsigned t = g * 4u + (threadIdx.x >> 6);
+  if (t >= nchunks) return;
+  rhs += col * ldr;
+  out += col * ldo;
+  if (reset_rhs) reset_rhs += col * ldr;
   const GlobalSrc<T> src{out};
-  for (;;) {
-    unsigned t = 0;
-    if (lane == 0) t = atomicAdd(ticket, 1u) - base;
-    t = __shfl(t, 0, 64);
-    if (t >= nchunks) break;
-    int e, r;
-    T y;
-    if (chunk_rows<T, TR, DIAG>(src, chunk, t, rows, dp, dcol, dval, dinv, rhs, abort_flag, limit, e, r, y)) {
-      st_agent(out + r, y);
-      // rhs and reset_rhs may be the same buffer: the row read it already
-      if (reset_rhs) reset_rhs[r] = sentinel_of<TR>(0);
-    }
+  int e, r;
+  T y;
+  if (chunk_rows<T, TR, DIAG>(src, chunk, t, rows, dp, dcol, dval, dinv, rhs, abort_flag, limit, e, r, y)) {
+    st_agent(out + r, y);
+    // rhs and reset_rhs may be the same buffer: the row read it already
+    if (reset_rhs) reset_rhs[r] = sentinel_of<TR>(0);
   }
 }
 
@@ -242,9 +248,13 @@ template <class T, class TR, bool DIAG>
 __global__ __launch_bounds__(256) void k_sweep_level(const int* __restrict__ chunk, const int* __restrict__ rows,
                                                      const int* __restrict__ dp, const int* __restrict__ dcol,
                                                      const T* __restrict__ dval, const T* __restrict__ dinv,
-                                                     const TR* rhs, T* out, TR* reset_rhs, unsigned nchunks) {
+                                                     const TR* rhs, T* out, TR* reset_rhs, unsigned nchunks,
+                                                     size_t ldr, size_t ldo) {
   const unsigned t = blockIdx.x * 4u + (threadIdx.x >> 6);
   if (t >= nchunks) return;
+  rhs += blockIdx.y * ldr;  // column blockIdx.y
+  out += blockIdx.y * ldo;
+  if (reset_rhs) reset_rhs += blockIdx.y * ldr;
   const FinalSrc<T> src{out};
   int e, r;
   T y;
@@ -262,7 +272,10 @@ template <class T, class TR, bool DIAG>
 __global__ __launch_bounds__(SWEEP_WG_THREADS) void k_sweep_lds(
     const int* __restrict__ chunk, const int* __restrict__ rows, const int* __restrict__ dp,
     const int* __restrict__ dslot, const T* __restrict__ dval, const T* __restrict__ dinv, const TR* rhs, T* out,
-    TR* reset_rhs, unsigned nchunks, int e0, int m, int* abort_flag, uint64_t limit) {
+    TR* reset_rhs, unsigned nchunks, int e0, int m, size_t ldr, size_t ldo, int* abort_flag, uint64_t limit) {
+  rhs += blockIdx.x * ldr;  // one workgroup per column
+  out += blockIdx.x * ldo;
+  if (reset_rhs) reset_rhs += blockIdx.x * ldr;
   extern __shared__ __align__(16) unsigned char sweep_smem[];
   T* xs = reinterpret_cast<T*>(sweep_smem);
   __shared__ unsigned ticket;
@@ -302,7 +315,7 @@ static uint64_t wall_limit_ticks() {
 
 template <class T>
 void launch_sweep_levels(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool rhs_is_f64, T* out,
-                         T* reset_rhs, hipStream_t s) {
+                         T* reset_rhs, hipStream_t s, int nb, size_t ldr, size_t ldo) {
   if (sw.nchunks == 0) return;
   if ((int)sw.lvl_c0.size() != sw.levels + 1) fail(GMG_ERR_INVALID_ARG, "level sweep: no level table");
   for (int l = 0; l < sw.levels; ++l) {
@@ -312,8 +325,8 @@ void launch_sweep_levels(Sweep& sw, const T* dval, const T* dinv, const void* rh
     const int* ch = sw.chunk.p + 3 * (size_t)c0;
     const unsigned blocks = (nchunks + 3) / 4;
 #define GMG_SWV(TR_, DG_, RHS_, RESET_)                                                                       \
-  hipLaunchKernelGGL((k_sweep_level<T, TR_, DG_>), dim3(blocks), dim3(256), 0, s, ch, sw.rows.p, sw.dp.p,    \
-                     sw.dcol.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks)
+  hipLaunchKernelGGL((k_sweep_level<T, TR_, DG_>), dim3(blocks, nb), dim3(256), 0, s, ch, sw.rows.p, sw.dp.p,    \
+                     sw.dcol.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, ldr, ldo)
     if (rhs_is_f64 && sizeof(T) == 4) {
       if (sw.has_diag) GMG_SWV(double, true, rhs, (double*)nullptr);
       else GMG_SWV(double, false, rhs, (double*)nullptr);
@@ -326,14 +339,16 @@ void launch_sweep_levels(Sweep& sw, const T* dval, const T* dinv, const void* rh
   }
 }
 template void launch_sweep_levels<double>(Sweep&, const double*, const double*, const void*, bool, double*, double*,
-                                          hipStream_t);
+                                          hipStream_t, int, size_t, size_t);
 template void launch_sweep_levels<float>(Sweep&, const float*, const float*, const void*, bool, float*, float*,
-                                         hipStream_t);
+                                         hipStream_t, int, size_t, size_t);
 
 template <class T>
 void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool rhs_is_f64, T* out,
-                  T* reset_rhs, int waves, bool whole, int* abort_flag, hipStream_t s) {
+                  T* reset_rhs, int waves, bool whole, int* abort_flag, hipStream_t s, int nb, size_t ldr,
+                  size_t ldo) {
   if (sw.nchunks == 0) return;
+  if (nb < 1 || ((int64_t)sw.nchunks / 4 + 1) * nb > 0x7fffffff) fail(GMG_ERR_INVALID_ARG, "sweep: bad column count");
   const uint64_t lim = wall_limit_ticks();
   // whole: every level device-wide in one launch; else the level ranges
   // chosen at setup
@@ -355,8 +370,8 @@ void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSweepLdsRows * sizeof(double)))); \
       attr = true;                                                                                                \
     }                                                                                                             \
-    hipLaunchKernelGGL((k_sweep_lds<T, TR_, DG_>), dim3(1), dim3(SWEEP_WG_THREADS), lds, s, ch, sw.rows.p,        \
-                       sw.dp.p, sw.dslot.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, e0, m, abort_flag, lim); \
+    hipLaunchKernelGGL((k_sweep_lds<T, TR_, DG_>), dim3(nb), dim3(SWEEP_WG_THREADS), lds, s, ch, sw.rows.p,        \
+                       sw.dp.p, sw.dslot.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, e0, m, ldr, ldo, abort_flag, lim); \
   } while (0)
       if (rhs_is_f64 && sizeof(T) == 4) {
         if (sw.has_diag) GMG_SWL(double, true, rhs, (double*)nullptr);
@@ -369,13 +384,25 @@ void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool
       HIPCK(hipGetLastError());
       continue;
     }
-    unsigned w = waves > 0 ? (unsigned)waves : 2048u;
-    if (w > nchunks) w = nchunks;
-    const unsigned blocks = (w + 3) / 4;
-    const unsigned used = blocks * 4;  // every wave takes exactly one ticket that ends it
+    const unsigned blocks = (nchunks + 3) / 4 * (unsigned)nb;
+    // Idle LDS holds the resident waves near `waves` a column: a few levels of
+    // look-ahead.  More only poll (200k-row graph, FP64: 49 us with 1024
+    // waves, 65 us with all 8192; 500k rows: 80 us with 2048, 86 us with
+    // 1024 or 8192; 16 columns of 200k rows: 390 us with 1024, 313 us with all)
+    size_t hold = 0;
+    const int64_t per_cu = std::max<int64_t>(1, ((int64_t)waves * nb + 4 * 256 - 1) / (4 * 256));
+    if (per_cu < 8) hold = (size_t)(160 * 1024) / per_cu - 1024;
 #define GMG_SW(TR_, DG_, RHS_, RESET_)                                                                        \
-  hipLaunchKernelGGL((k_sweep<T, TR_, DG_>), dim3(blocks), dim3(256), 0, s, ch, sw.rows.p, sw.dp.p, sw.dcol.p, \
-                     dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, sw.ticket.p, sw.ticket_base, abort_flag, lim)
+  do {                                                                                                        \
+    static bool attr = false;                                                                                 \
+    if (!attr) {                                                                                              \
+      HIPCK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<T, TR_, DG_>),                         \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));                      \
+      attr = true;                                                                                            \
+    }                                                                                                         \
+    hipLaunchKernelGGL((k_sweep<T, TR_, DG_>), dim3(blocks), dim3(256), hold, s, ch, sw.rows.p, sw.dp.p,       \
+                       sw.dcol.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, nb, ldr, ldo, abort_flag, lim); \
+  } while (0)
     if (rhs_is_f64 && sizeof(T) == 4) {
       // FP32 sweep with an FP64 right-hand side (first sweep of the FP32 cycle)
       if (sw.has_diag) GMG_SW(double, true, rhs, (double*)nullptr);
@@ -386,13 +413,12 @@ void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool
     }
 #undef GMG_SW
     HIPCK(hipGetLastError());
-    sw.ticket_base += nchunks + used;
   }
 }
 template void launch_sweep<double>(Sweep&, const double*, const double*, const void*, bool, double*, double*,
-                                   int, bool, int*, hipStream_t);
+                                   int, bool, int*, hipStream_t, int, size_t, size_t);
 template void launch_sweep<float>(Sweep&, const float*, const float*, const void*, bool, float*, float*, int,
-                                  bool, int*, hipStream_t);
+                                  bool, int*, hipStream_t, int, size_t, size_t);
 
 
 // ------------------------------------------------------- single-CU sweep
