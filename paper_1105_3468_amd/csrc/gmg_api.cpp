@@ -36,7 +36,7 @@ constexpr uint64_t kSent64 = 0x7FF8DEADBEEFF00DULL;
 constexpr uint32_t kSent32 = 0x7FC0FEEDu;
 constexpr int kMaxRestart = 2048;   // longest Krylov basis (vectors)
 constexpr int kPinCol = 2 * kMaxRestart + 8;  // doubles per pinned block (scalars, or h1, h2, ||w||^2)
-constexpr int kFused = 32;          // basis size handled by the fused CGS2 kernels
+constexpr int kFused = 32;          // basis size handled by the register-resident kernels
 
 static const char* kProfNames[PC_COUNT] = {"spmv", "sweep_fine", "sweep_coarse", "resid_restrict",
                                            "prolong", "ortho", "vector"};
@@ -60,7 +60,7 @@ struct BatchWork {
   DBuf<double> abc, auc, aec, as, at;                              // adjoint cycle
   DBuf<double> r;                                                  // fine residuals before the restriction
   DBuf<float> r32;
-  DBuf<double> V, Z, w, x, b, coef;                                // Krylov
+  DBuf<double> V, Z, w, x, b, coef, gram, gdots;                   // Krylov
 };
 
 struct Solver {
@@ -1433,27 +1433,21 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       else vcycle<double>(S, vj, zj);
       apply_op(S, adjoint, zj, w);
       const int kc = j + 1;
-      // classical Gram-Schmidt, twice: h1 = V^T w, w -= V h1, h2 = V^T w, w -= V h2
+      // h1 = V^T w; c = (2I - G) h1 (its correction d = c - h1 into h2's slot,
+      // where the host adds it); w <- w - V c with V^T w (the next Gram row)
+      // and ||w||^2 in the same read of V
       double* h1 = res;
       double* h2 = res + kc;
       double* nrm = res + 2 * kc;
-      const double* gdots = nullptr;  // V^T w_new when the pass took them (a Gram row), else the row is zero
-      const double* nrm_src = nrm;
       if (kc <= kFused) {
-        Prof p(S, PC_ORTHO, 8.0 * n * (3 * kc + 6));
+        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot(V, ld, kc, w, n, S.rw, h1, s);
-        launch_update_dot(V, ld, kc, h1, w, n, S.rw, h2, s);
-        launch_update_norm(V, ld, kc, h2, w, n, S.rw, nrm, s);
+        launch_update_gram(V, ld, kc, h1, S.gram.p, S.ldg, h2, w, n, S.rw, S.gdots.p, s);
       } else if (kc <= many_max()) {
-        // h1 = V^T w; c = (2I - G) h1 (its correction d = c - h1 into h2's
-        // slot, where the host adds it); w <- w - V c with V^T w and ||w||^2
-        // in the same read of V
         Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot_many(V, ld, kc, w, n, S.rw, h1, s);
         launch_gram_coef(kc, h1, S.gram.p, S.ldg, h2, S.gcoef.p, s);
         launch_update_dot_many(V, ld, kc, S.gcoef.p, w, n, true, S.rw, S.gdots.p, s);
-        gdots = S.gdots.p;
-        nrm_src = S.gdots.p + kc;
       } else {
         // the same projection over blocks of mm vectors: h1 block by block;
         // w -= V_b c_b for all blocks but the last, whose pass also takes its
@@ -1470,13 +1464,10 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
         launch_update_dot_many(V + (size_t)b0 * ld, ld, kl, S.gcoef.p + b0, w, n, true, S.rw, S.gdots.p + b0, s);
         for (int b = 0; b + 1 < nb; ++b)
           launch_multidot_many(V + (size_t)b * mm * ld, ld, mm, w, n, S.rw, S.gdots.p + b * mm, s);
-        gdots = S.gdots.p;
-        nrm_src = S.gdots.p + kc;
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
-        launch_normalize_gram(w, nrm_src, V + (size_t)(j + 1) * ld, n, j + 1, gdots, S.gram.p, S.ldg,
-                              nrm_src == nrm ? nullptr : nrm, s);
+        launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, S.gram.p, S.ldg, nrm, s);
       }
       d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, 2 * kc + 1, s);
       HIPCK(hipEventRecord(S.colev[j & 1], s));
@@ -1563,7 +1554,8 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
 // cost about what one column costs), the matrix, the aggregates and the
 // factors are read once per step for all columns, and the Krylov kernels run
 // one recurrence per column of their grid.
-constexpr int kBatchRS = 2 * kFused + 8;  // result doubles per column: h1, h2, ||w||^2
+constexpr int kBatchRS = 2 * kFused + 8;  // result doubles per column: h1, d, ||w||^2
+constexpr int kGramLd = kFused + 1;       // rows of a column's Gram matrix
 
 static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
   BatchWork& B = S.bw;
@@ -1611,6 +1603,8 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
     B.x.alloc(nf);
     B.b.alloc(nf);
     B.coef.alloc((size_t)B.cap * (B.m + 1));
+    B.gram.alloc((size_t)B.cap * kGramLd * kGramLd);
+    B.gdots.alloc((size_t)B.cap * kGramLd);
   }
   if (f32 && !B.f32) {
     const size_t nf = B.ld * B.cap, ncv = B.ldc * B.cap;
@@ -1804,7 +1798,9 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
   double* res = S.rw.result.p;
   double* hp = S.hpin;
   BatchResult out;
-  const BatchCols bcol{nb, ld, ld, (size_t)kBatchRS, (size_t)kBatchRS};
+  // coefficients and norms per column in res, products with w_new in gdots
+  const BatchCols bh{nb, ld, ld, (size_t)kBatchRS, 0, 0};
+  const BatchCols bg{nb, ld, ld, (size_t)kGramLd, (size_t)kBatchRS, (size_t)kGramLd * kGramLd};
   const DCsr& M = adjoint ? S.AT : S.A;
   launch_cols_from_rows(Bu, nrhs, c0, W.b.p, ld, n, nb, s);
   if (x0_given) launch_cols_from_rows(Xu, nrhs, c0, W.x.p, ld, n, nb, s);
@@ -1876,15 +1872,16 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
       }
       const int kc = j + 1;
       {
-        // classical Gram-Schmidt twice, every column in each launch
-        Prof p(S, PC_ORTHO, 8.0 * n * (3 * kc + 6) * nb);
-        launch_multidot(W.V.p, cap * ld, kc, W.w.p, n, S.rw, res, s, bcol);
-        launch_update_dot(W.V.p, cap * ld, kc, res, W.w.p, n, S.rw, res + kc, s, bcol);
-        launch_update_norm(W.V.p, cap * ld, kc, res + kc, W.w.p, n, S.rw, res + 2 * kc, s, bcol);
+        // the Gram-corrected projection of the single solve, every column in
+        // each launch
+        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) * nb);
+        launch_multidot(W.V.p, cap * ld, kc, W.w.p, n, S.rw, res, s, bh);
+        launch_update_gram(W.V.p, cap * ld, kc, res, W.gram.p, kGramLd, res + kc, W.w.p, n, S.rw, W.gdots.p, s, bg);
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16 * nb);
-        launch_normalize_cols(W.w.p, ld, res + 2 * kc, kBatchRS, W.V.p + (size_t)(j + 1) * cap * ld, ld, n, nb, s);
+        launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, W.gram.p, kGramLd,
+                              res + 2 * kc, s, bg);
       }
       d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, (size_t)nb * kBatchRS, s);
       HIPCK(hipEventRecord(S.colev[j & 1], s));

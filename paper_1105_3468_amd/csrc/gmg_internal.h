@@ -320,22 +320,22 @@ struct RedWork {  // scratch for deterministic two-level reductions
 void red_init(RedWork& rw, hipStream_t s);
 void red_reset(RedWork& rw, hipStream_t s);
 // Independent recurrences batched in one launch of the k <= 32 Krylov
-// kernels: column c (c < nb) works on V + c * vcol, w + c * wcol, h + c * hcol
-// and writes result + c * rcol.
+// kernels: column c (c < nb) works on V + c * vcol, w + c * wcol, the
+// coefficients h + c * hcol, the Gram matrix at c * gcol and writes
+// result + c * rcol.
 constexpr int KCOLS = 16;
 struct BatchCols {
   int nb = 1;
-  size_t vcol = 0, wcol = 0, rcol = 0, hcol = 0;
+  size_t vcol = 0, wcol = 0, rcol = 0, hcol = 0, gcol = 0;
 };
 // result[0..k) = V[0..k)^T w   (V rows with stride ld)
 void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t n,
                      RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
-// w -= V[0..k)^T h  (h device), then result[0..k) = V^T w_new
-void launch_update_dot(const double* V, size_t ld, int k, const double* h, double* w, int64_t n,
-                       RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
-// w -= V^T h, then result[0] = ||w||^2
-void launch_update_norm(const double* V, size_t ld, int k, const double* h, double* w, int64_t n,
-                        RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
+// c = (2I - G) h (d = c - h is stored), w -= V[0..k)^T c, then result[0..k) =
+// V^T w_new and result[k] = ||w_new||^2
+void launch_update_gram(const double* V, size_t ld, int k, const double* h, const double* gram, size_t ldg, double* d,
+                        double* w, int64_t n, RedWork& rw, double* result, hipStream_t s,
+                        const BatchCols& bc = BatchCols());
 // any k (<= 2048): w -= V^T h (h device); if want_norm, result[0] = ||w_new||^2
 // Many-vector passes (up to many_max() vectors): result[0..k) = V^T w, and
 // w <- w - V h with result[0..k) = V^T w_new (and result[k] = ||w_new||^2
@@ -350,11 +350,12 @@ void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, 
 // basis' loss of orthogonality, as a second Gram-Schmidt pass would give
 void launch_gram_coef(int kc, const double* h, const double* gram, size_t ldg, double* d, double* c,
                       hipStream_t s);
-// y = x / sqrt(*nrm2) (zero when *nrm2 is zero), and the Gram row of y:
-// G[row][i] = G[i][row] = dots[i] / sqrt(*nrm2) (i < row; zeros if dots is
-// null), G[row][row] = 1; *nrm2_out = *nrm2 when nrm2_out is not null
-void launch_normalize_gram(const double* x, const double* nrm2, double* y, int64_t n, int row, const double* dots,
-                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s);
+// y = x / sqrt(nrm2) (zero when it is zero) with nrm2 = dots[row], and the Gram
+// row of y: G[row][i] = G[i][row] = dots[i] / sqrt(nrm2) (i < row),
+// G[row][row] = 1; *nrm2_out = nrm2.  Batch: x at wcol, y at vcol, dots at
+// rcol, G at gcol, nrm2_out at hcol
+void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, double* gram, size_t ldg,
+                           double* nrm2_out, hipStream_t s, const BatchCols& bc = BatchCols());
 void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                         RedWork& rw, double* result, hipStream_t s);
 // result[0] = ||x||^2

@@ -1,12 +1,14 @@
-// Krylov-subspace vector kernels of FGMRES: block multi-dot products, the two
-// fused classical Gram-Schmidt passes (CGS2), norms, scaling and the solution
-// update.  Reductions are deterministic: every block writes its partial sums
+// Krylov-subspace vector kernels of FGMRES: block multi-dot products, the
+// Gram-corrected projection (two reads of the basis per step), norms, scaling
+// and the solution update.  Reductions are deterministic: every block writes its partial sums
 // in a fixed order and the last block to finish adds the partials in block
 // order (no floating-point atomics), so repeated runs are bitwise identical.
 // The partials are published like the sweeps' results: relaxed agent-scope
 // stores into a buffer reset to a NaN sentinel, polled by the last block,
 // which resets them again.  No fence is needed; an agent-scope fence writes
 // the whole L2 back and cost ~40 us per launch here.
+#include <algorithm>
+
 #include "gmg_internal.h"
 #include "kcommon.h"
 
@@ -15,6 +17,7 @@ namespace gmg {
 constexpr int KB = 256;          // threads per block
 constexpr int KGRID = 512;       // blocks of the reduction kernels
 constexpr int KMAX = 32;         // vectors per fused register-resident pass
+constexpr int KPART = KMAX + 1;  // partial sums per block: a product per vector and a norm
 constexpr int KLDS = 2048;       // vectors per LDS-staged pass (longest basis)
 // many-vector passes (a basis longer than KMAX)
 constexpr int MKB = 512;          // threads per block
@@ -50,7 +53,7 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[K], int kcount,
 #pragma unroll
     for (int w = 0; w < KB / 64; ++w) s += sh[w][threadIdx.x];
     if (is_sentinel(s)) s = __builtin_nan("");
-    st_agent(&partial[(size_t)blockIdx.x * KMAX + threadIdx.x], s);
+    st_agent(&partial[(size_t)blockIdx.x * KPART + threadIdx.x], s);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -75,7 +78,7 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[K], int kcount,
 #pragma unroll
           for (int u = 0; u < 16; ++u) {
             const unsigned b = b0 + u * NP;
-            v[u] = b < gridDim.x ? ld_agent(pp + (size_t)b * KMAX) : 0.0;
+            v[u] = b < gridDim.x ? ld_agent(pp + (size_t)b * KPART) : 0.0;
           }
 #pragma unroll
           for (int u = 0; u < 16; ++u) {
@@ -86,10 +89,10 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[K], int kcount,
               while (is_sentinel(v[u])) {
                 if (++spins > (1u << 22)) { v[u] = __builtin_nan(""); break; }  // bounded
                 __builtin_amdgcn_s_sleep(1);
-                v[u] = ld_agent(pp + (size_t)b * KMAX);
+                v[u] = ld_agent(pp + (size_t)b * KPART);
               }
               s += v[u];
-              st_agent(pp + (size_t)b * KMAX, sentinel_of<double>(0));
+              st_agent(pp + (size_t)b * KPART, sentinel_of<double>(0));
             }
           }
         }
@@ -117,12 +120,24 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[K], int kcount,
     V += col_ * vcol;                                     \
     w += col_ * wcol;                                     \
     result += col_ * rcol;                                \
-    partial += col_ * (size_t)KGRID * KMAX;               \
+    partial += col_ * (size_t)KGRID * KPART;               \
     counter += col_;                                      \
   } while (0)
 
+// Two rows per lane and 16-byte loads; vectors start on 64-row boundaries, and
+// their padding is loaded but never counted.
+__device__ __forceinline__ double2 ld2(const double* p) { return *reinterpret_cast<const double2*>(p); }
+
+// a value that all lanes share, in scalar registers (32 coefficients in vector
+// registers do not fit beside 32 rows of the basis)
+__device__ __forceinline__ double uniform(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 template <int K>
-__global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, size_t ld, int kc,
+__global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, size_t ld,
                                                  const double* __restrict__ w, int64_t n, double* partial,
                                                  unsigned* counter, double* result, size_t vcol, size_t wcol,
                                                  size_t rcol) {
@@ -130,79 +145,92 @@ __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, s
   double acc[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) acc[k] = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)KB + threadIdx.x; i < n; i += (int64_t)gridDim.x * KB) {
-    const double wi = w[i];
-    double v[K];
+  for (int64_t i = 2 * (blockIdx.x * (int64_t)KB + threadIdx.x); i < n; i += 2 * (int64_t)gridDim.x * KB) {
+    const double2 wi = ld2(w + i);
+    double2 v[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = V[k * ld + i];
+    for (int k = 0; k < K; ++k) v[k] = ld2(V + k * ld + i);
     ALL_LOADS_ISSUED();
+    if (i + 1 < n) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += v[k] * wi;
+      for (int k = 0; k < K; ++k) acc[k] += v[k].x * wi.x + v[k].y * wi.y;
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k) acc[k] += v[k].x * wi.x;
+    }
   }
-  block_reduce_store<K>(acc, kc, partial, counter, result);
+  block_reduce_store<K>(acc, K, partial, counter, result);
 }
 
-// w <- w - sum_k h[k] V[k]; result[k] = V[k] . w_new
+// w <- w - sum_k c[k] V[k]; result[k] = V[k] . w_new, result[K] = ||w_new||^2.
+// c = h + d, d_i = -sum_{l != i} G[i][l] h[l] with the basis' Gram matrix G
+// (k_gram_coef says why); every block forms it for itself, block 0 stores d.
+// The products with w_new are the Gram row of the next basis vector, so a
+// step reads the basis twice.  A second Gram-Schmidt pass in its place read
+// it a third time: 27 vectors of 16 columns of 262k rows took 201 + 194 + 181
+// us in three passes.
 template <int K>
-__global__ __launch_bounds__(KB) void k_update_dot(const double* __restrict__ V, size_t ld, int kc,
-                                                   const double* __restrict__ h, double* __restrict__ w,
-                                                   int64_t n, double* partial, unsigned* counter,
-                                                   double* result, size_t vcol, size_t wcol, size_t rcol,
-                                                   size_t hcol) {
+__global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V, size_t ld,
+                                                    const double* __restrict__ h, const double* __restrict__ gram,
+                                                    size_t ldg, double* __restrict__ d, double* __restrict__ w,
+                                                    int64_t n, double* partial, unsigned* counter, double* result,
+                                                    size_t vcol, size_t wcol, size_t rcol, size_t hcol, size_t gcol) {
   KRYLOV_COLUMN();
   h += blockIdx.y * hcol;
-  double acc[K], hk[K];
+  d += blockIdx.y * hcol;
+  gram += blockIdx.y * gcol;
+  __shared__ double hs[K], cs[K];
+  if (threadIdx.x < K) hs[threadIdx.x] = h[threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x < K) {
+    double g[K], t = 0.0;
 #pragma unroll
-  for (int k = 0; k < K; ++k) { acc[k] = 0.0; hk[k] = h[k]; }
-  for (int64_t i = blockIdx.x * (int64_t)KB + threadIdx.x; i < n; i += (int64_t)gridDim.x * KB) {
-    double v[K];
-    double s = w[i];
+    for (int l = 0; l < K; ++l) g[l] = gram[(size_t)l * ldg + threadIdx.x];  // symmetric
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = V[k * ld + i];
+    for (int l = 0; l < K; ++l)
+      if (l != (int)threadIdx.x) t += g[l] * hs[l];
+    cs[threadIdx.x] = hs[threadIdx.x] + (-t);
+    if (blockIdx.x == 0) d[threadIdx.x] = -t;
+  }
+  __syncthreads();
+  double acc[K + 1], ck[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) { acc[k] = 0.0; ck[k] = uniform(cs[k]); }
+  acc[K] = 0.0;
+  for (int64_t i = 2 * (blockIdx.x * (int64_t)KB + threadIdx.x); i < n; i += 2 * (int64_t)gridDim.x * KB) {
+    double2 v[K];
+    double2 s = ld2(w + i);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = ld2(V + k * ld + i);
     ALL_LOADS_ISSUED();
 #pragma unroll
-    for (int k = 0; k < K; ++k) s -= hk[k] * v[k];
-    w[i] = s;
+    for (int k = 0; k < K; ++k) {
+      s.x -= ck[k] * v[k].x;
+      s.y -= ck[k] * v[k].y;
+    }
+    if (i + 1 < n) {
+      *reinterpret_cast<double2*>(w + i) = s;
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += v[k] * s;
+      for (int k = 0; k < K; ++k) acc[k] += v[k].x * s.x + v[k].y * s.y;
+      acc[K] += s.x * s.x + s.y * s.y;
+    } else {
+      w[i] = s.x;
+#pragma unroll
+      for (int k = 0; k < K; ++k) acc[k] += v[k].x * s.x;
+      acc[K] += s.x * s.x;
+    }
   }
-  block_reduce_store<K>(acc, kc, partial, counter, result);
-}
-
-// w <- w - sum_k h[k] V[k]; result[0] = ||w_new||^2
-template <int K>
-__global__ __launch_bounds__(KB) void k_update_norm(const double* __restrict__ V, size_t ld, int kc,
-                                                    const double* __restrict__ h, double* __restrict__ w,
-                                                    int64_t n, double* partial, unsigned* counter,
-                                                    double* result, size_t vcol, size_t wcol, size_t rcol,
-                                                    size_t hcol) {
-  KRYLOV_COLUMN();
-  h += blockIdx.y * hcol;
-  double acc[1] = {0.0}, hk[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) hk[k] = h[k];
-  for (int64_t i = blockIdx.x * (int64_t)KB + threadIdx.x; i < n; i += (int64_t)gridDim.x * KB) {
-    double v[K];
-    double s = w[i];
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = V[k * ld + i];
-    ALL_LOADS_ISSUED();
-#pragma unroll
-    for (int k = 0; k < K; ++k) s -= hk[k] * v[k];
-    w[i] = s;
-    acc[0] += s * s;
-  }
-  block_reduce_store<1>(acc, 1, partial, counter, result);
+  block_reduce_store<K + 1>(acc, K + 1, partial, counter, result);
 }
 
 void red_init(RedWork& rw, hipStream_t s) {
   rw.blocks = KGRID;
-  rw.partial.alloc((size_t)KGRID * KMAX * KCOLS);
+  rw.partial.alloc((size_t)KGRID * KPART * KCOLS);
   rw.counter.alloc(KCOLS);
   rw.result.alloc(2 * KLDS + 8);
   rw.mpart.alloc((size_t)MGRID * MSTR);
   launch_fill_u32(rw.counter.p, 0u, KCOLS, s);
-  launch_fill_f64_bits(rw.partial.p, SENT64, (size_t)KGRID * KMAX * KCOLS, s);
+  launch_fill_f64_bits(rw.partial.p, SENT64, (size_t)KGRID * KPART * KCOLS, s);
 }
 
 // Back to the state red_init leaves (every partial the sentinel, counters
@@ -210,12 +238,17 @@ void red_init(RedWork& rw, hipStream_t s) {
 // ran out): a partial that lands later must not be read by the next one.
 void red_reset(RedWork& rw, hipStream_t s) {
   launch_fill_u32(rw.counter.p, 0u, KCOLS, s);
-  launch_fill_f64_bits(rw.partial.p, SENT64, (size_t)KGRID * KMAX * KCOLS, s);
+  launch_fill_f64_bits(rw.partial.p, SENT64, (size_t)KGRID * KPART * KCOLS, s);
 }
 
-static unsigned red_grid(int64_t n) {
-  int64_t g = (n + KB - 1) / KB;
-  if (g > KGRID) g = KGRID;
+// Blocks of a reduction over n rows in nb columns: two rows a lane, at most
+// KGRID blocks a column and, for a batch, four blocks a CU in all (every block
+// ends with a reduction per vector: 16 columns of 262k rows in 512 blocks each
+// spent most of their time there).
+static unsigned red_grid(int64_t n, int nb = 1) {
+  int64_t g = (n + 2 * KB - 1) / (2 * KB);
+  const int64_t cap = nb > 1 ? std::max(32, 1024 / nb) : KGRID;
+  if (g > cap) g = cap;
   if (g < 1) g = 1;
   return (unsigned)g;
 }
@@ -243,24 +276,16 @@ void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t
                      double* result, hipStream_t s, const BatchCols& bc) {
   if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "multidot: bad vector count");
   check_cols(bc);
-  GMG_DISPATCH_K(k, k_multidot, dim3(red_grid(n), bc.nb), dim3(KB), 0, s, V, ld, k, w, n, rw.partial.p,
+  GMG_DISPATCH_K(k, k_multidot, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, w, n, rw.partial.p,
                  rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol);
   HIPCK(hipGetLastError());
 }
-void launch_update_dot(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
-                       double* result, hipStream_t s, const BatchCols& bc) {
-  if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update_dot: bad vector count");
+void launch_update_gram(const double* V, size_t ld, int k, const double* h, const double* gram, size_t ldg, double* d,
+                        double* w, int64_t n, RedWork& rw, double* result, hipStream_t s, const BatchCols& bc) {
+  if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update_gram: bad vector count");
   check_cols(bc);
-  GMG_DISPATCH_K(k, k_update_dot, dim3(red_grid(n), bc.nb), dim3(KB), 0, s, V, ld, k, h, w, n, rw.partial.p,
-                 rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol, bc.hcol);
-  HIPCK(hipGetLastError());
-}
-void launch_update_norm(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
-                        double* result, hipStream_t s, const BatchCols& bc) {
-  if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update_norm: bad vector count");
-  check_cols(bc);
-  GMG_DISPATCH_K(k, k_update_norm, dim3(red_grid(n), bc.nb), dim3(KB), 0, s, V, ld, k, h, w, n, rw.partial.p,
-                 rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol, bc.hcol);
+  GMG_DISPATCH_K(k, k_update_gram, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, h, gram, ldg, d, w, n,
+                 rw.partial.p, rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol, bc.hcol, bc.gcol);
   HIPCK(hipGetLastError());
 }
 
@@ -268,7 +293,7 @@ __global__ __launch_bounds__(KB) void k_norm2(const double* __restrict__ x, int6
                                               unsigned* counter, double* result, size_t xcol, size_t rcol) {
   x += blockIdx.y * xcol;
   result += blockIdx.y * rcol;
-  partial += blockIdx.y * (size_t)KGRID * KMAX;
+  partial += blockIdx.y * (size_t)KGRID * KPART;
   counter += blockIdx.y;
   double acc[1] = {0.0};
   for (int64_t i = blockIdx.x * (int64_t)KB + threadIdx.x; i < n; i += (int64_t)gridDim.x * KB) {
@@ -280,7 +305,7 @@ __global__ __launch_bounds__(KB) void k_norm2(const double* __restrict__ x, int6
 void launch_norm2(const double* x, int64_t n, RedWork& rw, double* result, hipStream_t s, int nb, size_t xcol,
                   size_t rcol) {
   if (nb < 1 || nb > KCOLS) fail(GMG_ERR_INVALID_ARG, "norm2: bad column count");
-  hipLaunchKernelGGL(k_norm2, dim3(red_grid(n), nb), dim3(KB), 0, s, x, n, rw.partial.p, rw.counter.p, result, xcol,
+  hipLaunchKernelGGL(k_norm2, dim3(red_grid(n, nb), nb), dim3(KB), 0, s, x, n, rw.partial.p, rw.counter.p, result, xcol,
                      rcol);
   HIPCK(hipGetLastError());
 }
@@ -318,39 +343,44 @@ void launch_scale(const double* x, double a, double* y, int64_t n, hipStream_t s
   HIPCK(hipGetLastError());
 }
 
-// y = x / sqrt(*nrm2) (zero when the norm is zero), and the basis' Gram
-// matrix row `row` (and its mirror column) for the new vector y: block 0
-// stores G[row][i] = (V[i] . x) / ||x|| for i < row from the products `dots`
-// taken while x was formed (zeros when dots is null: a vector orthogonalised
-// by two full passes) and G[row][row] = 1, and copies *nrm2 to nrm2_out when
-// that is not null.
-__global__ void k_normalize_gram(const double* __restrict__ x, const double* __restrict__ nrm2,
-                                 double* __restrict__ y, int64_t n, int row, const double* __restrict__ dots,
-                                 double* __restrict__ gram, size_t ldg, double* __restrict__ nrm2_out) {
-  const double nv = *nrm2;
+// y = x / sqrt(nrm2) (zero when the norm is zero), and the basis' Gram matrix
+// row `row` (and its mirror column) for the new vector y: block 0 stores
+// G[row][i] = (V[i] . x) / ||x|| for i < row from the products dots[0..row)
+// taken while x was formed, and G[row][row] = 1; nrm2 = dots[row] goes to
+// *nrm2_out.  Column blockIdx.y of a batch.
+__global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
+                                 const double* __restrict__ dots, double* __restrict__ gram, size_t ldg,
+                                 double* __restrict__ nrm2_out, size_t xcol, size_t ycol, size_t dcol, size_t gcol,
+                                 size_t rcol) {
+  x += blockIdx.y * xcol;
+  y += blockIdx.y * ycol;
+  dots += blockIdx.y * dcol;
+  gram += blockIdx.y * gcol;
+  const double nv = dots[row];
   const double hn = sqrt(nv);
   const double a = hn != 0.0 ? 1.0 / hn : 0.0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = a * x[i];
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < row; i += blockDim.x) {
-      const double gv = dots ? dots[i] * a : 0.0;
+      const double gv = dots[i] * a;
       gram[(size_t)row * ldg + i] = gv;
       gram[(size_t)i * ldg + row] = gv;
     }
     if (threadIdx.x == 0) {
       gram[(size_t)row * ldg + row] = 1.0;
-      if (nrm2_out) *nrm2_out = nv;
+      nrm2_out[blockIdx.y * rcol] = nv;
     }
   }
 }
-void launch_normalize_gram(const double* x, const double* nrm2, double* y, int64_t n, int row, const double* dots,
-                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s) {
+void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, double* gram, size_t ldg,
+                           double* nrm2_out, hipStream_t s, const BatchCols& bc) {
   if (n <= 0) return;
+  check_cols(bc);
   int64_t g = (n + 255) / 256;
-  if (g > 8192) g = 8192;
-  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g), dim3(256), 0, s, x, nrm2, y, n, row, dots, gram, ldg,
-                     nrm2_out);
+  if (g > 8192 / bc.nb) g = 8192 / bc.nb;
+  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots, gram, ldg,
+                     nrm2_out, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
   HIPCK(hipGetLastError());
 }
 
