@@ -479,7 +479,6 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   constexpr int kHelperEntries = 256, kHelperRows = 32;
   constexpr int kSliceLgRows = 4;             // rows per slice of a node above 64 rows: 16
   constexpr int kWideRows = 1024, kWideLgRows = 3;  // rows per slice of a node of 1024 rows or more: 8
-  constexpr size_t kSmallInvLds = 40 * 1024;  // inversion chunks launched with this much LDS or less first
   const int nn = (int)tree.size();
   if (nn == 0 || n <= 0) return false;
   std::vector<int> node_of(n, -1), nlo(nn), nsz(nn);
@@ -589,17 +588,22 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     for (int q = 0; q < nsl; ++q)
       task.insert(task.end(), {1, d.lo, sz, q * R, std::min(sz, (q + 1) * R), k, (has_ext ? 1 : 0) | lgR << 1, nsl});
   }
-  // inversion tasks: W-column chunks of every node, small-LDS ones first
+  // inversion tasks: the diagonal blocks of every node, then the columns of
+  // the nodes of several blocks, those with the most blocks to form first
   std::vector<int> itask[2];
-  size_t ilds[2] = {0, 0};
   for (int k = 0; k < nn; ++k) {
     const int sz = tree[k].hi - tree[k].lo;
-    if (sz == 0) continue;
-    const int lgW = tree_inv_width(sz);
-    const size_t need = tree_inv_lds(sz, lgW);
-    const int cls = need <= kSmallInvLds ? 0 : 1;
-    ilds[cls] = std::max(ilds[cls], need);
-    for (int c0 = 0; c0 < sz; c0 += 1 << lgW) itask[cls].insert(itask[cls].end(), {tree[k].lo, sz, c0, k, lgW, 0, 0, 0});
+    for (int b0 = 0; b0 < sz; b0 += kTreeInvBlock)
+      itask[0].insert(itask[0].end(), {tree[k].lo + b0, sz, b0, std::min(kTreeInvBlock, sz - b0), k, 0, 0, 0});
+  }
+  std::vector<int> wide;
+  for (int k = 0; k < nn; ++k)
+    if (nsz[k] > kTreeInvBlock) wide.push_back(k);
+  std::stable_sort(wide.begin(), wide.end(), [&](int x, int y) { return nsz[x] > nsz[y]; });
+  for (int k : wide) {
+    const int sz = nsz[k], ncol = (sz + kTreeInvCols - 1) / kTreeInvCols;
+    for (int q = 0; q < ncol; ++q)
+      itask[1].insert(itask[1].end(), {sz, (lower ? q : ncol - 1 - q) * kTreeInvCols, k, 0, 0, 0, 0, 0});
   }
   ts.lower = lower;
   ts.has_diag = dinv != nullptr;
@@ -660,9 +664,9 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
       if (itask[c].empty()) continue;
       dit[c].alloc(itask[c].size());
       h2d(dit[c].p, itask[c].data(), itask[c].size(), s);
-      launch_tree_invert(ts, dit[c].p, (int)itask[c].size() / 8, ilds[c], dblk.p, dinv ? ddinv.p : nullptr,
-                         ts.inv.p, s);
     }
+    launch_tree_invert(ts, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, dblk.p,
+                       dinv ? ddinv.p : nullptr, ts.inv.p, s);
     launch_cast_f32(ts.eval.p, ts.eval32.p, ne, s);
     launch_cast_f32(ts.inv.p, ts.inv32.p, total, s);
     HIPCK(hipStreamSynchronize(s));  // host vectors and staging buffers go out of scope

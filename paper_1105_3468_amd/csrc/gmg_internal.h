@@ -199,19 +199,18 @@ struct TreeSolve {
 template <class T>
 void launch_tree(const TreeSolve& ts, const void* rhs, bool rhs_is_f64, T* out, T* reset_rhs, T* ext,
                  int* abort_flag, hipStream_t s, int nb = 1, size_t ld = 0, int* ncount = nullptr);
-// Setup: inverses of the diagonal blocks blk (same layout as inv) into inv,
-// one workgroup per task (8 ints: lo, s, c0, node, log2 W; a chunk of W
-// columns of one node), with `lds` bytes of LDS (tree_inv_lds of each task,
-// at most kTreeInvLds).
-constexpr size_t kTreeInvLds = 128 * 1024;
+// Setup: inverses of the diagonal blocks blk (same layout as inv, zeroed
+// beforehand) into inv.  dtask: a task of 8 ints per kTreeInvBlock rows of a
+// node (first row of the factor, the node's rows, first row in the node, rows,
+// node); otask: one per kTreeInvCols columns of a node with more rows than
+// that (the node's rows, first column, node).
+constexpr int kTreeInvBlock = 64, kTreeInvCols = 16;
 // Setup: dense diagonal blocks (zeroed beforehand) and outside-entry lists of
 // a factor whose row r holds entries [rp[r] + skip, rp[r+1]).
 void launch_tree_fill(int n, const int* rp, const int* ci, const double* v, int skip, const int* node_of,
                       const int* nlo, const int* nsz, const int64_t* boff, const int* erp, double* blk, int* ecol,
                       double* eval, hipStream_t s);
-size_t tree_inv_lds(int rows, int lgW);
-int tree_inv_width(int rows);
-void launch_tree_invert(const TreeSolve& ts, const int* itask, int ntask, size_t lds, const double* blk,
+void launch_tree_invert(const TreeSolve& ts, const int* dtask, int ndiag, const int* otask, int noff, const double* blk,
                         const double* dinv, double* inv, hipStream_t s);
 
 // Per-kernel-class profiling with events.
