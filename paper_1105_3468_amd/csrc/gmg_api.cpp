@@ -471,25 +471,101 @@ static std::vector<NdNode> split_tree(const std::vector<NdNode>& t, int max_rows
   return out;
 }
 
+// The tree with every subtree of at most `rows` rows made one node (its rows
+// are consecutive: a node is numbered after its descendants).  Fewer levels to
+// cross, larger dense inverses to read.  Node 0 stays the root.
+static std::vector<NdNode> merge_tree(const std::vector<NdNode>& t, int rows) {
+  const int nn = (int)t.size();
+  // children before parents: by height (a parent's exceeds its children's)
+  std::vector<int> order(nn);
+  for (int k = 0; k < nn; ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return t[x].height < t[y].height; });
+  std::vector<int> sub(nn, 0), first(nn, INT32_MAX), last(nn, 0);  // rows of the subtree, and where they lie
+  for (int k : order) {
+    sub[k] += t[k].hi - t[k].lo;
+    if (t[k].hi > t[k].lo) {
+      first[k] = std::min(first[k], t[k].lo);
+      last[k] = std::max(last[k], t[k].hi);
+    }
+    const int p = t[k].parent;
+    if (p < 0) continue;
+    sub[p] += sub[k];
+    first[p] = std::min(first[p], first[k]);
+    last[p] = std::max(last[p], last[k]);
+  }
+  auto whole = [&](int k) { return sub[k] > 0 && sub[k] <= rows && last[k] - first[k] == sub[k]; };
+  std::vector<int> id(nn, -1);
+  std::vector<NdNode> out;
+  for (int q = nn - 1; q >= 0; --q) {  // parents before children
+    const int k = order[q], p = t[k].parent;
+    if (p >= 0 && (id[p] < 0 || whole(p))) continue;  // inside a merged subtree
+    id[k] = (int)out.size();
+    if (whole(k)) out.push_back({first[k], last[k], p < 0 ? -1 : id[p], 0});
+    else out.push_back({t[k].lo, t[k].hi, p < 0 ? -1 : id[p], 0});
+  }
+  for (int k = (int)out.size() - 1; k > 0; --k)
+    out[out[k].parent].height = std::max(out[out[k].parent].height, out[k].height + 1);
+  return out;
+}
+
+// The tree a factor is laid out over: the dissection tree with its small
+// subtrees merged.  A level costs its two hand-overs (helper, slice), about 3
+// us whatever it holds; every byte of the dense inverses' triangles costs a
+// read (1.2 TB/s in a solve of one column of this size, with batches between).
+// A merge pays while the levels it saves outweigh the bytes it adds, which
+// holds for small factors only.  Microseconds a solve, none / 256 / 512 / 1024
+// rows merged, one column (16 columns): N_c = 657 17.7 / 11.8 / 9.7 / 7.4
+// (16.8 / 12.3 / 11.0 / 13.2); 1636 22.0 / 15.9 / 13.6 / 12.9 (23.8 / 19.3 /
+// 18.5 / 20.9); 3191 26.2 / 20.1 / 17.9 / 17.0 (30.1 / 29.6 / 29.8 / 33.8);
+// 14799 36.1 / 32.8 / 34.0 / 37.9 (72 / 92 / 105 / 131).
+static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
+  constexpr double kLevelUs = 3.0, kBytesPerUs = 1.2e6;
+  constexpr int kMergeNc = 4096, kMergeRows = 1024;
+  std::vector<NdNode> best = split_tree(tree_in, kTreeMaxRows);
+  auto cost = [&](const std::vector<NdNode>& t) {
+    double bytes = 0.0;
+    int h = 0;
+    for (const NdNode& d : t) {
+      const double s = d.hi - d.lo;
+      bytes += 4.0 * s * s;
+      h = std::max(h, d.height);
+    }
+    return kLevelUs * (h + 1) + bytes / kBytesPerUs;
+  };
+  int n = 0;
+  for (const NdNode& d : best) n += d.hi - d.lo;
+  if (n > kMergeNc) return best;
+  double least = cost(best);
+  const std::vector<NdNode> whole = best;
+  for (int rows = 128; rows <= kMergeRows; rows *= 2) {
+    std::vector<NdNode> t = merge_tree(whole, rows);
+    const double c = cost(t);
+    if (c < least) {
+      least = c;
+      best = std::move(t);
+    }
+  }
+  return best;
+}
+
 static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n, const std::vector<int>& rp,
                        const std::vector<int>& ci, const std::vector<int>* src, int skip,
                        const std::vector<double>& vals, bool lower, const std::vector<double>* dinv,
                        hipStream_t s) {
-  const std::vector<NdNode> tree = split_tree(tree_in, kTreeMaxRows);
+  const std::vector<NdNode> tree = solve_tree(tree_in);
   constexpr int kHelperEntries = 256, kHelperRows = 32;
   constexpr int kSliceLgRows = 4;             // rows per slice of a node above 64 rows: 16
   constexpr int kWideRows = 1024, kWideLgRows = 3;  // rows per slice of a node of 1024 rows or more: 8
   const int nn = (int)tree.size();
   if (nn == 0 || n <= 0) return false;
   std::vector<int> node_of(n, -1), nlo(nn), nsz(nn);
-  int max_rows = 0, max_h = 0;
+  int max_rows = 0;
   for (int k = 0; k < nn; ++k) {
     const NdNode& d = tree[k];
     if (d.hi - d.lo > kTreeMaxRows) return false;
     nlo[k] = d.lo;
     nsz[k] = d.hi - d.lo;
     max_rows = std::max(max_rows, d.hi - d.lo);
-    max_h = std::max(max_h, d.height);
     for (int r = d.lo; r < d.hi; ++r) node_of[r] = k;
   }
   for (int r = 0; r < n; ++r)
@@ -609,7 +685,8 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   ts.has_diag = dinv != nullptr;
   ts.ntasks = (int)task.size() / 8;
   ts.max_rows = max_rows;
-  ts.heights = max_h + 1;
+  ts.heights = 1;  // depth of the dissection tree itself
+  for (const NdNode& d : split_tree(tree_in, kTreeMaxRows)) ts.heights = std::max(ts.heights, d.height + 1);
   const size_t ne = (size_t)erp[n];
   const size_t nent = (size_t)rp[n];
   ts.task.alloc(task.size());
