@@ -56,7 +56,6 @@ struct BatchWork {
   bool f32 = false, adj = false;
   DBuf<double> t, rc, yc, ec, wz, wy, wt, text, y;                 // FP64 cycle (y: level sweeps)
   DBuf<float> t32, rc32, yc32, ec32, wz32, wy32, wt32, text32, y32;  // FP32 cycle
-  DBuf<int> ncLc, ncUc, ncUct, ncLct;                              // tree node counters per column
   DBuf<double> abc, auc, aec, as, at;                              // adjoint cycle
   DBuf<double> r;                                                  // fine residuals before the restriction
   DBuf<float> r32;
@@ -510,17 +509,15 @@ static std::vector<NdNode> merge_tree(const std::vector<NdNode>& t, int rows) {
 
 // The tree a factor is laid out over: the dissection tree with its small
 // subtrees merged.  A level costs its two hand-overs (helper, slice), about 3
-// us whatever it holds; every byte of the dense inverses' triangles costs a
-// read (1.2 TB/s in a solve of one column of this size, with batches between).
-// A merge pays while the levels it saves outweigh the bytes it adds, which
-// holds for small factors only.  Microseconds a solve, none / 256 / 512 / 1024
-// rows merged, one column (16 columns): N_c = 657 17.7 / 11.8 / 9.7 / 7.4
-// (16.8 / 12.3 / 11.0 / 13.2); 1636 22.0 / 15.9 / 13.6 / 12.9 (23.8 / 19.3 /
-// 18.5 / 20.9); 3191 26.2 / 20.1 / 17.9 / 17.0 (30.1 / 29.6 / 29.8 / 33.8);
-// 14799 36.1 / 32.8 / 34.0 / 37.9 (72 / 92 / 105 / 131).
+// us whatever it holds; the bytes of the dense inverses' triangles cost their
+// read, at about 1.2 TB/s in solves of this size.  A merge pays while the
+// levels it saves outweigh the bytes it adds, which ends it near 20k rows.
+// Microseconds a solve without and with merging, one column (16 columns):
+// N_c = 657 17.4, 7.3; 3087 26.1, 18.0 (33.2, 23.4); 7751 30.6, 25.5 (40.3,
+// 35.0); 14799 36.4, 33.0 (56.3, 52.6); in 3D 9788 42.7, 36.3 (63.3, 54.9).
 static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
   constexpr double kLevelUs = 3.0, kBytesPerUs = 1.2e6;
-  constexpr int kMergeNc = 4096, kMergeRows = 1024;
+  constexpr int kMergeRows = 1024;
   std::vector<NdNode> best = split_tree(tree_in, kTreeMaxRows);
   auto cost = [&](const std::vector<NdNode>& t) {
     double bytes = 0.0;
@@ -532,9 +529,6 @@ static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
     }
     return kLevelUs * (h + 1) + bytes / kBytesPerUs;
   };
-  int n = 0;
-  for (const NdNode& d : best) n += d.hi - d.lo;
-  if (n > kMergeNc) return best;
   double least = cost(best);
   const std::vector<NdNode> whole = best;
   for (int rows = 128; rows <= kMergeRows; rows *= 2) {
@@ -554,6 +548,11 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
                        hipStream_t s) {
   const std::vector<NdNode> tree = solve_tree(tree_in);
   constexpr int kHelperEntries = 256, kHelperRows = 32;
+  // helpers of the solve of several columns (of 4 or 8; of 16): entries and
+  // rows at most, and the entries beyond which a row gets the whole workgroup
+  // (two rounds of a wave's loads at 16 columns).  64 entries at most, or 16
+  // rows, were slower on the 512^2 grid's 43k coarse rows, 256 everywhere.
+  constexpr struct { int entries, rows, wide; } kCols[2] = {{128, 8, 64}, {128, 4, 64}};
   constexpr int kSliceLgRows = 4;             // rows per slice of a node above 64 rows: 16
   constexpr int kWideRows = 1024, kWideLgRows = 3;  // rows per slice of a node of 1024 rows or more: 8
   const int nn = (int)tree.size();
@@ -622,7 +621,7 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
     return lower ? tree[x].height < tree[y].height : tree[x].height > tree[y].height;
   });
-  std::vector<int> task;
+  std::vector<int> task, ctask[2];
   int pair_open = -1;  // offset of a pair task whose second half is free
   for (int k : order) {
     const NdNode& d = tree[k];
@@ -643,8 +642,30 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
         r = r1;
       }
     }
-    // the node's slices: one for a leaf-sized block, else kSliceRows rows each
     const int sz = d.hi - d.lo;
+    // several columns: helpers over some rows, or over one long row; slices of
+    // four 16-row tiles for a leaf-sized block, else of one
+    for (int w = 0; w < 2; ++w) {
+      std::vector<int>& ct = ctask[w];
+      if (has_ext)
+        for (int r = d.lo; r < d.hi;) {
+          int ents = erp[r + 1] - erp[r], longest = ents, r1 = r + 1;
+          while (r1 < d.hi && r1 - r < kCols[w].rows && ents + erp[r1 + 1] - erp[r1] <= kCols[w].entries) {
+            const int e = erp[r1 + 1] - erp[r1];
+            ents += e;
+            longest = std::max(longest, e);
+            ++r1;
+          }
+          int lg = 0;
+          while ((1 << lg) * 8 < longest && lg < 4) ++lg;
+          ct.insert(ct.end(), {0, r, r1, r1 == r + 1 && longest > kCols[w].wide ? 1 : 0, lg, 0, 0, 0});
+          r = r1;
+        }
+      const int R2 = sz <= 64 ? 64 : 16, n2 = (sz + R2 - 1) / R2;
+      for (int q = 0; q < n2; ++q)
+        ct.insert(ct.end(), {1, d.lo, sz, q * R2, std::min(sz, (q + 1) * R2), k, has_ext ? 1 : 0, n2});
+    }
+    // the node's slices: one for a leaf-sized block, else kSliceRows rows each
     const int lgR = sz <= 64 ? 6 : sz >= kWideRows ? kWideLgRows : kSliceLgRows, R = 1 << lgR;
     const int nsl = (sz + R - 1) / R;
     if (lower && !has_ext && sz <= 64) {
@@ -690,6 +711,11 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   const size_t ne = (size_t)erp[n];
   const size_t nent = (size_t)rp[n];
   ts.task.alloc(task.size());
+  for (int w = 0; w < 2; ++w) {
+    ts.nctasks[w] = (int)ctask[w].size() / 8;
+    ts.ctask[w].alloc(ctask[w].size());
+    h2d(ts.ctask[w].p, ctask[w].data(), ctask[w].size(), s);
+  }
   ts.erp.alloc(n + 1);
   ts.ecol.alloc(ne > 0 ? ne : 1);
   ts.eval.alloc(ne > 0 ? ne : 1);
@@ -1671,13 +1697,6 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
       B.y.alloc(nf);
       launch_fill_f64_bits(B.y.p, kSent64, nf, s);
     }
-    auto counters = [&](DBuf<int>& c, const TreeSolve& t) {
-      if (!t.ncount.p) return;
-      c.alloc(t.ncount.n * B.cap);
-      launch_fill_u32(reinterpret_cast<unsigned*>(c.p), 0u, c.n, s);
-    };
-    counters(B.ncLc, S.tLc);
-    counters(B.ncUc, S.tUc);
     B.V.alloc(B.ld * B.cap * (B.m + 1));
     B.Z.alloc(B.ld * B.cap * B.m);
     B.w.alloc(nf);
@@ -1723,13 +1742,6 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
     launch_fill_f64_bits(B.auc.p, kSent64, ncv, s);
     launch_fill_f64_bits(B.aec.p, kSent64, ncv, s);
     launch_fill_f64_bits(B.at.p, kSent64, nf, s);
-    auto counters = [&](DBuf<int>& c, const TreeSolve& t) {
-      if (!t.ncount.p) return;
-      c.alloc(t.ncount.n * B.cap);
-      launch_fill_u32(reinterpret_cast<unsigned*>(c.p), 0u, c.n, s);
-    };
-    counters(B.ncUct, S.tUct);
-    counters(B.ncLct, S.tLct);
     B.adj = true;
   }
 }
@@ -1744,8 +1756,16 @@ static void reset_batch_buffers(Solver& S) {
     if (b->p) launch_fill_f64_bits(b->p, kSent64, b->n, s);
   for (DBuf<float>* b : {&B.t32, &B.yc32, &B.ec32, &B.text32, &B.wy32, &B.wt32, &B.y32})
     if (b->p) launch_fill_f32_bits(b->p, kSent32, b->n, s);
-  for (DBuf<int>* c : {&B.ncLc, &B.ncUc, &B.ncUct, &B.ncLct})
-    if (c->p) launch_fill_u32(reinterpret_cast<unsigned*>(c->p), 0u, c->n, s);
+  for (TreeSolve* t : {&S.tLc, &S.tUc, &S.tUct, &S.tLct})
+    if (t->ncount.p) launch_fill_u32(reinterpret_cast<unsigned*>(t->ncount.p), 0u, t->ncount.n, s);
+}
+
+// Layout of a batch's coarse vectors: rows of columns for the tree solves,
+// columns ldc apart for the coarse solves that take one at a time.
+static CoarseCols coarse_cols(bool tree, size_t ldc, int nb) {
+  if (!tree) return {1, ldc, 1};
+  const int cw = tree_cols(nb);
+  return {(size_t)cw, 1, cw};
 }
 
 // q_c = B~^{-1} z_c for the columns c < nb (z_c = z + c * ldz, q_c = q + c * ldq)
@@ -1760,6 +1780,8 @@ static void vcycle_batch(Solver& S, const double* z, size_t ldz, double* q, size
   T* ec = F32 ? (T*)B.ec32.p : (T*)B.ec.p;
   const T* Av = F32 ? (const T*)S.A.v32.p : (const T*)S.A.v.p;
   const size_t sz = sizeof(T), ld = B.ld, ldc = B.ldc;
+  const bool tree = S.opt.coarse_mode == 0 && S.tree;
+  const CoarseCols lc = coarse_cols(tree, ldc, nb);
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.L0, sz, 8, false) + sweep_bytes(S.U0, sz, sz, true)));
     launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, true, F32 ? (T*)B.wz32.p : (T*)B.wz.p, F32 ? (T*)B.wy32.p : (T*)B.wy.p,
@@ -1786,24 +1808,24 @@ static void vcycle_batch(Solver& S, const double* z, size_t ldz, double* q, size
                                      nb * ((double)S.n * (8 + 3 * sz + 4) + (double)S.nc * 2 * sz));
     T* r = F32 ? (T*)B.r32.p : (T*)B.r.p;
     launch_resid_fine_cols<T>(S.n, S.A.rp.p, S.A.ci.p, Av, t, ld, z, ldz, r, ld, nb, s);
-    launch_restrict_cols_t<T>(S.nc, S.aptr.p, S.amem.p, r, ld, rc, ec, ldc, nb, s);
+    launch_restrict_cols<T>(S.nc, S.aptr.p, S.amem.p, r, ld, rc, ec, lc, nb, s);
   }
-  if (S.opt.coarse_mode == 0 && S.tree) {
+  if (tree) {
     T* ext = F32 ? (T*)B.text32.p : (T*)B.text.p;
     {
       Prof p(S, PC_SWEEP_COARSE, nb * sweep_bytes(S.Lc, sz, sz, false));
-      launch_tree<T>(S.tLc, rc, false, yc, nullptr, ext, S.abort_flag.p, s, nb, ldc, B.ncLc.p);
+      launch_tree_cols<T>(S.tLc, rc, yc, nullptr, ext, S.abort_flag.p, s, lc.width);
     }
     {
       Prof p(S, PC_SWEEP_COARSE, nb * sweep_bytes(S.Uc, sz, sz, true));
-      launch_tree<T>(S.tUc, yc, false, ec, yc, ext, S.abort_flag.p, s, nb, ldc, B.ncUc.p);
+      launch_tree_cols<T>(S.tUc, yc, ec, yc, ext, S.abort_flag.p, s, lc.width);
     }
   } else {
     for (int c = 0; c < nb; ++c) coarse_apply<T>(S, rc + c * ldc, ec + c * ldc);
   }
   {
     Prof p(S, PC_PROLONG, nb * ((double)S.n * (4 + 2 * sz + 8) + (double)S.nc * sz));
-    launch_prolong_cols<T>(S.n, S.agg.p, t, ld, ec, ldc, q, ldq, nb, s);
+    launch_prolong_cols<T>(S.n, S.agg.p, t, ld, ec, lc, q, ldq, nb, s);
   }
 }
 
@@ -1814,25 +1836,27 @@ static void vcycle_adjoint_batch(Solver& S, const double* z, size_t ldz, double*
   BatchWork& B = S.bw;
   hipStream_t s = S.s;
   const size_t ld = B.ld, ldc = B.ldc;
+  const bool tree = S.opt.coarse_mode == 0 && S.tree_adj;
+  const CoarseCols lc = coarse_cols(tree, ldc, nb);
   {
     Prof p(S, PC_RESID_RESTRICT, nb * ((double)S.n * 12 + (double)S.nc * 16));
-    launch_restrict_cols(S.nc, S.aptr.p, S.amem.p, z, ldz, B.abc.p, B.aec.p, ldc, nb, s);
+    launch_restrict_cols<double>(S.nc, S.aptr.p, S.amem.p, z, ldz, B.abc.p, B.aec.p, lc, nb, s);
   }
-  if (S.opt.coarse_mode == 0 && S.tree_adj) {
+  if (tree) {
     {
       Prof p(S, PC_SWEEP_COARSE, nb * sweep_bytes(S.Uct, 8, 8, false));
-      launch_tree<double>(S.tUct, B.abc.p, false, B.auc.p, nullptr, B.text.p, S.abort_flag.p, s, nb, ldc, B.ncUct.p);
+      launch_tree_cols<double>(S.tUct, B.abc.p, B.auc.p, nullptr, B.text.p, S.abort_flag.p, s, lc.width);
     }
     {
       Prof p(S, PC_SWEEP_COARSE, nb * sweep_bytes(S.Lct, 8, 8, true));
-      launch_tree<double>(S.tLct, B.auc.p, false, B.aec.p, B.auc.p, B.text.p, S.abort_flag.p, s, nb, ldc, B.ncLct.p);
+      launch_tree_cols<double>(S.tLct, B.auc.p, B.aec.p, B.auc.p, B.text.p, S.abort_flag.p, s, lc.width);
     }
   } else {
     for (int c = 0; c < nb; ++c) coarse_adjoint(S, B.abc.p + c * ldc, B.aec.p + c * ldc);
   }
   {
     Prof p(S, PC_RESID_RESTRICT, (double)S.nnz * 12 + (double)S.n * 4 + nb * ((double)S.n * 24 + (double)S.nc * 8));
-    launch_resid_adj_cols(S.n, S.AT.rp.p, S.AT.ci.p, S.AT.v.p, S.agg.p, B.aec.p, ldc, z, ldz, B.as.p, ld, nb, s);
+    launch_resid_adj_cols(S.n, S.AT.rp.p, S.AT.ci.p, S.AT.v.p, S.agg.p, B.aec.p, lc, z, ldz, B.as.p, ld, nb, s);
   }
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.U0t, 8, 8, false) + sweep_bytes(S.L0t, 8, 8, true)));
@@ -1852,7 +1876,7 @@ static void vcycle_adjoint_batch(Solver& S, const double* z, size_t ldz, double*
   }
   {
     Prof p(S, PC_PROLONG, nb * ((double)S.n * 28 + (double)S.nc * 8));
-    launch_prolong_cols<double>(S.n, S.agg.p, B.at.p, ld, B.aec.p, ldc, q, ldq, nb, s);
+    launch_prolong_cols<double>(S.n, S.agg.p, B.at.p, ld, B.aec.p, lc, q, ldq, nb, s);
   }
 }
 

@@ -191,6 +191,8 @@ constexpr int kDenseMaxCoarse = 8192;  // largest A_c of the dense exact coarse 
 struct TreeSolve {
   bool lower = true, has_diag = false;
   int ntasks = 0, max_rows = 0, heights = 0;
+  int nctasks[2] = {0, 0};    // tasks of the solve of several columns: of 4 or 8, of 16
+  DBuf<int> ctask[2];
   DBuf<int> task, erp, ecol, ncount;
   DBuf<int64_t> boff;
   DBuf<double> eval, inv;
@@ -198,7 +200,13 @@ struct TreeSolve {
 };
 template <class T>
 void launch_tree(const TreeSolve& ts, const void* rhs, bool rhs_is_f64, T* out, T* reset_rhs, T* ext,
-                 int* abort_flag, hipStream_t s, int nb = 1, size_t ld = 0, int* ncount = nullptr);
+                 int* abort_flag, hipStream_t s);
+// Several columns: vectors row-major, cw = tree_cols(nb) values per row (zeros
+// in the columns past the batch's)
+int tree_cols(int nb);
+template <class T>
+void launch_tree_cols(const TreeSolve& ts, const T* rhs, T* out, T* reset_rhs, T* ext, int* abort_flag, hipStream_t s,
+                      int cw);
 // Setup: inverses of the diagonal blocks blk (same layout as inv, zeroed
 // beforehand) into inv.  dtask: a task of 8 ints per kTreeInvBlock rows of a
 // node (first row of the factor, the node's rows, first row in the node, rows,
@@ -381,23 +389,27 @@ void launch_spmm(int n, const int* rp, const int* ci, const T* v, const T* x, si
 // r_c = b_c - A x_c
 void launch_residual_cols(int n, const int* rp, const int* ci, const double* v, const double* x, size_t ldx,
                           const double* b, size_t ldb, double* r, size_t ldr, int nb, hipStream_t s);
+// The coarse vectors of a batch: value (I, c) at I * row + c * col; padded to
+// `width` columns when the columns of a row are adjacent (col == 1; the tree
+// solves' layout), else column by column.
+struct CoarseCols {
+  size_t row, col;
+  int width;
+};
 // out_c = z_c - A^T P ec_c (rp/ci/v: A^T as CSR)
 void launch_resid_adj_cols(int n, const int* rp, const int* ci, const double* v, const int* agg, const double* ec,
-                           size_t ldc, const double* z, size_t ldz, double* out, size_t ldo, int nb, hipStream_t s);
+                           CoarseCols lc, const double* z, size_t ldz, double* out, size_t ldo, int nb, hipStream_t s);
 // r_c = z_c - A t_c (t and r in precision T, z FP64)
 template <class T>
 void launch_resid_fine_cols(int n, const int* rp, const int* ci, const T* v, const T* t, size_t ldt, const double* z,
                             size_t ldz, T* r, size_t ldr, int nb, hipStream_t s);
-// rc_c = P^T r_c in precision T; reset_c <- sentinel (reset may be null)
+// rc_c = P^T z_c in precision T; reset_c <- sentinel
 template <class T>
-void launch_restrict_cols_t(int nc, const int* aptr, const int* amem, const T* r, size_t ldr, T* rc, T* reset,
-                            size_t ldc, int nb, hipStream_t s);
-// rc_c = P^T z_c; reset_c <- sentinel (reset may be null)
-void launch_restrict_cols(int nc, const int* aptr, const int* amem, const double* z, size_t ldz, double* rc,
-                          double* reset, size_t ldc, int nb, hipStream_t s);
+void launch_restrict_cols(int nc, const int* aptr, const int* amem, const T* z, size_t ldz, T* rc, T* reset,
+                          CoarseCols lc, int nb, hipStream_t s);
 // q_c = t_c + P ec_c (widened to FP64); t_c <- sentinel
 template <class T>
-void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, size_t ldc, double* q, size_t ldq,
+void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, CoarseCols lc, double* q, size_t ldq,
                          int nb, hipStream_t s);
 // out_c[i] = X[i * nrhs + c0 + c] (c < nb), and the reverse
 void launch_cols_from_rows(const double* X, int nrhs, int c0, double* out, size_t ld, int64_t n, int nb,

@@ -10,6 +10,8 @@
 //   k_prolong_cols   q_c = t_c + P e_c
 //   k_cols_from_rows / k_rows_from_cols: between the caller's (N, nrhs)
 //                    row-major arrays and the column-major batch
+#include <algorithm>
+
 #include "gmg_internal.h"
 #include "kcommon.h"
 
@@ -23,12 +25,14 @@ constexpr int BCAP = 3072;    // (column, value) pairs of a tile staged in LDS
 // its own row, reading the entry once and the nb columns' values of x at that
 // entry (consecutive lanes hold consecutive rows, so for fixed column and
 // entry position the gathers are nearly contiguous).
-// MODE 0: y = A x; 1: y = b - A x; 2: y = b - A (P e), x indexed through agg.
+// MODE 0: y = A x; 1: y = b - A x; 2: y = b - A (P e), x indexed through agg
+// and rsx apart from row to row.
 template <class T, class TB, int MODE>
 __global__ __launch_bounds__(BROWS) void k_spmm(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const T* __restrict__ v, const int* __restrict__ agg,
-                                                const T* __restrict__ x, size_t ldx, const TB* __restrict__ b,
-                                                size_t ldb, T* __restrict__ y, size_t ldy, int nb) {
+                                                const T* __restrict__ x, size_t ldx, size_t rsx,
+                                                const TB* __restrict__ b, size_t ldb, T* __restrict__ y, size_t ldy,
+                                                int nb) {
   __shared__ int sc[BCAP];
   __shared__ T sv[BCAP];
   const int r0 = blockIdx.x * BROWS;
@@ -61,7 +65,7 @@ __global__ __launch_bounds__(BROWS) void k_spmm(int n, const int* __restrict__ r
     if (MODE == 2) j = agg[j];
     T xv[BATCH_MAX];
 #pragma unroll
-    for (int c = 0; c < BATCH_MAX; ++c) xv[c] = c < nb ? x[c * ldx + j] : (T)0;
+    for (int c = 0; c < BATCH_MAX; ++c) xv[c] = c < nb ? x[c * ldx + (MODE == 2 ? j * rsx : j)] : (T)0;
 #pragma unroll
     for (int c = 0; c < BATCH_MAX; ++c) acc[c] += a * xv[c];
   }
@@ -72,18 +76,18 @@ __global__ __launch_bounds__(BROWS) void k_spmm(int n, const int* __restrict__ r
 
 template <class T, class TB, int MODE>
 static void spmm_launch(int n, const int* rp, const int* ci, const T* v, const int* agg, const T* x, size_t ldx,
-                        const TB* b, size_t ldb, T* y, size_t ldy, int nb, hipStream_t s) {
+                        size_t rsx, const TB* b, size_t ldb, T* y, size_t ldy, int nb, hipStream_t s) {
   if (n <= 0) return;
   if (nb < 1 || nb > BATCH_MAX) fail(GMG_ERR_INVALID_ARG, "spmm: bad column count");
   hipLaunchKernelGGL((k_spmm<T, TB, MODE>), dim3((n + BROWS - 1) / BROWS), dim3(BROWS), 0, s, n, rp, ci, v, agg, x,
-                     ldx, b, ldb, y, ldy, nb);
+                     ldx, rsx, b, ldb, y, ldy, nb);
   HIPCK(hipGetLastError());
 }
 
 template <class T>
 void launch_spmm(int n, const int* rp, const int* ci, const T* v, const T* x, size_t ldx, T* y, size_t ldy, int nb,
                  hipStream_t s) {
-  spmm_launch<T, T, 0>(n, rp, ci, v, nullptr, x, ldx, (const T*)nullptr, 0, y, ldy, nb, s);
+  spmm_launch<T, T, 0>(n, rp, ci, v, nullptr, x, ldx, 1, (const T*)nullptr, 0, y, ldy, nb, s);
 }
 template void launch_spmm<double>(int, const int*, const int*, const double*, const double*, size_t, double*, size_t,
                                   int, hipStream_t);
@@ -92,12 +96,13 @@ template void launch_spmm<float>(int, const int*, const int*, const float*, cons
 
 void launch_residual_cols(int n, const int* rp, const int* ci, const double* v, const double* x, size_t ldx,
                           const double* b, size_t ldb, double* r, size_t ldr, int nb, hipStream_t s) {
-  spmm_launch<double, double, 1>(n, rp, ci, v, nullptr, x, ldx, b, ldb, r, ldr, nb, s);
+  spmm_launch<double, double, 1>(n, rp, ci, v, nullptr, x, ldx, 1, b, ldb, r, ldr, nb, s);
 }
 
 void launch_resid_adj_cols(int n, const int* rp, const int* ci, const double* v, const int* agg, const double* ec,
-                           size_t ldc, const double* z, size_t ldz, double* out, size_t ldo, int nb, hipStream_t s) {
-  spmm_launch<double, double, 2>(n, rp, ci, v, agg, ec, ldc, z, ldz, out, ldo, nb, s);
+                           CoarseCols lc, const double* z, size_t ldz, double* out, size_t ldo, int nb,
+                           hipStream_t s) {
+  spmm_launch<double, double, 2>(n, rp, ci, v, agg, ec, lc.col, lc.row, z, ldz, out, ldo, nb, s);
 }
 
 // r_c = z_c - A t_c over the column batch (t in the cycle's precision T, z
@@ -105,7 +110,7 @@ void launch_resid_adj_cols(int n, const int* rp, const int* ci, const double* v,
 template <class T>
 void launch_resid_fine_cols(int n, const int* rp, const int* ci, const T* v, const T* t, size_t ldt, const double* z,
                             size_t ldz, T* r, size_t ldr, int nb, hipStream_t s) {
-  spmm_launch<T, double, 1>(n, rp, ci, v, nullptr, t, ldt, z, ldz, r, ldr, nb, s);
+  spmm_launch<T, double, 1>(n, rp, ci, v, nullptr, t, ldt, 1, z, ldz, r, ldr, nb, s);
 }
 template void launch_resid_fine_cols<double>(int, const int*, const int*, const double*, const double*, size_t,
                                              const double*, size_t, double*, size_t, int, hipStream_t);
@@ -113,38 +118,90 @@ template void launch_resid_fine_cols<float>(int, const int*, const int*, const f
                                             const double*, size_t, float*, size_t, int, hipStream_t);
 
 // rc_c[I] = sum over members (ascending) of z_c[k]; reset_c[I] <- sentinel
-// (column blockIdx.y)
-template <class T, class TZ>
+// (column blockIdx.y, coarse columns ldc apart)
+template <class T>
 __global__ void k_restrict_cols(int nc, const int* __restrict__ aptr, const int* __restrict__ amem,
-                                const TZ* __restrict__ z, size_t ldz, T* __restrict__ rc, T* __restrict__ reset,
+                                const T* __restrict__ z, size_t ldz, T* __restrict__ rc, T* __restrict__ reset,
                                 size_t ldc) {
   const int I = blockIdx.x * blockDim.x + threadIdx.x;
   if (I >= nc) return;
   z += blockIdx.y * ldz;
   T s = (T)0;
-  for (int m = aptr[I]; m < aptr[I + 1]; ++m) s += (T)z[amem[m]];
+  for (int m = aptr[I]; m < aptr[I + 1]; ++m) s += z[amem[m]];
   rc[blockIdx.y * ldc + I] = s;
   if (reset) reset[blockIdx.y * ldc + I] = sentinel_of<T>(0);
 }
-void launch_restrict_cols(int nc, const int* aptr, const int* amem, const double* z, size_t ldz, double* rc,
-                          double* reset, size_t ldc, int nb, hipStream_t s) {
-  if (nc <= 0) return;
-  hipLaunchKernelGGL((k_restrict_cols<double, double>), dim3((nc + 255) / 256, nb), dim3(256), 0, s, nc, aptr, amem, z,
-                     ldz, rc, reset, ldc);
-  HIPCK(hipGetLastError());
+
+// The same into rows of CW columns (zeros past the batch's nb).  A workgroup
+// takes 64 aggregates: its waves gather CW / 4 columns each, lanes along the
+// aggregates (near members of a column share lines), and the rows leave
+// through LDS coalesced.
+template <class T, int CW>
+__global__ __launch_bounds__(256) void k_restrict_rows(int nc, const int* __restrict__ aptr,
+                                                       const int* __restrict__ amem, const T* __restrict__ z,
+                                                       size_t ldz, T* __restrict__ rc, T* __restrict__ reset, int nb) {
+  __shared__ T sh[64][CW + 1];
+  constexpr int NC = CW / 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int I0 = blockIdx.x * 64, I = I0 + lane;
+  const int m0 = I < nc ? aptr[I] : 0, m1 = I < nc ? aptr[I + 1] : 0;
+  T acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = (T)0;
+  for (int m = m0; m < m1; m += 8) {
+    int k[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) k[u] = m + u < m1 ? amem[m + u] : -1;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = wave + 4 * c;
+      if (col >= nb) break;
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = k[u] >= 0 ? z[col * ldz + k[u]] : (T)0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (k[u] >= 0) acc[c] += v[u];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) sh[lane][wave + 4 * c] = acc[c];
+  __syncthreads();
+  const int rows = min(64, nc - I0);
+  for (int o = threadIdx.x; o < rows * CW; o += 256) {
+    rc[(size_t)I0 * CW + o] = sh[o / CW][o & (CW - 1)];
+    reset[(size_t)I0 * CW + o] = sentinel_of<T>(0);
+  }
 }
+
+#define GMG_COLS_WIDTH(cw, CALL)                                       \
+  do {                                                                 \
+    if ((cw) == 4) CALL(4);                                            \
+    else if ((cw) == 8) CALL(8);                                       \
+    else if ((cw) == 16) CALL(16);                                     \
+    else fail(GMG_ERR_INVALID_ARG, "coarse columns: bad row width");   \
+  } while (0)
+
 template <class T>
-void launch_restrict_cols_t(int nc, const int* aptr, const int* amem, const T* r, size_t ldr, T* rc, T* reset,
-                            size_t ldc, int nb, hipStream_t s) {
+void launch_restrict_cols(int nc, const int* aptr, const int* amem, const T* z, size_t ldz, T* rc, T* reset,
+                          CoarseCols lc, int nb, hipStream_t s) {
   if (nc <= 0) return;
-  hipLaunchKernelGGL((k_restrict_cols<T, T>), dim3((nc + 255) / 256, nb), dim3(256), 0, s, nc, aptr, amem, r, ldr, rc,
-                     reset, ldc);
+  if (lc.col == 1) {
+#define GMG_RESTRICT(CW_)                                                                                             \
+  hipLaunchKernelGGL((k_restrict_rows<T, CW_>), dim3((nc + 63) / 64), dim3(256), 0, s, nc, aptr, amem, z, ldz, rc,    \
+                     reset, nb)
+    GMG_COLS_WIDTH(lc.width, GMG_RESTRICT);
+#undef GMG_RESTRICT
+  } else {
+    hipLaunchKernelGGL(k_restrict_cols<T>, dim3((nc + 255) / 256, nb), dim3(256), 0, s, nc, aptr, amem, z, ldz, rc,
+                       reset, lc.col);
+  }
   HIPCK(hipGetLastError());
 }
-template void launch_restrict_cols_t<double>(int, const int*, const int*, const double*, size_t, double*, double*,
-                                             size_t, int, hipStream_t);
-template void launch_restrict_cols_t<float>(int, const int*, const int*, const float*, size_t, float*, float*, size_t,
-                                            int, hipStream_t);
+template void launch_restrict_cols<double>(int, const int*, const int*, const double*, size_t, double*, double*,
+                                           CoarseCols, int, hipStream_t);
+template void launch_restrict_cols<float>(int, const int*, const int*, const float*, size_t, float*, float*,
+                                          CoarseCols, int, hipStream_t);
 
 // q_c[k] = t_c[k] + ec_c[agg[k]] (in T, widened); t_c[k] <- sentinel
 template <class T>
@@ -159,18 +216,51 @@ __global__ void k_prolong_cols(int n, const int* __restrict__ agg, T* __restrict
     t[k] = sentinel_of<T>(0);
   }
 }
+// The same from rows of CW coarse columns: a lane reads its aggregate's row
+// once, in 16-byte pieces, and the columns of t and q follow lane by lane.
+template <class T, int CW>
+__global__ __launch_bounds__(256) void k_prolong_rows(int n, const int* __restrict__ agg, T* __restrict__ t,
+                                                      size_t ldt, const T* __restrict__ ec, double* __restrict__ q,
+                                                      size_t ldq, int nb) {
+  constexpr int V = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(V)));
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
+    const vec* row = reinterpret_cast<const vec*>(ec + (size_t)agg[k] * CW);
+    vec e[CW / V];
+    T tv[CW];
+#pragma unroll
+    for (int u = 0; u < CW / V; ++u) e[u] = row[u];
+#pragma unroll
+    for (int c = 0; c < CW; ++c) tv[c] = c < nb ? t[c * ldt + k] : (T)0;
+#pragma unroll
+    for (int c = 0; c < CW; ++c)
+      if (c < nb) {
+        const T val = tv[c] + e[c / V][c % V];
+        q[c * ldq + k] = (double)val;
+        t[c * ldt + k] = sentinel_of<T>(0);
+      }
+  }
+}
 template <class T>
-void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, size_t ldc, double* q, size_t ldq,
+void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, CoarseCols lc, double* q, size_t ldq,
                          int nb, hipStream_t s) {
   if (n <= 0) return;
-  const unsigned g = (unsigned)std::min<int64_t>(1024, ((int64_t)n + 255) / 256);
-  hipLaunchKernelGGL(k_prolong_cols<T>, dim3(g, nb), dim3(256), 0, s, n, agg, t, ldt, ec, ldc, q, ldq);
+  if (lc.col == 1) {
+    const unsigned g = (unsigned)std::min<int64_t>(4096, ((int64_t)n + 255) / 256);
+#define GMG_PROLONG(CW_) \
+  hipLaunchKernelGGL((k_prolong_rows<T, CW_>), dim3(g), dim3(256), 0, s, n, agg, t, ldt, ec, q, ldq, nb)
+    GMG_COLS_WIDTH(lc.width, GMG_PROLONG);
+#undef GMG_PROLONG
+  } else {
+    const unsigned g = (unsigned)std::min<int64_t>(1024, ((int64_t)n + 255) / 256);
+    hipLaunchKernelGGL(k_prolong_cols<T>, dim3(g, nb), dim3(256), 0, s, n, agg, t, ldt, ec, lc.col, q, ldq);
+  }
   HIPCK(hipGetLastError());
 }
-template void launch_prolong_cols<double>(int, const int*, double*, size_t, const double*, size_t, double*, size_t,
+template void launch_prolong_cols<double>(int, const int*, double*, size_t, const double*, CoarseCols, double*, size_t,
                                           int, hipStream_t);
-template void launch_prolong_cols<float>(int, const int*, float*, size_t, const float*, size_t, double*, size_t, int,
-                                         hipStream_t);
+template void launch_prolong_cols<float>(int, const int*, float*, size_t, const float*, CoarseCols, double*, size_t,
+                                         int, hipStream_t);
 
 // out_c[i] = X[i * nrhs + c0 + c] for c < nb (column blockIdx.y), and back
 __global__ void k_cols_from_rows(const double* __restrict__ X, int nrhs, int c0, double* __restrict__ out, size_t ld,

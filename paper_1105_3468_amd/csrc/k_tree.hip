@@ -59,29 +59,15 @@ __device__ __forceinline__ T tree_poll(const T* p, int* abort_flag, uint64_t lim
 //                       slice each, one per half of the workgroup (s' = 0:
 //                       none), so that a tree's many leaves fit the workgroups
 //                       resident at once
-//
-// nb > 1 solves nb right-hand sides in one launch: workgroup t * nb + c runs
-// task t for column c, whose vectors (rhs, out, ext, reset_rhs) start at
-// c * ld and whose node counters at c * nnode.  A task waits only on earlier
-// tasks of its own column, which have lower workgroup indices.
 template <class T, class TR, bool LOWER>
 __global__ __launch_bounds__(TREE_THREADS) void k_tree(const int* __restrict__ task, const int64_t* __restrict__ boff,
                                                        const int* __restrict__ erp, const int* __restrict__ ecol,
                                                        const T* __restrict__ eval, const T* __restrict__ inv,
                                                        int* ncount, const TR* rhs, T* out, T* ext, TR* reset_rhs,
-                                                       int* abort_flag, uint64_t limit, int nb, size_t ld, int nnode) {
+                                                       int* abort_flag, uint64_t limit) {
   extern __shared__ __align__(16) unsigned char tree_smem[];
   T* y = reinterpret_cast<T*>(tree_smem);
-  const int tix = blockIdx.x / nb;
-  {
-    const int col = blockIdx.x - tix * nb;
-    rhs += col * ld;
-    out += col * ld;
-    ext += col * ld;
-    if (reset_rhs) reset_rhs += col * ld;
-    ncount += (size_t)col * nnode;
-  }
-  const int* tk = task + 8 * (size_t)tix;
+  const int* tk = task + 8 * (size_t)blockIdx.x;
   const int kind = tk[0];
 
   if (kind == 0) {
@@ -247,12 +233,8 @@ static uint64_t tree_limit_ticks() {
 
 template <class T>
 void launch_tree(const TreeSolve& ts, const void* rhs, bool rhs_is_f64, T* out, T* reset_rhs, T* ext, int* abort_flag,
-                 hipStream_t s, int nb, size_t ld, int* ncount) {
+                 hipStream_t s) {
   if (ts.ntasks == 0) return;
-  if (nb < 1 || (int64_t)ts.ntasks * nb > 0x7fffffff) fail(GMG_ERR_INVALID_ARG, "tree solve: bad column count");
-  if (nb > 1 && !ncount) fail(GMG_ERR_INVALID_ARG, "tree solve: columns need their own node counters");
-  int* cnt = ncount ? ncount : ts.ncount.p;
-  const int nnode = (int)ts.ncount.n;
   constexpr bool F32 = sizeof(T) == 4;
   const T* ev = F32 ? (const T*)ts.eval32.p : (const T*)ts.eval.p;
   const T* iv = F32 ? (const T*)ts.inv32.p : (const T*)ts.inv.p;
@@ -266,9 +248,9 @@ void launch_tree(const TreeSolve& ts, const void* rhs, bool rhs_is_f64, T* out, 
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTreeMaxRows * sizeof(double)))); \
       attr = true;                                                                                                 \
     }                                                                                                              \
-    hipLaunchKernelGGL((k_tree<T, TR_, LO_>), dim3(ts.ntasks * nb), dim3(TREE_THREADS), lds, s, ts.task.p,        \
-                       ts.boff.p, ts.erp.p, ts.ecol.p, ev, iv, cnt, (const TR_*)RHS_, out, ext, RESET_, abort_flag, \
-                       lim, nb, ld, nnode);                                                                        \
+    hipLaunchKernelGGL((k_tree<T, TR_, LO_>), dim3(ts.ntasks), dim3(TREE_THREADS), lds, s, ts.task.p, ts.boff.p,   \
+                       ts.erp.p, ts.ecol.p, ev, iv, ts.ncount.p, (const TR_*)RHS_, out, ext, RESET_, abort_flag,   \
+                       lim);                                                                                       \
   } while (0)
 #define GMG_TREE_RHS(TR_, RHS_, RESET_)                \
   do {                                                 \
@@ -281,10 +263,247 @@ void launch_tree(const TreeSolve& ts, const void* rhs, bool rhs_is_f64, T* out, 
 #undef GMG_TREE
   HIPCK(hipGetLastError());
 }
-template void launch_tree<double>(const TreeSolve&, const void*, bool, double*, double*, double*, int*, hipStream_t,
-                                  int, size_t, int*);
-template void launch_tree<float>(const TreeSolve&, const void*, bool, float*, float*, float*, int*, hipStream_t, int,
-                                 size_t, int*);
+template void launch_tree<double>(const TreeSolve&, const void*, bool, double*, double*, double*, int*, hipStream_t);
+template void launch_tree<float>(const TreeSolve&, const void*, bool, float*, float*, float*, int*, hipStream_t);
+
+// ------------------------------------------------- several right-hand sides
+// The same solve for CW = 4, 8 or 16 columns in one launch, vectors row-major
+// (value (r, c) at r * CW + c, columns past the batch's zero).  A node's rows
+// are then X = Tinv (B - E X_outside) with CW-column matrices: the product
+// with the inverse runs on the matrix cores, every entry of the factor is
+// read once for all columns, and a row's values, polled or not, are one
+// contiguous piece.  With a workgroup per task and column instead the 16
+// columns of a 512^2 grid took 205 + 165 us for the lower and the upper solve,
+// most of it workgroups queueing.
+//
+// ctask[8t ..]: helper: 0, r0, r1, wide, log2 G;  slice: 1, lo, s, a, b, node, has_ext, slices
+//
+// v_mfma_*_16x16x4: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; D's
+// row of register r is 4 r + l / 16 in FP64, 4 (l / 16) + r in FP32.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <class T>
+struct Mma;
+template <>
+struct Mma<double> {
+  using acc = f64x4;
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int r, int q) { return 4 * r + q; }
+};
+template <>
+struct Mma<float> {
+  using acc = f32x4;
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int r, int q) { return 4 * q + r; }
+};
+
+constexpr int TREE_HB = 8;   // helper loads in flight per lane
+constexpr int TREE_KB = 8;   // products of four columns of the inverse whose operands are in flight together
+
+// Operands of up to NK consecutive products of the four-column steps k, k + 4,
+// ...: the values of the right-hand side at rows kk < ke (polled when POLL)
+template <class T, int CW, int NK>
+__device__ __forceinline__ void cols_operand(const T* y, int k, int ke, int q, int l16, bool poll, int* abort_flag,
+                                             uint64_t limit, T (&b)[NK]) {
+#pragma unroll
+  for (int u = 0; u < NK; ++u) {
+    const int kk = k + 4 * u + q;
+    const bool in = kk < ke && l16 < CW;
+    b[u] = in ? (poll ? ld_agent(y + (size_t)kk * CW + l16) : y[(size_t)kk * CW + l16]) : (T)0;
+  }
+  if (poll) {
+#pragma unroll
+    for (int u = 0; u < NK; ++u)
+      if (is_sentinel(b[u])) b[u] = tree_poll(y + (size_t)(k + 4 * u + q) * CW + l16, abort_flag, limit);
+  }
+}
+
+template <class T, bool LOWER, int CW>
+__global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __restrict__ ctask,
+                                                            const int64_t* __restrict__ boff,
+                                                            const int* __restrict__ erp, const int* __restrict__ ecol,
+                                                            const T* __restrict__ eval, const T* __restrict__ inv,
+                                                            int* ncount, const T* rhs, T* out, T* ext, T* reset_rhs,
+                                                            int* abort_flag, uint64_t limit) {
+  constexpr int NT = 4;  // row tiles of a slice at most (a leaf of 64 rows)
+  __shared__ T part[TREE_THREADS / 64][NT * 16][CW + 1];
+  __shared__ int last_slice;
+  const int* tk = ctask + 8 * (size_t)blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (tk[0] == 0) {
+    // helper: ext[r] = rhs[r] - sum over entries outside the node.  CW lanes hold
+    // an entry's columns; a wave's 64 / CW such groups are shared by its rows,
+    // G to a row, TREE_HB entries in flight each.  `wide`: all four waves share
+    // the one row (a long row taken by one wave waits for round after round)
+    constexpr int E = 64 / CW, W = TREE_THREADS / 64;
+    // past a row's end: load its last entry again (16 columns: branches around
+    // the loads cost more, 117 against 97 us on the 512^2 grid) or nothing (4
+    // and 8 columns: more such loads in a wave, 64 against 78 us)
+    constexpr bool kAll = CW == 16;
+    const bool wide = tk[3] != 0;
+    const int G = wide ? E : min(1 << tk[4], E), rows = E / G;  // powers of two
+    const int c = lane & (CW - 1), slot = lane / CW / G, sub = lane / CW & (G - 1);
+    for (int rb = wide ? tk[1] : tk[1] + wave * rows; rb < tk[2]; rb += W * rows) {
+      const int r = rb + slot;
+      const bool active = r < tk[2];
+      const size_t at = (size_t)r * CW + c;
+      const T rh = active && sub == 0 ? rhs[at] : (T)0;
+      const int q1 = active ? erp[r + 1] : 0, step = (wide ? W : 1) * G * TREE_HB;
+      T acc = (T)0;
+      for (int q = (active ? erp[r] : 0) + sub + (wide ? wave * E * TREE_HB : 0); q < q1; q += step) {
+        int cc[TREE_HB];
+        T v[TREE_HB], a[TREE_HB];
+#pragma unroll
+        for (int u = 0; u < TREE_HB; ++u) {
+          const bool in = kAll || q + u * G < q1;
+          const int qq = min(q + u * G, q1 - 1);
+          cc[u] = in ? ecol[qq] : 0;
+          a[u] = in ? eval[qq] : (T)0;
+        }
+#pragma unroll
+        for (int u = 0; u < TREE_HB; ++u)
+          v[u] = kAll || q + u * G < q1 ? ld_agent(out + (size_t)cc[u] * CW + c) : (T)0;
+#pragma unroll
+        for (int u = 0; u < TREE_HB; ++u)
+          if (is_sentinel(v[u])) v[u] = tree_poll(out + (size_t)cc[u] * CW + c, abort_flag, limit);
+#pragma unroll
+        for (int u = 0; u < TREE_HB; ++u)
+          if (q + u * G < q1) acc += a[u] * v[u];
+      }
+      for (int off = CW; off < CW * G; off <<= 1) acc += __shfl_xor(acc, off, 64);
+      if (wide) {
+        if (sub == 0) part[wave][0][c] = acc;
+        __syncthreads();
+        acc = (T)0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) acc += part[w][0][c];
+      }
+      if (active && sub == 0 && (!wide || wave == 0)) {
+        T e = rh - acc;
+        if (is_sentinel(e)) e = (T)__builtin_nan("");
+        st_agent(ext + at, e);
+        if (reset_rhs) reset_rhs[at] = sentinel_of<T>(0);
+      }
+    }
+    return;
+  }
+  // slice: rows [a, b) of the node, in tiles of 16; the four waves share the
+  // columns [k0, k1) of the inverse (its other triangle holds zeros) and their
+  // sums are added in order
+  const int lo = tk[1], s = tk[2], a = tk[3], b = tk[4], node = tk[5], has_ext = tk[6], nsl = tk[7];
+  const int k0 = LOWER ? 0 : a, k1 = LOWER ? b : s;
+  const int per = (k1 - k0 + 15) / 16 * 4;
+  const int kb = k0 + wave * per, ke = min(kb + per, k1);
+  const int l16 = lane & 15, q = lane >> 4;
+  const T* M = inv + boff[node];
+  const T* y = (has_ext ? ext : rhs) + (size_t)lo * CW;
+  using Acc = typename Mma<T>::acc;
+  const int tiles = (b - a + 15) / 16;
+  auto store = [&](int t, const Acc& acc) {
+    if (l16 < CW) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][16 * t + Mma<T>::row(r, q)][l16] = acc[r];
+    }
+  };
+  if (tiles > 1) {  // a leaf: at most 64 columns, 16 of them per wave
+    T m[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = a + 16 * t + l16, kk = kb + 4 * u + q;
+        m[t][u] = i < b && kk < ke ? M[(int64_t)kk * s + i] : (T)0;
+      }
+    T v[4];
+    cols_operand<T, CW>(y, kb, ke, q, l16, has_ext != 0, abort_flag, limit, v);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      Acc acc = {};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = Mma<T>::mul(m[t][u], v[u], acc);
+      store(t, acc);
+    }
+  } else {
+    const int i = a + l16;
+    Acc acc = {};
+    for (int k = kb; k < ke; k += 4 * TREE_KB) {
+      T m[TREE_KB], v[TREE_KB];
+      // the inverse's entries are in flight while the inputs are awaited
+#pragma unroll
+      for (int u = 0; u < TREE_KB; ++u) {
+        const int kk = k + 4 * u + q;
+        m[u] = i < b && kk < ke ? M[(int64_t)kk * s + i] : (T)0;
+      }
+      cols_operand<T, CW>(y, k, ke, q, l16, has_ext != 0, abort_flag, limit, v);
+#pragma unroll
+      for (int u = 0; u < TREE_KB; ++u) acc = Mma<T>::mul(m[u], v[u], acc);
+    }
+    store(0, acc);
+  }
+  __syncthreads();
+  for (int o = threadIdx.x; o < (b - a) * CW; o += TREE_THREADS) {
+    const int rr = o / CW, c = o & (CW - 1);
+    T x = (T)0;
+#pragma unroll
+    for (int w = 0; w < TREE_THREADS / 64; ++w) x += part[w][rr][c];
+    if (is_sentinel(x)) x = (T)__builtin_nan("");
+    st_agent(out + (size_t)(lo + a) * CW + o, x);
+  }
+  // the last slice of the node resets what the slices read (as in k_tree)
+  if (threadIdx.x == 0) {
+    bool last = true;
+    if (nsl > 1) {
+      const int t = atomicAdd(ncount + node, 1);
+      last = t == nsl - 1;
+      if (last) st_agent(ncount + node, 0);
+    }
+    last_slice = last;
+  }
+  __syncthreads();
+  if (last_slice) {
+    for (int o = threadIdx.x; o < s * CW; o += TREE_THREADS) {
+      if (has_ext) st_agent(ext + (size_t)lo * CW + o, sentinel_of<T>(0));
+      else if (reset_rhs) reset_rhs[(size_t)lo * CW + o] = sentinel_of<T>(0);
+    }
+  }
+}
+
+int tree_cols(int nb) { return nb <= 4 ? 4 : nb <= 8 ? 8 : 16; }
+
+template <class T>
+void launch_tree_cols(const TreeSolve& ts, const T* rhs, T* out, T* reset_rhs, T* ext, int* abort_flag, hipStream_t s,
+                      int cw) {
+  const int list = cw < 16 ? 0 : 1;
+  if (ts.nctasks[list] == 0) return;
+  constexpr bool F32 = sizeof(T) == 4;
+  const T* ev = F32 ? (const T*)ts.eval32.p : (const T*)ts.eval.p;
+  const T* iv = F32 ? (const T*)ts.inv32.p : (const T*)ts.inv.p;
+  const uint64_t lim = tree_limit_ticks();
+#define GMG_TREE_COLS(LO_, CW_)                                                                                      \
+  hipLaunchKernelGGL((k_tree_cols<T, LO_, CW_>), dim3(ts.nctasks[list]), dim3(TREE_THREADS), 0, s, ts.ctask[list].p, ts.boff.p,  \
+                     ts.erp.p, ts.ecol.p, ev, iv, ts.ncount.p, rhs, out, ext, reset_rhs, abort_flag, lim)
+  if (cw == 4) {
+    if (ts.lower) GMG_TREE_COLS(true, 4);
+    else GMG_TREE_COLS(false, 4);
+  } else if (cw == 8) {
+    if (ts.lower) GMG_TREE_COLS(true, 8);
+    else GMG_TREE_COLS(false, 8);
+  } else if (cw == 16) {
+    if (ts.lower) GMG_TREE_COLS(true, 16);
+    else GMG_TREE_COLS(false, 16);
+  } else {
+    fail(GMG_ERR_INVALID_ARG, "tree solve: bad column count");
+  }
+#undef GMG_TREE_COLS
+  HIPCK(hipGetLastError());
+}
+template void launch_tree_cols<double>(const TreeSolve&, const double*, double*, double*, double*, int*, hipStream_t,
+                                       int);
+template void launch_tree_cols<float>(const TreeSolve&, const float*, float*, float*, float*, int*, hipStream_t, int);
 
 // ---------------------------------------------------------------- setup
 // Inverse of a node's diagonal block T (unit diagonal, or diagonal 1/dinv), by
@@ -298,7 +517,6 @@ template void launch_tree<float>(const TreeSolve&, const void*, bool, float*, fl
 // size, took 57 ms for the 2048-row blocks of a 128^3 grid's coarse factor.
 constexpr int INV_B = 64;    // rows of a block
 constexpr int INV_W = 16;    // columns per workgroup of k_tree_inv_off
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // One wave per diagonal block; lane c solves for column c of the inverse, its
 // unknowns in registers, T in LDS (every lane reads the same entry).
