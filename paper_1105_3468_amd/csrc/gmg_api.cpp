@@ -1194,112 +1194,243 @@ static void build_wave(WaveSweep& f, const WaveGrid& g, const std::vector<int>& 
 
 // The transposed fine and coarse factors of the adjoint cycle, built on the
 // first adjoint use (a forward-only caller never pays for them).
+// Transpose of a factor's rows (entries q in [rp[i] + skip, rp[i+1])): row j
+// lists, ascending, the rows i that hold column j, and the entry q.  Every
+// host thread counts and then places the entries of its range of rows; the
+// ranges follow each other within a row.
+static void transpose_lists(const HCsr& F, int skip, std::vector<int>& trp, std::vector<int>& tci,
+                            std::vector<int>& tsrc) {
+  const int n = F.n;
+  std::vector<std::vector<int>> at(std::max(1, std::min(host_threads(), n / 4096)));  // as parallel_ranges splits
+  for (auto& a : at) a.assign(n, 0);
+  parallel_ranges(n, [&](int i0, int i1, int t) {
+    for (int i = i0; i < i1; ++i)
+      for (int q = F.rp[i] + skip; q < F.rp[i + 1]; ++q) at[t][F.ci[q]]++;
+  });
+  trp.assign(n + 1, 0);
+  for (int j = 0; j < n; ++j) {
+    int o = trp[j];
+    for (auto& a : at) {
+      const int c = a[j];
+      a[j] = o;
+      o += c;
+    }
+    trp[j + 1] = o;
+  }
+  tci.resize(trp[n]);
+  tsrc.resize(trp[n]);
+  parallel_ranges(n, [&](int i0, int i1, int t) {
+    for (int i = i0; i < i1; ++i)
+      for (int q = F.rp[i] + skip; q < F.rp[i + 1]; ++q) {
+        const int o = at[t][F.ci[q]]++;
+        tci[o] = i;
+        tsrc[o] = q;
+      }
+  });
+}
+
+// The transposed factors of the fine smoother.
+static void adjoint_fine(Solver& S) {
+  hipStream_t s = S.s;
+  const int n = S.n;
+  const int64_t nnz64 = S.nnz;
+  const gmg_options& o = S.opt;
+  // row j of U0^T lists i < j with (i, j) in strict U; of L0^T lists i > j
+  // with (i, j) in strict L; src: the entry of the factored matrix (A, or
+  // F = Q A Q^T for the reordered smoothers) that holds the value
+  std::vector<int> hat_rp, hat_ci, hat_src;
+  if (!S.fine_nd) {
+    hat_rp = to_host_int(S.AT.rp.p, n + 1, s);
+    hat_ci = to_host_int(S.AT.ci.p, nnz64, s);
+    hat_src = to_host_int(S.at_src.p, nnz64, s);
+  } else {
+    DBuf<int> ftrp, ftci, ftsrc;
+    transpose_csr(n, n, nnz64, S.frp.p, S.fci.p, nullptr, ftrp, ftci, nullptr, &ftsrc, s);
+    hat_rp = to_host_int(ftrp.p, n + 1, s);
+    hat_ci = to_host_int(ftci.p, nnz64, s);
+    hat_src = to_host_int(ftsrc.p, nnz64, s);
+    HIPCK(hipStreamSynchronize(s));
+  }
+  HIPCK(hipStreamSynchronize(s));
+  std::vector<int> ut_rp(n + 1, 0), lt_rp(n + 1, 0);
+  parallel_ranges(n, [&](int j0, int j1, int) {
+    for (int j = j0; j < j1; ++j) {
+      int nu = 0, nl = 0;
+      for (int q = hat_rp[j]; q < hat_rp[j + 1]; ++q) {
+        nu += hat_ci[q] < j;
+        nl += hat_ci[q] > j;
+      }
+      ut_rp[j + 1] = nu;
+      lt_rp[j + 1] = nl;
+    }
+  });
+  for (int j = 0; j < n; ++j) {
+    ut_rp[j + 1] += ut_rp[j];
+    lt_rp[j + 1] += lt_rp[j];
+  }
+  std::vector<int> ut_ci(ut_rp[n]), ut_src(ut_rp[n]), lt_ci(lt_rp[n]), lt_src(lt_rp[n]);
+  parallel_ranges(n, [&](int j0, int j1, int) {
+    for (int j = j0; j < j1; ++j) {
+      int qu = ut_rp[j], ql = lt_rp[j];
+      for (int q = hat_rp[j]; q < hat_rp[j + 1]; ++q) {
+        const int i = hat_ci[q], p = hat_src[q];
+        if (i < j) { ut_ci[qu] = i; ut_src[qu++] = p; }
+        else if (i > j) { lt_ci[ql] = i; lt_src[ql++] = p; }
+      }
+    }
+  });
+  S.U0t.n = S.L0t.n = n;
+  S.U0t.nnz = (int64_t)ut_ci.size();
+  S.L0t.nnz = (int64_t)lt_ci.size();
+  S.U0t.has_diag = true;
+  S.ftree_adj = false;
+  if (S.wave) {
+    build_wave(S.wU0t, S.wg, ut_rp, ut_ci, ut_src, true, S.ilu.p, nnz64, S.u0dinv.p, n, s);
+    build_wave(S.wL0t, S.wg, lt_rp, lt_ci, lt_src, false, S.ilu.p, nnz64, nullptr, n, s);
+    launch_fill_f64_bits(S.wy.p, kSent64, S.wg.total, s);
+    launch_fill_f64_bits(S.wt.p, kSent64, S.wg.total, s);
+    return;
+  }
+  if (S.ftree) {
+    // the transposes of factors that follow the dissection tree follow it
+    // too (checked all the same)
+    std::vector<double> hilu(nnz64), hud(n);
+    d2h(hilu.data(), S.ilu.p, nnz64, s);
+    d2h(hud.data(), S.u0dinv.p, n, s);
+    HIPCK(hipStreamSynchronize(s));
+    S.ftree_adj = build_tree(S.tU0t, S.fnd_tree, n, ut_rp, ut_ci, &ut_src, 0, hilu, true, &hud, s) &&
+                  build_tree(S.tL0t, S.fnd_tree, n, lt_rp, lt_ci, &lt_src, 0, hilu, false, nullptr, s);
+    if (!S.ftree_adj) {
+      S.tU0t = TreeSolve();
+      S.tL0t = TreeSolve();
+    }
+  }
+  if (!S.ftree_adj) {
+    // the two layouts are independent host work: L0^T's on a second thread
+    std::exception_ptr l_err;
+    int dev = 0;
+    HIPCK(hipGetDevice(&dev));
+    std::thread lt([&] {
+      try {
+        HIPCK(hipSetDevice(dev));
+        PoolStream scope(s);
+        build_sweep(S.L0t, n, lt_rp, lt_ci, lt_src, nullptr, S.ilu.p, false, false, nullptr, nullptr,
+                    o.sweep_wg_chunks, o.sweep_kernel == 2, s);
+      } catch (...) {
+        l_err = std::current_exception();
+      }
+    });
+    try {
+      build_sweep(S.U0t, n, ut_rp, ut_ci, ut_src, nullptr, S.ilu.p, true, true, nullptr, S.u0dinv.p,
+                  o.sweep_wg_chunks, o.sweep_kernel == 2, s);
+    } catch (...) {
+      lt.join();
+      throw;
+    }
+    lt.join();
+    if (l_err) std::rethrow_exception(l_err);
+  } else {
+    S.U0t.levels = S.L0t.levels = S.tU0t.heights;
+  }
+}
+
+// The transposed ILUT factors of A_c (coarse_mode 0): U~^T row j lists i < j
+// (strict part), L~^T row j lists i > j.  Over the dissection tree when they
+// follow it, U~^T's layout on a second host thread and stream as in the setup.
+static void adjoint_ilut(Solver& S, bool threads) {
+  hipStream_t s = S.s;
+  const int nc = S.nc;
+  const gmg_options& o = S.opt;
+  const HCsr &L = S.hLc, &U = S.hUc;
+  std::vector<double> udinv(nc);
+  for (int i = 0; i < nc; ++i) udinv[i] = 1.0 / U.v[U.rp[i]];
+  std::vector<int> u_rp, u_ci, u_src, l_rp, l_ci, l_src;
+  S.tree_adj = false;
+  if (S.tree && threads) {
+    hipStream_t s2 = nullptr;
+    HIPCK(hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
+    bool ok_u = false, ok_l = false;
+    std::exception_ptr u_err, l_err;
+    int dev = 0;
+    HIPCK(hipGetDevice(&dev));
+    std::thread ut([&] {
+      try {
+        HIPCK(hipSetDevice(dev));
+        transpose_lists(U, 1, u_rp, u_ci, u_src);
+        ok_u = build_tree(S.tUct, S.nd_tree, nc, u_rp, u_ci, &u_src, 0, U.v, true, &udinv, s2);
+      } catch (...) {
+        u_err = std::current_exception();
+      }
+    });
+    try {
+      transpose_lists(L, 0, l_rp, l_ci, l_src);
+      ok_l = build_tree(S.tLct, S.nd_tree, nc, l_rp, l_ci, &l_src, 0, L.v, false, nullptr, s);
+    } catch (...) {
+      l_err = std::current_exception();
+    }
+    ut.join();
+    (void)hipStreamSynchronize(s2);
+    (void)hipStreamDestroy(s2);
+    if (l_err) std::rethrow_exception(l_err);
+    if (u_err) std::rethrow_exception(u_err);
+    S.tree_adj = ok_u && ok_l;
+  } else {
+    transpose_lists(U, 1, u_rp, u_ci, u_src);
+    transpose_lists(L, 0, l_rp, l_ci, l_src);
+    S.tree_adj = S.tree && build_tree(S.tUct, S.nd_tree, nc, u_rp, u_ci, &u_src, 0, U.v, true, &udinv, s) &&
+                 build_tree(S.tLct, S.nd_tree, nc, l_rp, l_ci, &l_src, 0, L.v, false, nullptr, s);
+  }
+  if (S.tree_adj) {
+    S.Uct.n = S.Lct.n = nc;
+    S.Uct.nnz = (int64_t)u_ci.size();
+    S.Lct.nnz = (int64_t)l_ci.size();
+    S.Uct.has_diag = true;
+  } else {
+    S.tUct = TreeSolve();
+    S.tLct = TreeSolve();
+    build_sweep(S.Uct, nc, u_rp, u_ci, u_src, &U.v, nullptr, true, true, &udinv, nullptr, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
+    build_sweep(S.Lct, nc, l_rp, l_ci, l_src, &L.v, nullptr, false, false, nullptr, nullptr, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
+  }
+}
+
+// Transposed factors, built at the first adjoint call.  The coarse ones run on
+// a second host thread beside the fine ones; both queue work on the solver's
+// stream, on disjoint buffers.  First adjoint application on 128^3: 680 -> 211
+// ms; small factors stay on one thread (50k-row graph: 1 ms less a training
+// step; the threads' blocks come from the runtime, not the cache).
 static void ensure_adjoint(Solver& S) {
   if (S.adj_ready) return;
   hipStream_t s = S.s;
-  const int n = S.n, nc = S.nc;
-  const int64_t nnz64 = S.nnz;
+  const int nc = S.nc;
   const gmg_options& o = S.opt;
-  {
-    // row j of U0^T lists i < j with (i, j) in strict U; of L0^T lists i > j
-    // with (i, j) in strict L; src: the entry of the factored matrix (A, or
-    // F = Q A Q^T for the reordered smoothers) that holds the value
-    std::vector<int> hat_rp, hat_ci, hat_src;
-    if (!S.fine_nd) {
-      hat_rp = to_host_int(S.AT.rp.p, n + 1, s);
-      hat_ci = to_host_int(S.AT.ci.p, nnz64, s);
-      hat_src = to_host_int(S.at_src.p, nnz64, s);
-    } else {
-      DBuf<int> ftrp, ftci, ftsrc;
-      transpose_csr(n, n, nnz64, S.frp.p, S.fci.p, nullptr, ftrp, ftci, nullptr, &ftsrc, s);
-      hat_rp = to_host_int(ftrp.p, n + 1, s);
-      hat_ci = to_host_int(ftci.p, nnz64, s);
-      hat_src = to_host_int(ftsrc.p, nnz64, s);
-      HIPCK(hipStreamSynchronize(s));
-    }
-    HIPCK(hipStreamSynchronize(s));
-    std::vector<int> ut_rp(n + 1, 0), ut_ci, ut_src, lt_rp(n + 1, 0), lt_ci, lt_src;
-    for (int j = 0; j < n; ++j) {
-      for (int q = hat_rp[j]; q < hat_rp[j + 1]; ++q) {
-        const int i = hat_ci[q], p = hat_src[q];
-        if (i < j) { ut_ci.push_back(i); ut_src.push_back(p); }
-        else if (i > j) { lt_ci.push_back(i); lt_src.push_back(p); }
+  constexpr int64_t kThreadEntries = 2000000;
+  const bool threads = S.nnz + (int64_t)S.hLc.ci.size() + (int64_t)S.hUc.ci.size() >= kThreadEntries;
+  if (o.coarse_mode == 0 && threads) {
+    std::exception_ptr err;
+    int dev = 0;
+    HIPCK(hipGetDevice(&dev));
+    std::thread ct([&] {
+      try {
+        HIPCK(hipSetDevice(dev));
+        PoolStream scope(s);
+        adjoint_ilut(S, true);
+      } catch (...) {
+        err = std::current_exception();
       }
-      ut_rp[j + 1] = (int)ut_ci.size();
-      lt_rp[j + 1] = (int)lt_ci.size();
+    });
+    try {
+      adjoint_fine(S);
+    } catch (...) {
+      ct.join();
+      throw;
     }
-    S.U0t.n = S.L0t.n = n;
-    S.U0t.nnz = (int64_t)ut_ci.size();
-    S.L0t.nnz = (int64_t)lt_ci.size();
-    S.U0t.has_diag = true;
-    S.ftree_adj = false;
-    if (S.wave) {
-      build_wave(S.wU0t, S.wg, ut_rp, ut_ci, ut_src, true, S.ilu.p, nnz64, S.u0dinv.p, n, s);
-      build_wave(S.wL0t, S.wg, lt_rp, lt_ci, lt_src, false, S.ilu.p, nnz64, nullptr, n, s);
-    } else {
-      if (S.ftree) {
-        // the transposes of factors that follow the dissection tree follow it
-        // too (checked all the same)
-        std::vector<double> hilu(nnz64), hud(n);
-        d2h(hilu.data(), S.ilu.p, nnz64, s);
-        d2h(hud.data(), S.u0dinv.p, n, s);
-        HIPCK(hipStreamSynchronize(s));
-        S.ftree_adj = build_tree(S.tU0t, S.fnd_tree, n, ut_rp, ut_ci, &ut_src, 0, hilu, true, &hud, s) &&
-                      build_tree(S.tL0t, S.fnd_tree, n, lt_rp, lt_ci, &lt_src, 0, hilu, false, nullptr, s);
-        if (!S.ftree_adj) {
-          S.tU0t = TreeSolve();
-          S.tL0t = TreeSolve();
-        }
-      }
-      if (!S.ftree_adj) {
-        build_sweep(S.U0t, n, ut_rp, ut_ci, ut_src, nullptr, S.ilu.p, true, true, nullptr, S.u0dinv.p, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
-        build_sweep(S.L0t, n, lt_rp, lt_ci, lt_src, nullptr, S.ilu.p, false, false, nullptr, nullptr, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
-      } else {
-        S.U0t.levels = S.L0t.levels = S.tU0t.heights;
-      }
-    }
+    ct.join();
+    if (err) std::rethrow_exception(err);
+  } else {
+    adjoint_fine(S);
+    if (o.coarse_mode == 0) adjoint_ilut(S, false);
   }
-  if (o.coarse_mode == 0) {
-    // U~^T row j lists i < j (strict part), L~^T row j lists i > j
-    const HCsr &L = S.hLc, &U = S.hUc;
-    std::vector<double> udinv(nc);
-    std::vector<int> uct_cnt(nc + 1, 0), lct_cnt(nc + 1, 0);
-    for (int i = 0; i < nc; ++i) {
-      udinv[i] = 1.0 / U.v[U.rp[i]];
-      for (int q = U.rp[i] + 1; q < U.rp[i + 1]; ++q) uct_cnt[U.ci[q] + 1]++;
-      for (int q = L.rp[i]; q < L.rp[i + 1]; ++q) lct_cnt[L.ci[q] + 1]++;
-    }
-    for (int j = 0; j < nc; ++j) { uct_cnt[j + 1] += uct_cnt[j]; lct_cnt[j + 1] += lct_cnt[j]; }
-    std::vector<int> uct_ci(uct_cnt[nc]), uct_src(uct_cnt[nc]), lct_ci(lct_cnt[nc]), lct_src(lct_cnt[nc]);
-    std::vector<int> fu(uct_cnt.begin(), uct_cnt.end() - 1), fl(lct_cnt.begin(), lct_cnt.end() - 1);
-    for (int i = 0; i < nc; ++i) {
-      for (int q = U.rp[i] + 1; q < U.rp[i + 1]; ++q) {
-        const int o2 = fu[U.ci[q]]++;
-        uct_ci[o2] = i;
-        uct_src[o2] = q;
-      }
-      for (int q = L.rp[i]; q < L.rp[i + 1]; ++q) {
-        const int o2 = fl[L.ci[q]]++;
-        lct_ci[o2] = i;
-        lct_src[o2] = q;
-      }
-    }
-    // the transposes of tree-following factors follow the tree too (an entry
-    // into a descendant becomes one into an ancestor); checked all the same
-    S.tree_adj = S.tree && build_tree(S.tUct, S.nd_tree, nc, uct_cnt, uct_ci, &uct_src, 0, U.v, true, &udinv, s) &&
-                 build_tree(S.tLct, S.nd_tree, nc, lct_cnt, lct_ci, &lct_src, 0, L.v, false, nullptr, s);
-    if (S.tree_adj) {
-      S.Uct.n = S.Lct.n = nc;
-      S.Uct.nnz = (int64_t)uct_ci.size();
-      S.Lct.nnz = (int64_t)lct_ci.size();
-      S.Uct.has_diag = true;
-    } else {
-      S.tUct = TreeSolve();
-      S.tLct = TreeSolve();
-      build_sweep(S.Uct, nc, uct_cnt, uct_ci, uct_src, &U.v, nullptr, true, true, &udinv, nullptr, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
-      build_sweep(S.Lct, nc, lct_cnt, lct_ci, lct_src, &L.v, nullptr, false, false, nullptr, nullptr, o.sweep_wg_chunks, o.sweep_kernel == 2, s);
-    }
-  } else if (o.coarse_mode == 1) {
+  if (o.coarse_mode == 1) {
     // the Jacobi sweeps of the adjoint run on L~^T and U~^T (the diagonal
     // stays in U~^T's rows; the sweep skips it)
     auto tr = [&](DCsr& T, const DCsr& F) {
@@ -1313,13 +1444,9 @@ static void ensure_adjoint(Solver& S) {
     S.dMcT.n = S.dMcT.m = nc;
     S.dMcT.nnz = S.dMc.nnz;
     transpose_csr(nc, nc, S.dMc.nnz, S.dMc.rp.p, S.dMc.ci.p, S.dMc.v.p, S.dMcT.rp, S.dMcT.ci, &S.dMcT.v, nullptr, s);
-  } else {
+  } else if (o.coarse_mode == 3) {
     S.cinvT.alloc((size_t)S.cnp * S.cnp);
     launch_dense_transpose(nc, S.cnp, S.cinv.p, S.cinvT.p, s);
-  }
-  if (S.wave) {
-    launch_fill_f64_bits(S.wy.p, kSent64, S.wg.total, s);
-    launch_fill_f64_bits(S.wt.p, kSent64, S.wg.total, s);
   }
   HIPCK(hipStreamSynchronize(s));
   S.adj_ready = true;
