@@ -1680,28 +1680,26 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       } else if (kc <= many_max()) {
         Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot_many(V, ld, kc, w, n, S.rw, h1, s);
-        launch_gram_coef(kc, h1, S.gram.p, S.ldg, h2, S.gcoef.p, s);
+        launch_gram_coef(kc, h1, S.gram.p, S.ldg, nullptr, h2, S.gcoef.p, s);
         launch_update_dot_many(V, ld, kc, S.gcoef.p, w, n, true, S.rw, S.gdots.p, s);
       } else {
-        // the same projection over blocks of mm vectors: h1 block by block;
-        // w -= V_b c_b for all blocks but the last, whose pass also takes its
-        // products with w_new and ||w_new||^2; then the other blocks'
-        // products with w_new (the Gram row)
-        const int mm = many_max(), nb = (kc + mm - 1) / mm, kl = kc - mm * (nb - 1);
-        Prof p(S, PC_ORTHO, 8.0 * n * (3 * kc - kl + 4 * nb) + 8.0 * kc * kc);
-        for (int b = 0; b < nb; ++b)
-          launch_multidot_many(V + (size_t)b * mm * ld, ld, std::min(mm, kc - b * mm), w, n, S.rw, h1 + b * mm, s);
-        launch_gram_coef(kc, h1, S.gram.p, S.ldg, h2, S.gcoef.p, s);
-        for (int b = 0; b + 1 < nb; ++b)
-          launch_update_many(V + (size_t)b * mm * ld, ld, mm, S.gcoef.p + b * mm, w, n, false, S.rw, nullptr, s);
-        const int b0 = mm * (nb - 1);
-        launch_update_dot_many(V + (size_t)b0 * ld, ld, kl, S.gcoef.p + b0, w, n, true, S.rw, S.gdots.p + b0, s);
-        for (int b = 0; b + 1 < nb; ++b)
-          launch_multidot_many(V + (size_t)b * mm * ld, ld, mm, w, n, S.rw, S.gdots.p + b * mm, s);
+        // longer than the register-resident passes hold: h1 over equal blocks,
+        // and in the same read the products of the newest basis vector (the
+        // Gram row that a fused update would have left); then w -= V c in one
+        // pass.  Two reads of the basis, as below many_max().
+        const int mm = many_max(), nb = (kc + mm - 1) / mm, per = ((kc + nb - 1) / nb + 15) / 16 * 16;
+        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 2 * nb + 2) + 8.0 * kc * kc);
+        const double* vlast = V + (size_t)(kc - 1) * ld;
+        for (int k0 = 0; k0 < kc; k0 += per)
+          launch_multidot_many(V + (size_t)k0 * ld, ld, std::min(per, kc - k0), w, n, S.rw, h1 + k0, s, vlast,
+                               S.gdots.p + k0);
+        launch_gram_coef(kc, h1, S.gram.p, S.ldg, S.gdots.p, h2, S.gcoef.p, s);
+        launch_update_many(V, ld, kc, S.gcoef.p, w, n, true, S.rw, S.gdots.p + kc, s);
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
-        launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, S.gram.p, S.ldg, nrm, s);
+        launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, kc <= many_max(), S.gram.p, S.ldg, nrm,
+                              s);
       }
       d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, 2 * kc + 1, s);
       HIPCK(hipEventRecord(S.colev[j & 1], s));
@@ -2112,7 +2110,7 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16 * nb);
-        launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, W.gram.p, kGramLd,
+        launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, true, W.gram.p, kGramLd,
                               res + 2 * kc, s, bg);
       }
       d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, (size_t)nb * kBatchRS, s);

@@ -346,23 +346,26 @@ void launch_update_gram(const double* V, size_t ld, int k, const double* h, cons
 // any k (<= 2048): w -= V^T h (h device); if want_norm, result[0] = ||w_new||^2
 // Many-vector passes (up to many_max() vectors): result[0..k) = V^T w, and
 // w <- w - V h with result[0..k) = V^T w_new (and result[k] = ||w_new||^2
-// when want_norm), each reading V once.
+// when want_norm), each reading V once.  w2: also result2[0..k) = V^T w2.
 int many_max();
 void launch_multidot_many(const double* V, size_t ld, int k, const double* w, int64_t n, RedWork& rw, double* result,
-                          hipStream_t s);
+                          hipStream_t s, const double* w2 = nullptr, double* result2 = nullptr);
 void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                             RedWork& rw, double* result, hipStream_t s);
 // c = (2I - G) h and d = c - h for the basis' Gram matrix G (row-major, ldg;
 // unit diagonal assumed): the coefficients of a projection corrected for the
 // basis' loss of orthogonality, as a second Gram-Schmidt pass would give
-void launch_gram_coef(int kc, const double* h, const double* gram, size_t ldg, double* d, double* c,
+// fresh (may be null): V^T v of the last vector v, used as its Gram row and
+// stored there
+void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const double* fresh, double* d, double* c,
                       hipStream_t s);
 // y = x / sqrt(nrm2) (zero when it is zero) with nrm2 = dots[row], and the Gram
-// row of y: G[row][i] = G[i][row] = dots[i] / sqrt(nrm2) (i < row),
-// G[row][row] = 1; *nrm2_out = nrm2.  Batch: x at wcol, y at vcol, dots at
+// row of y: G[row][i] = G[i][row] = dots[i] / sqrt(nrm2) (i < row, when
+// have_dots), G[row][row] = 1; *nrm2_out = nrm2.  Batch: x at wcol, y at vcol, dots at
 // rcol, G at gcol, nrm2_out at hcol
-void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, double* gram, size_t ldg,
-                           double* nrm2_out, hipStream_t s, const BatchCols& bc = BatchCols());
+void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
+                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s,
+                           const BatchCols& bc = BatchCols());
 void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                         RedWork& rw, double* result, hipStream_t s);
 // result[0] = ||x||^2

@@ -25,6 +25,7 @@ constexpr int MROWS = 64;         // rows per chunk (two per thread)
 constexpr int MG = MKB / (MROWS / 2);  // vector groups per block
 constexpr int MGRID = 256;        // blocks (one per CU)
 constexpr int MMAX = 384;         // longest basis they take (24 vectors per thread group)
+constexpr int MPIPE2 = 12;        // the same when two products are taken
 constexpr int MPARTS = 32;        // thread groups adding the block partials of one vector
 constexpr int MPIPE = 16;         // up to this many vectors per thread, the next chunk is loaded early
 constexpr int MSTR = MMAX + 8;    // stride of a block's row of partials (one extra slot for a norm)
@@ -228,7 +229,7 @@ void red_init(RedWork& rw, hipStream_t s) {
   rw.partial.alloc((size_t)KGRID * KPART * KCOLS);
   rw.counter.alloc(KCOLS);
   rw.result.alloc(2 * KLDS + 8);
-  rw.mpart.alloc((size_t)MGRID * MSTR);
+  rw.mpart.alloc((size_t)2 * MGRID * MSTR);
   launch_fill_u32(rw.counter.p, 0u, KCOLS, s);
   launch_fill_f64_bits(rw.partial.p, SENT64, (size_t)KGRID * KPART * KCOLS, s);
 }
@@ -346,11 +347,12 @@ void launch_scale(const double* x, double a, double* y, int64_t n, hipStream_t s
 // y = x / sqrt(nrm2) (zero when the norm is zero), and the basis' Gram matrix
 // row `row` (and its mirror column) for the new vector y: block 0 stores
 // G[row][i] = (V[i] . x) / ||x|| for i < row from the products dots[0..row)
-// taken while x was formed, and G[row][row] = 1; nrm2 = dots[row] goes to
-// *nrm2_out.  Column blockIdx.y of a batch.
+// taken while x was formed (unless have_dots is 0: the next projection takes
+// them), and G[row][row] = 1; nrm2 = dots[row] goes to *nrm2_out.  Column
+// blockIdx.y of a batch.
 __global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
-                                 const double* __restrict__ dots, double* __restrict__ gram, size_t ldg,
-                                 double* __restrict__ nrm2_out, size_t xcol, size_t ycol, size_t dcol, size_t gcol,
+                                 const double* __restrict__ dots, int have_dots, double* __restrict__ gram,
+                                 size_t ldg, double* __restrict__ nrm2_out, size_t xcol, size_t ycol, size_t dcol, size_t gcol,
                                  size_t rcol) {
   x += blockIdx.y * xcol;
   y += blockIdx.y * ycol;
@@ -362,7 +364,7 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = a * x[i];
   if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < row; i += blockDim.x) {
+    for (int i = threadIdx.x; i < row && have_dots; i += blockDim.x) {
       const double gv = dots[i] * a;
       gram[(size_t)row * ldg + i] = gv;
       gram[(size_t)i * ldg + row] = gv;
@@ -373,14 +375,14 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
     }
   }
 }
-void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, double* gram, size_t ldg,
-                           double* nrm2_out, hipStream_t s, const BatchCols& bc) {
+void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
+                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s, const BatchCols& bc) {
   if (n <= 0) return;
   check_cols(bc);
   int64_t g = (n + 255) / 256;
   if (g > 8192 / bc.nb) g = 8192 / bc.nb;
-  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots, gram, ldg,
-                     nrm2_out, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
+  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots,
+                     have_dots ? 1 : 0, gram, ldg, nrm2_out, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
   HIPCK(hipGetLastError());
 }
 
@@ -486,46 +488,58 @@ __device__ __forceinline__ double2 many_load(const double* __restrict__ V, size_
 }
 
 // h[k] = V[k] . w for k < kc (block partials); the next chunk's loads are
-// issued before the current chunk's products
-template <int PER>
+// issued before the current chunk's products.  DUAL: also V[k] . w2, in the
+// same read of V (partials mpart2).
+template <int PER, bool DUAL>
 __global__ __launch_bounds__(MKB) void k_multidot_many(const double* __restrict__ V, size_t ld, int kc,
-                                                       const double* __restrict__ w, int64_t n,
-                                                       double* __restrict__ mpart) {
+                                                       const double* __restrict__ w, const double* __restrict__ w2,
+                                                       int64_t n, double* __restrict__ mpart,
+                                                       double* __restrict__ mpart2) {
   const int r = threadIdx.x % MRT, g = threadIdx.x / MRT;
-  double acc[PER];
+  double acc[PER], acc2[DUAL ? PER : 1];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) acc[u] = 0.0;
+  for (int u = 0; u < PER; ++u) {
+    acc[u] = 0.0;
+    if constexpr (DUAL) acc2[u] = 0.0;
+  }
   const int64_t nch = (n + MROWS - 1) / MROWS;
-  double2 v[PER], wi;
-  auto load = [&](double2 (&x)[PER], double2& xw, int64_t c) {
+  double2 v[PER], wi, wi2;
+  auto load = [&](double2 (&x)[PER], double2& xw, double2& xw2, int64_t c) {
     const int64_t i = c * MROWS + 2 * r;
     const bool ok = c < nch;
     xw = many_load(w, 0, 0, i, n, ok);
+    if constexpr (DUAL) xw2 = many_load(w2, 0, 0, i, n, ok);
 #pragma unroll
     for (int u = 0; u < PER; ++u) x[u] = many_load(V, ld, g + MG * u, i, n, ok && g + MG * u < kc);
   };
-  if constexpr (PER <= MPIPE) {
-    load(v, wi, blockIdx.x);
+  auto add = [&](int u) {
+    acc[u] += v[u].x * wi.x + v[u].y * wi.y;
+    if constexpr (DUAL) acc2[u] += v[u].x * wi2.x + v[u].y * wi2.y;
+  };
+  if constexpr (PER <= (DUAL ? MPIPE2 : MPIPE)) {
+    load(v, wi, wi2, blockIdx.x);
     for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
-      double2 vn[PER], wn;
-      load(vn, wn, ch + gridDim.x);
+      double2 vn[PER], wn, wn2;
+      load(vn, wn, wn2, ch + gridDim.x);
       ALL_LOADS_ISSUED();
 #pragma unroll
       for (int u = 0; u < PER; ++u) {
-        acc[u] += v[u].x * wi.x + v[u].y * wi.y;
+        add(u);
         v[u] = vn[u];
       }
       wi = wn;
+      if constexpr (DUAL) wi2 = wn2;
     }
   } else {
     for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
-      load(v, wi, ch);
+      load(v, wi, wi2, ch);
       ALL_LOADS_ISSUED();
 #pragma unroll
-      for (int u = 0; u < PER; ++u) acc[u] += v[u].x * wi.x + v[u].y * wi.y;
+      for (int u = 0; u < PER; ++u) add(u);
     }
   }
   many_block_sums<PER>(acc, kc, mpart);
+  if constexpr (DUAL) many_block_sums<PER>(acc2, kc, mpart2);
 }
 
 // A barrier that orders LDS accesses only: global loads issued before it stay
@@ -660,21 +674,33 @@ static unsigned many_grid(int64_t n) {
 #define GMG_MANY(KERNEL, kc, ...)                                                  \
   do {                                                                             \
     const int per_ = (kc + MG - 1) / MG;                                           \
-    if (per_ <= 8) hipLaunchKernelGGL(KERNEL<8>, __VA_ARGS__);                     \
-    else if (per_ <= 16) hipLaunchKernelGGL(KERNEL<16>, __VA_ARGS__);              \
-    else hipLaunchKernelGGL(KERNEL<24>, __VA_ARGS__);                              \
+    if (per_ <= 8) hipLaunchKernelGGL(KERNEL(8), __VA_ARGS__);                     \
+    else if (per_ <= 16) hipLaunchKernelGGL(KERNEL(16), __VA_ARGS__);              \
+    else hipLaunchKernelGGL(KERNEL(24), __VA_ARGS__);                              \
   } while (0)
+#define GMG_DOT(PER_) (k_multidot_many<PER_, false>)
+#define GMG_DOT2(PER_) (k_multidot_many<PER_, true>)
+#define GMG_UPDATE(PER_) (k_update_dot_many<PER_>)
 
 static_assert(MMAX <= 24 * MG, "the widest many-vector instance holds 24 vectors per group");
 int many_max() { return MMAX; }
 
+static void colsum(const double* mpart, unsigned nb, int k, double* result, hipStream_t s) {
+  hipLaunchKernelGGL(k_colsum, dim3((k + KB / MPARTS - 1) / (KB / MPARTS)), dim3(KB), 0, s, mpart, (int)nb, k, result);
+}
+
 void launch_multidot_many(const double* V, size_t ld, int k, const double* w, int64_t n, RedWork& rw, double* result,
-                          hipStream_t s) {
+                          hipStream_t s, const double* w2, double* result2) {
   if (k < 1 || k > MMAX) fail(GMG_ERR_INVALID_ARG, "multidot_many: bad vector count");
   const unsigned nb = many_grid(n);
-  GMG_MANY(k_multidot_many, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, w, n, rw.mpart.p);
-  hipLaunchKernelGGL(k_colsum, dim3((k + KB / MPARTS - 1) / (KB / MPARTS)), dim3(KB), 0, s, rw.mpart.p, (int)nb, k,
-                     result);
+  double* m2 = rw.mpart.p + (size_t)MGRID * MSTR;
+  if (w2) {
+    GMG_MANY(GMG_DOT2, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, w, w2, n, rw.mpart.p, m2);
+    colsum(m2, nb, k, result2, s);
+  } else {
+    GMG_MANY(GMG_DOT, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, w, w2, n, rw.mpart.p, m2);
+  }
+  colsum(rw.mpart.p, nb, k, result, s);
   HIPCK(hipGetLastError());
 }
 
@@ -683,9 +709,8 @@ void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, 
   if (k < 1 || k > MMAX) fail(GMG_ERR_INVALID_ARG, "update_dot_many: bad vector count");
   const unsigned nb = many_grid(n);
   const int wn = want_norm ? 1 : 0;
-  GMG_MANY(k_update_dot_many, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, h, w, n, wn, rw.mpart.p);
-  hipLaunchKernelGGL(k_colsum, dim3((k + wn + KB / MPARTS - 1) / (KB / MPARTS)), dim3(KB), 0, s, rw.mpart.p, (int)nb,
-                     k + wn, result);
+  GMG_MANY(GMG_UPDATE, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, h, w, n, wn, rw.mpart.p);
+  colsum(rw.mpart.p, nb, k + wn, result, s);
   HIPCK(hipGetLastError());
 }
 
@@ -694,28 +719,39 @@ void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, 
 // i.e. c = (2I - G) h, the first-order form of G^{-1} h: the same as a second
 // classical Gram-Schmidt pass, V^T (w - V h) = h - G h, without reading V
 // again.  One wave per coefficient, lanes over l, added in a fixed order.
-__global__ __launch_bounds__(64) void k_gram_coef(int kc, const double* __restrict__ h,
-                                                  const double* __restrict__ gram, size_t ldg,
-                                                  double* __restrict__ d, double* __restrict__ c) {
+// `fresh`: the products of the last vector with the basis, when its Gram row
+// was not taken as it was formed; used in the row's place and stored there.
+__global__ __launch_bounds__(64) void k_gram_coef(int kc, const double* __restrict__ h, double* gram, size_t ldg,
+                                                  const double* __restrict__ fresh, double* __restrict__ d,
+                                                  double* __restrict__ c) {
   const int i = blockIdx.x, lane = threadIdx.x;
   const double* gi = gram + (size_t)i * ldg;
   double s = 0.0;
-  for (int l = lane; l < kc; l += 64)
-    if (l != i) s += gi[l] * h[l];
+  for (int l = lane; l < kc; l += 64) {
+    const double g = !fresh ? gi[l] : i == kc - 1 ? fresh[l] : l == kc - 1 ? fresh[i] : gi[l];
+    if (l != i) s += g * h[l];
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if (lane == 0) {
     d[i] = -s;
     c[i] = h[i] + (-s);
+    if (fresh && i < kc - 1) {
+      gram[(size_t)(kc - 1) * ldg + i] = fresh[i];
+      gram[(size_t)i * ldg + kc - 1] = fresh[i];
+    }
   }
 }
-void launch_gram_coef(int kc, const double* h, const double* gram, size_t ldg, double* d, double* c,
+void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const double* fresh, double* d, double* c,
                       hipStream_t s) {
   if (kc < 1) return;
-  hipLaunchKernelGGL(k_gram_coef, dim3(kc), dim3(64), 0, s, kc, h, gram, ldg, d, c);
+  hipLaunchKernelGGL(k_gram_coef, dim3(kc), dim3(64), 0, s, kc, h, gram, ldg, fresh, d, c);
   HIPCK(hipGetLastError());
 }
 #undef GMG_MANY
+#undef GMG_DOT
+#undef GMG_DOT2
+#undef GMG_UPDATE
 
 
 __global__ __launch_bounds__(KB) void k_xupdate_many(double* __restrict__ x, const double* __restrict__ Z, size_t ld,
