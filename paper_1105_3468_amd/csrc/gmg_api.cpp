@@ -606,11 +606,18 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   for (char b : bad)
     if (b) return false;
   for (int r = 0; r < n; ++r) erp[r + 1] += erp[r];
-  std::vector<int64_t> boff(nn, 0), node_ext(nn, 0);
-  int64_t total = 0;
+  // log2 of the rows per slice of a node
+  auto slice_lg = [&](int sz) { return sz <= kTreeLeaf ? 6 : sz >= kWideRows ? kWideLgRows : kSliceLgRows; };
+  // offsets of the nodes' blocks: column-major (work) and in the solves'
+  // layout, where every slice has its full rows and nodes start on a line
+  std::vector<int64_t> woff(nn, 0), boff(nn, 0), node_ext(nn, 0);
+  int64_t total = 0, packed = 0;
   for (int k = 0; k < nn; ++k) {
-    boff[k] = total;
-    total += (int64_t)nsz[k] * nsz[k];
+    const int64_t sz = nsz[k], R = (int64_t)1 << slice_lg(nsz[k]);
+    woff[k] = total;
+    boff[k] = packed;
+    total += sz * sz;
+    packed += ((sz <= kTreeLeaf ? sz : (sz + R - 1) / R * R) * sz + 15) / 16 * 16;
     node_ext[k] = erp[tree[k].hi] - erp[tree[k].lo];
   }
   // tasks: nodes by height (lower: ascending, upper: descending), each node's
@@ -661,14 +668,15 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
           ct.insert(ct.end(), {0, r, r1, r1 == r + 1 && longest > kCols[w].wide ? 1 : 0, lg, 0, 0, 0});
           r = r1;
         }
-      const int R2 = sz <= 64 ? 64 : 16, n2 = (sz + R2 - 1) / R2;
+      const int R2 = sz <= kTreeLeaf ? 64 : 16, n2 = (sz + R2 - 1) / R2;
       for (int q = 0; q < n2; ++q)
-        ct.insert(ct.end(), {1, d.lo, sz, q * R2, std::min(sz, (q + 1) * R2), k, has_ext ? 1 : 0, n2});
+        ct.insert(ct.end(), {1, d.lo, sz, q * R2, std::min(sz, (q + 1) * R2), k,
+                             (has_ext ? 1 : 0) | slice_lg(sz) << 1, n2});
     }
     // the node's slices: one for a leaf-sized block, else kSliceRows rows each
-    const int lgR = sz <= 64 ? 6 : sz >= kWideRows ? kWideLgRows : kSliceLgRows, R = 1 << lgR;
+    const int lgR = slice_lg(sz), R = 1 << lgR;
     const int nsl = (sz + R - 1) / R;
-    if (lower && !has_ext && sz <= 64) {
+    if (lower && !has_ext && sz <= kTreeLeaf) {
       // no outside entries: the node waits on nothing, so it may share the
       // workgroup of an earlier one like it (a pair task, one node per half)
       if (pair_open >= 0) {
@@ -702,6 +710,10 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     for (int q = 0; q < ncol; ++q)
       itask[1].insert(itask[1].end(), {sz, (lower ? q : ncol - 1 - q) * kTreeInvCols, k, 0, 0, 0, 0, 0});
   }
+  std::vector<int> ptask;
+  for (int k = 0; k < nn; ++k)
+    for (int j0 = 0; j0 < nsz[k]; j0 += kTreePackCols)
+      ptask.insert(ptask.end(), {nsz[k], j0, std::min(kTreePackCols, nsz[k] - j0), k, slice_lg(nsz[k]), 0, 0, 0});
   ts.lower = lower;
   ts.has_diag = dinv != nullptr;
   ts.ntasks = (int)task.size() / 8;
@@ -722,8 +734,8 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   ts.eval32.alloc(ne > 0 ? ne : 1);
   ts.boff.alloc(nn);
   ts.ncount.alloc(nn);
-  ts.inv.alloc(total > 0 ? total : 1);
-  ts.inv32.alloc(total > 0 ? total : 1);
+  ts.inv.alloc(packed > 0 ? packed : 1);
+  ts.inv32.alloc(packed > 0 ? packed : 1);
   h2d(ts.task.p, task.data(), task.size(), s);
   h2d(ts.erp.p, erp.data(), n + 1, s);
   h2d(ts.boff.p, boff.data(), nn, s);
@@ -731,8 +743,14 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   {
     // the factor's rows on the device, values in entry order
     DBuf<int> drp, dci, dnode, dlo, dsz;
-    DBuf<double> dv, dblk, ddinv;
-    DBuf<int> dit[2];
+    DBuf<double> dv, dblk, ddinv, work;
+    DBuf<int> dit[2], dpt;
+    DBuf<int64_t> dwoff;
+    dwoff.alloc(nn);
+    h2d(dwoff.p, woff.data(), nn, s);
+    dpt.alloc(ptask.size());
+    h2d(dpt.p, ptask.data(), ptask.size(), s);
+    work.alloc(total > 0 ? total : 1);
     drp.alloc(n + 1);
     dci.alloc(nent > 0 ? nent : 1);
     dv.alloc(nent > 0 ? nent : 1);
@@ -756,22 +774,22 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     h2d(dsz.p, nsz.data(), nn, s);
     dblk.alloc(total > 0 ? total : 1);
     HIPCK(hipMemsetAsync(dblk.p, 0, sizeof(double) * (total > 0 ? total : 1), s));
-    launch_tree_fill(n, drp.p, dci.p, dv.p, skip, dnode.p, dlo.p, dsz.p, ts.boff.p, ts.erp.p, dblk.p, ts.ecol.p,
+    launch_tree_fill(n, drp.p, dci.p, dv.p, skip, dnode.p, dlo.p, dsz.p, dwoff.p, ts.erp.p, dblk.p, ts.ecol.p,
                      ts.eval.p, s);
     if (dinv) {
       ddinv.alloc(n);
       h2d(ddinv.p, dinv->data(), n, s);
     }
-    HIPCK(hipMemsetAsync(ts.inv.p, 0, sizeof(double) * (total > 0 ? total : 1), s));
+    HIPCK(hipMemsetAsync(work.p, 0, sizeof(double) * (total > 0 ? total : 1), s));
     for (int c = 0; c < 2; ++c) {
       if (itask[c].empty()) continue;
       dit[c].alloc(itask[c].size());
       h2d(dit[c].p, itask[c].data(), itask[c].size(), s);
     }
-    launch_tree_invert(ts, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, dblk.p,
-                       dinv ? ddinv.p : nullptr, ts.inv.p, s);
+    launch_tree_invert(lower, dwoff.p, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, dblk.p,
+                       dinv ? ddinv.p : nullptr, work.p, s);
+    launch_tree_pack(dpt.p, (int)ptask.size() / 8, dwoff.p, ts.boff.p, work.p, ts.inv.p, ts.inv32.p, s);
     launch_cast_f32(ts.eval.p, ts.eval32.p, ne, s);
-    launch_cast_f32(ts.inv.p, ts.inv32.p, total, s);
     HIPCK(hipStreamSynchronize(s));  // host vectors and staging buffers go out of scope
   }
   return true;

@@ -185,8 +185,8 @@ constexpr int kTreeMaxRows = 2048;  // rows of one node (its values are staged i
 constexpr int kDenseMaxCoarse = 8192;  // largest A_c of the dense exact coarse solve (512 MiB in FP64)
 // A triangular factor laid out for the tree solve: per task 8 ints (helper
 // or node slice), outside entries as CSR over rows (erp, ecol, eval), and per
-// node the inverse of its diagonal block, dense column-major at boff[node]
-// (zeros in the other triangle); ncount[node] counts the node's slices
+// node the inverse of its diagonal block at boff[node] (k_tree_pack's layout,
+// zeros in the other triangle); ncount[node] counts the node's slices
 // arriving in a solve (zero between solves).
 struct TreeSolve {
   bool lower = true, has_diag = false;
@@ -207,19 +207,27 @@ int tree_cols(int nb);
 template <class T>
 void launch_tree_cols(const TreeSolve& ts, const T* rhs, T* out, T* reset_rhs, T* ext, int* abort_flag, hipStream_t s,
                       int cw);
-// Setup: inverses of the diagonal blocks blk (same layout as inv, zeroed
-// beforehand) into inv.  dtask: a task of 8 ints per kTreeInvBlock rows of a
-// node (first row of the factor, the node's rows, first row in the node, rows,
-// node); otask: one per kTreeInvCols columns of a node with more rows than
-// that (the node's rows, first column, node).
+// Setup: inverses of the diagonal blocks blk into inv (both column-major, node
+// k at woff[k], inv zeroed beforehand).  dtask: a task of 8 ints per
+// kTreeInvBlock rows of a node (first row of the factor, the node's rows, first
+// row in the node, rows, node); otask: one per kTreeInvCols columns of a node
+// with more rows than that (the node's rows, first column, node).
 constexpr int kTreeInvBlock = 64, kTreeInvCols = 16;
+// Rows up to which a node is solved by one slice (and stored column-major).
+constexpr int kTreeLeaf = 64;
+// Setup: the inverses into the solves' layout; ptask: one of 8 ints per
+// kTreePackCols columns of a node (its rows, first column, columns, node, log2
+// of its slices' rows).
+constexpr int kTreePackCols = 16;
+void launch_tree_pack(const int* ptask, int npack, const int64_t* woff, const int64_t* boff, const double* work,
+                      double* inv, float* inv32, hipStream_t s);
 // Setup: dense diagonal blocks (zeroed beforehand) and outside-entry lists of
 // a factor whose row r holds entries [rp[r] + skip, rp[r+1]).
 void launch_tree_fill(int n, const int* rp, const int* ci, const double* v, int skip, const int* node_of,
                       const int* nlo, const int* nsz, const int64_t* boff, const int* erp, double* blk, int* ecol,
                       double* eval, hipStream_t s);
-void launch_tree_invert(const TreeSolve& ts, const int* dtask, int ndiag, const int* otask, int noff, const double* blk,
-                        const double* dinv, double* inv, hipStream_t s);
+void launch_tree_invert(bool lower, const int64_t* woff, const int* dtask, int ndiag, const int* otask, int noff,
+                        const double* blk, const double* dinv, double* inv, hipStream_t s);
 
 // Per-kernel-class profiling with events.
 enum ProfClass {

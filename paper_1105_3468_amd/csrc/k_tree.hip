@@ -149,12 +149,15 @@ __global__ __launch_bounds__(TREE_THREADS) void k_tree(const int* __restrict__ t
   // thread reads only its row's side of the diagonal
   const int jb = LOWER ? jg : (jg > i ? jg : i);
   const int je = LOWER ? (jge < i + 1 ? jge : i + 1) : jge;
-  const T* col = inv + boff[node] + i;  // column-major: Tinv[j][i] at j * s + i
+  // columns of the slice's rows: `cs` apart (tree_packed)
+  const bool packed = s > kTreeLeaf;
+  const int cs = packed ? R : s;
+  const T* col = inv + boff[node] + (packed ? (int64_t)a * s + (i - a) : (int64_t)i);
   // the first batch of the block's entries does not depend on the
   // right-hand side: in flight while the inputs are awaited
   T m[TREE_MBATCH];
 #pragma unroll
-  for (int u = 0; u < TREE_MBATCH; ++u) m[u] = jb + u < je ? col[(int64_t)(jb + u) * s] : (T)0;
+  for (int u = 0; u < TREE_MBATCH; ++u) m[u] = jb + u < je ? col[(int64_t)(jb + u) * cs] : (T)0;
   // the slice's right-hand side: all loads issued first, pending ones polled
   // (s <= kTreeMaxRows, checked on the host)
   constexpr int YK = kTreeMaxRows / TREE_THREADS;
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(TREE_THREADS) void k_tree(const int* __restrict__ t
     if (jb + u < je) acc += m[u] * y[jb + u - j0];
   for (int j = jb + TREE_MBATCH; j < je; j += TREE_MBATCH) {
 #pragma unroll
-    for (int u = 0; u < TREE_MBATCH; ++u) m[u] = j + u < je ? col[(int64_t)(j + u) * s] : (T)0;
+    for (int u = 0; u < TREE_MBATCH; ++u) m[u] = j + u < je ? col[(int64_t)(j + u) * cs] : (T)0;
 #pragma unroll
     for (int u = 0; u < TREE_MBATCH; ++u)
       if (j + u < je) acc += m[u] * y[j + u - j0];
@@ -276,7 +279,7 @@ template void launch_tree<float>(const TreeSolve&, const void*, bool, float*, fl
 // columns of a 512^2 grid took 205 + 165 us for the lower and the upper solve,
 // most of it workgroups queueing.
 //
-// ctask[8t ..]: helper: 0, r0, r1, wide, log2 G;  slice: 1, lo, s, a, b, node, has_ext, slices
+// ctask[8t ..]: helper: 0, r0, r1, wide, log2 G;  slice: 1, lo, s, a, b, node, has_ext | log2 R << 1, slices
 //
 // v_mfma_*_16x16x4: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; D's
 // row of register r is 4 r + l / 16 in FP64, 4 (l / 16) + r in FP32.
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __rest
   // slice: rows [a, b) of the node, in tiles of 16; the four waves share the
   // columns [k0, k1) of the inverse (its other triangle holds zeros) and their
   // sums are added in order
-  const int lo = tk[1], s = tk[2], a = tk[3], b = tk[4], node = tk[5], has_ext = tk[6], nsl = tk[7];
+  const int lo = tk[1], s = tk[2], a = tk[3], b = tk[4], node = tk[5], has_ext = tk[6] & 1, nsl = tk[7];
   const int k0 = LOWER ? 0 : a, k1 = LOWER ? b : s;
   const int per = (k1 - k0 + 15) / 16 * 4;
   const int kb = k0 + wave * per, ke = min(kb + per, k1);
@@ -416,7 +419,7 @@ __global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __rest
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int i = a + 16 * t + l16, kk = kb + 4 * u + q;
-        m[t][u] = i < b && kk < ke ? M[(int64_t)kk * s + i] : (T)0;
+        m[t][u] = i < b && kk < ke ? M[(int64_t)kk * s + i] : (T)0;  // not packed
       }
     T v[4];
     cols_operand<T, CW>(y, kb, ke, q, l16, has_ext != 0, abort_flag, limit, v);
@@ -428,7 +431,10 @@ __global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __rest
       store(t, acc);
     }
   } else {
-    const int i = a + l16;
+    const int i = a + l16, lgR = tk[6] >> 1, R = 1 << lgR;
+    const bool packed = s > kTreeLeaf;
+    const int cs = packed ? R : s;
+    const T* col = M + (packed ? (int64_t)(i >> lgR) * R * s + (i & (R - 1)) : (int64_t)i);
     Acc acc = {};
     for (int k = kb; k < ke; k += 4 * TREE_KB) {
       T m[TREE_KB], v[TREE_KB];
@@ -436,7 +442,7 @@ __global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __rest
 #pragma unroll
       for (int u = 0; u < TREE_KB; ++u) {
         const int kk = k + 4 * u + q;
-        m[u] = i < b && kk < ke ? M[(int64_t)kk * s + i] : (T)0;
+        m[u] = i < b && kk < ke ? col[(int64_t)kk * cs] : (T)0;
       }
       cols_operand<T, CW>(y, k, ke, q, l16, has_ext != 0, abort_flag, limit, v);
 #pragma unroll
@@ -631,19 +637,61 @@ __global__ __launch_bounds__(256) void k_tree_inv_off(const int* __restrict__ it
   }
 }
 
-void launch_tree_invert(const TreeSolve& ts, const int* dtask, int ndiag, const int* otask, int noff, const double* blk,
-                        const double* dinv, double* inv, hipStream_t s) {
+// The inverses from the column-major work layout (node k's at woff[k]) to the
+// solves' layout in FP64 and FP32.  Nodes above kTreeLeaf rows are packed by
+// slices: the R rows of a slice of one column are adjacent, and the columns
+// follow, so a slice's workgroup streams one contiguous piece.  (In column-
+// major order a slice of 8 rows read 64 bytes of every line, the other half
+// going to another slice's workgroup; 16 rows straddled lines.)
+// ptask[8t ..]: s, first column, columns, node, log2 R
+constexpr int PACK_COLS = 16;
+__global__ __launch_bounds__(256) void k_tree_pack(const int* __restrict__ ptask, const int64_t* __restrict__ woff,
+                                                   const int64_t* __restrict__ boff, const double* __restrict__ work,
+                                                   double* __restrict__ inv, float* __restrict__ inv32) {
+  const int* t = ptask + 8 * (size_t)blockIdx.x;
+  const int s = t[0], j0 = t[1], nj = t[2], node = t[3], lgR = t[4], R = 1 << lgR;
+  const double* W = work + woff[node];
+  double* O = inv + boff[node];
+  float* O32 = inv32 + boff[node];
+  if (s <= kTreeLeaf) {
+    for (int e = threadIdx.x; e < nj * s; e += 256) {
+      const double v = W[(int64_t)j0 * s + e];
+      O[(int64_t)j0 * s + e] = v;
+      O32[(int64_t)j0 * s + e] = (float)v;
+    }
+    return;
+  }
+  const int slices = (s + R - 1) >> lgR;
+  for (int e = threadIdx.x; e < slices * R * nj; e += 256) {
+    const int rr = e & (R - 1), j = (e >> lgR) % nj, q = (e >> lgR) / nj, i = (q << lgR) + rr;
+    const double v = i < s ? W[(int64_t)(j0 + j) * s + i] : 0.0;
+    const int64_t o = ((int64_t)q * s + j0 + j) * R + rr;
+    O[o] = v;
+    O32[o] = (float)v;
+  }
+}
+
+void launch_tree_pack(const int* ptask, int npack, const int64_t* woff, const int64_t* boff, const double* work,
+                      double* inv, float* inv32, hipStream_t s) {
+  if (npack == 0) return;
+  hipLaunchKernelGGL(k_tree_pack, dim3(npack), dim3(256), 0, s, ptask, woff, boff, work, inv, inv32);
+  HIPCK(hipGetLastError());
+}
+static_assert(kTreePackCols == PACK_COLS, "packing tasks");
+
+void launch_tree_invert(bool lower, const int64_t* woff, const int* dtask, int ndiag, const int* otask, int noff,
+                        const double* blk, const double* dinv, double* inv, hipStream_t s) {
   if (ndiag == 0) return;
 #define GMG_INV(LO_, DG_) \
-  hipLaunchKernelGGL((k_tree_inv_diag<LO_, DG_>), dim3(ndiag), dim3(INV_B), 0, s, dtask, ts.boff.p, blk, dinv, inv)
-  if (ts.lower) {
+  hipLaunchKernelGGL((k_tree_inv_diag<LO_, DG_>), dim3(ndiag), dim3(INV_B), 0, s, dtask, woff, blk, dinv, inv)
+  if (lower) {
     if (dinv) GMG_INV(true, true);
     else GMG_INV(true, false);
-    if (noff) hipLaunchKernelGGL(k_tree_inv_off<true>, dim3(noff), dim3(256), 0, s, otask, ts.boff.p, blk, inv);
+    if (noff) hipLaunchKernelGGL(k_tree_inv_off<true>, dim3(noff), dim3(256), 0, s, otask, woff, blk, inv);
   } else {
     if (dinv) GMG_INV(false, true);
     else GMG_INV(false, false);
-    if (noff) hipLaunchKernelGGL(k_tree_inv_off<false>, dim3(noff), dim3(256), 0, s, otask, ts.boff.p, blk, inv);
+    if (noff) hipLaunchKernelGGL(k_tree_inv_off<false>, dim3(noff), dim3(256), 0, s, otask, woff, blk, inv);
   }
 #undef GMG_INV
   HIPCK(hipGetLastError());
