@@ -1564,7 +1564,8 @@ static void vcycle_adjoint(Solver& S, const double* z, double* q) {
   coarse_adjoint(S, S.abc.p, S.aec.p);
   {
     Prof p(S, PC_RESID_RESTRICT, (double)S.nnz * 12 + (double)S.n * 24);
-    launch_resid_adj(S.n, S.AT.rp.p, S.AT.ci.p, S.AT.v.p, S.agg.p, S.aec.p, z, S.as.p, s);
+    launch_resid_adj(S.n, S.AT.rp.p, S.AT.ci.p, S.AT.v.p, S.agg.p, S.aec.p, z, S.as.p, s,
+                     S.spmv_cap);
   }
   smooth_adjoint(S, S.as.p, S.at.p);
   {

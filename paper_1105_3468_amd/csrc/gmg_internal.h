@@ -281,7 +281,7 @@ void launch_restrict_plain(int nc, const int* aptr, const int* amem, const doubl
                            double* bc, double* reset, uint64_t sentinel_bits, hipStream_t s);
 // s[k] = z[k] - sum_l AT[k,l] ec[agg[l]]
 void launch_resid_adj(int n, const int* rp, const int* ci, const double* v, const int* agg,
-                      const double* ec, const double* z, double* out, hipStream_t s);
+                      const double* ec, const double* z, double* out, hipStream_t s, int cap = 4096);
 // Transpose a device CSR (n rows, m cols) into T (m rows, n cols); columns ascending.
 void transpose_csr(int n, int m, int64_t nnz, const int* rp, const int* ci, const double* v,
                    DBuf<int>& trp, DBuf<int>& tci, DBuf<double>* tv, DBuf<int>* tsrc,
