@@ -2739,8 +2739,11 @@ static void setup_impl(Solver& S, int64_t n64, int64_t nnz64, const int32_t* row
       DBuf<int> dsched;
       dsched.alloc(sched.size() > 0 ? sched.size() : 1);
       h2d(dsched.p, sched.data(), sched.size(), s);
+      int longest = 0;
+      for (int i = 0; i < n; ++i) longest = std::max(longest, hrp[i + 1] - hrp[i]);
       for (int l = 0; l < levels; ++l)
-        launch_ilu0_level(dsched.p + lptr[l], lptr[l + 1] - lptr[l], frp_dev, fci_dev, S.dpos.p, S.ilu.p, bad.p, s);
+        launch_ilu0_level(dsched.p + lptr[l], lptr[l + 1] - lptr[l], frp_dev, fci_dev, S.dpos.p, S.ilu.p, bad.p, s,
+                          longest);
       HIPCK(hipStreamSynchronize(s));
     }
     int hb = 0;

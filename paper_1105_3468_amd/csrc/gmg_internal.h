@@ -318,8 +318,9 @@ void launch_cu_sweep(CuSweep& cs, const T* wval, const T* dinv_e, const void* rh
 bool ilu0_grid_fits(int nx, int ny);
 void launch_ilu0_grid(int n, int nx, const int* rp, const int* ci, const int* dpos, double* a, int* bad,
                       hipStream_t s);
+// one dependency level of L0; longest: entries of the matrix's longest row
 void launch_ilu0_level(const int* rows, int count, const int* rp, const int* ci, const int* dpos,
-                       double* a, int* bad, hipStream_t s);
+                       double* a, int* bad, hipStream_t s, int longest);
 // yout[i] = (b[i] - sum_{j != i} F_ij yin[j]) * (dinv ? dinv[i] : 1)
 void launch_jacobi(int n, const int* rp, const int* ci, const double* v, const double* dinv, const double* b,
                    const double* yin, double* yout, hipStream_t s);

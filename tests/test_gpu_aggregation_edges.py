@@ -1,6 +1,7 @@
 """Galerkin products whose aggregates' entry lists lie around the 256 pairs
 that a wave sorts in LDS, and aggregates with more members than a wave has
-lanes: aggregates and A_c bit-exact against the oracle."""
+lanes; ILU(0) of rows around the 16 lanes and 64 entries that a group of lanes
+holds: aggregates, A_c and ILU(0) bit-exact against the oracle."""
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -26,7 +27,7 @@ def _matrix(n, row, seed):
     return sp.csr_matrix(a)
 
 
-@pytest.mark.parametrize("n,row,cf", [(2, 2, 2.0), (40, 40, 4.0), (63, 63, 4.0), (64, 64, 4.0), (65, 65, 4.0),
+@pytest.mark.parametrize("n,row,cf", [(2, 2, 2.0), (40, 40, 4.0), (15, 15, 2.0), (16, 16, 2.0), (17, 17, 2.0), (63, 63, 4.0), (64, 64, 4.0), (65, 65, 4.0),
                                       (128, 128, 2.0), (129, 129, 2.0), (300, 300, 4.0), (500, 12, 100.0),
                                       (700, 3, 200.0), (1000, 6, 4.0)])
 def test_lists_around_the_wave_sort(n, row, cf):
@@ -39,4 +40,7 @@ def test_lists_around_the_wave_sort(n, row, cf):
         got = got.cpu().numpy()
         assert np.array_equal(got.view(np.uint64) if got.dtype == np.float64 else got,
                               ref.view(np.uint64) if ref.dtype == np.float64 else ref)
+    ilu = O.ilu0()
+    ref = ilu[-1] if isinstance(ilu, tuple) else ilu
+    assert np.array_equal(S.ilu0().cpu().numpy().view(np.uint64), ref.view(np.uint64))
     S.close()
