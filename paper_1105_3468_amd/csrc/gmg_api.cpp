@@ -1647,17 +1647,21 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
   int total = 0;
   double rate = 1.0;   // last ratio of successive residual estimates
   for (;;) {
-    {
-      Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)n * 28);
-      const DCsr& M = adjoint ? S.AT : S.A;
-      launch_residual(S.n, M.rp.p, M.ci.p, M.v.p, x, b, w, s, S.spmv_cap);
+    // r = b - A x; b itself, whose norm is in hp[0], while x is zero
+    const bool zero_x = total == 0 && !x0_given;
+    if (!zero_x) {
+      {
+        Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)n * 28);
+        const DCsr& M = adjoint ? S.AT : S.A;
+        launch_residual(S.n, M.rp.p, M.ci.p, M.v.p, x, b, w, s, S.spmv_cap);
+      }
+      {
+        Prof p(S, PC_VECTOR, (double)n * 8);
+        launch_norm2(w, n, S.rw, res, s);
+      }
+      d2h(hp, res, 1, s);
+      HIPCK(hipStreamSynchronize(s));
     }
-    {
-      Prof p(S, PC_VECTOR, (double)n * 8);
-      launch_norm2(w, n, S.rw, res, s);
-    }
-    d2h(hp, res, 1, s);
-    HIPCK(hipStreamSynchronize(s));
     const double beta = std::sqrt(hp[0]);
     out.relres = beta / bnorm;
     if (!std::isfinite(out.relres)) { out.st = GMG_ERR_NONFINITE; break; }
@@ -1666,7 +1670,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
     if (total > 0) ++out.restarts;
     {
       Prof p(S, PC_VECTOR, (double)n * 16);
-      launch_scale(w, 1.0 / beta, V, n, s);
+      launch_scale(zero_x ? b : w, 1.0 / beta, V, n, s);
     }
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
@@ -1691,7 +1695,6 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       // and ||w||^2 in the same read of V
       double* h1 = res;
       double* h2 = res + kc;
-      double* nrm = res + 2 * kc;
       if (kc <= kFused) {
         Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot(V, ld, kc, w, n, S.rw, h1, s);
@@ -1717,10 +1720,9 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
-        launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, kc <= many_max(), S.gram.p, S.ldg, nrm,
-                              s);
+        launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, kc <= many_max(), S.gram.p, S.ldg, res,
+                              hp + (size_t)kPinCol * (1 + (j & 1)), s);
       }
-      d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, 2 * kc + 1, s);
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };
     // true when the cycle ends with step j
@@ -2074,18 +2076,24 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
   std::vector<std::vector<double>> hist(nb);
   for (int c = 0; c < nb; ++c)
     if (bnorm[c] == 0.0) done[c] = 1;   // x = 0 (set below) is exact
+  bool first = true;
   for (;;) {
-    // r_c = b_c - A x_c and its norm, every column
-    {
-      Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)n * 4 + (double)n * 20 * nb);
-      launch_residual_cols((int)n, M.rp.p, M.ci.p, M.v.p, W.x.p, ld, W.b.p, ld, W.w.p, ld, nb, s);
+    // r_c = b_c - A x_c and its norm, every column; b_c itself, whose norms are
+    // in hp, while x is zero
+    const bool zero_x = first && !x0_given;
+    first = false;
+    if (!zero_x) {
+      {
+        Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)n * 4 + (double)n * 20 * nb);
+        launch_residual_cols((int)n, M.rp.p, M.ci.p, M.v.p, W.x.p, ld, W.b.p, ld, W.w.p, ld, nb, s);
+      }
+      {
+        Prof p(S, PC_VECTOR, (double)n * 8 * nb);
+        launch_norm2(W.w.p, n, S.rw, res, s, nb, ld, 1);
+      }
+      d2h(hp, res, nb, s);
+      HIPCK(hipStreamSynchronize(s));
     }
-    {
-      Prof p(S, PC_VECTOR, (double)n * 8 * nb);
-      launch_norm2(W.w.p, n, S.rw, res, s, nb, ld, 1);
-    }
-    d2h(hp, res, nb, s);
-    HIPCK(hipStreamSynchronize(s));
     bool any = false;
     for (int c = 0; c < nb; ++c) {
       if (done[c] && bnorm[c] == 0.0) { relres[c] = 0.0; continue; }
@@ -2106,7 +2114,7 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
     // v_1 = r / ||r|| for every column (finished ones carried along)
     {
       Prof p(S, PC_VECTOR, (double)n * 16 * nb);
-      launch_normalize_cols(W.w.p, ld, res, 1, W.V.p, ld, n, nb, s);
+      launch_normalize_cols(zero_x ? W.b.p : W.w.p, ld, res, 1, W.V.p, ld, n, nb, s);
     }
     bool breakdown = false;
     auto enqueue_step = [&](int j) {
@@ -2130,9 +2138,8 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
       {
         Prof p(S, PC_VECTOR, (double)n * 16 * nb);
         launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, true, W.gram.p, kGramLd,
-                              res + 2 * kc, s, bg);
+                              res, hp + (size_t)kPinCol * (1 + (j & 1)), s, bg);
       }
-      d2h(hp + (size_t)kPinCol * (1 + (j & 1)), res, (size_t)nb * kBatchRS, s);
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };
     // true when every column's cycle has ended with step j

@@ -370,10 +370,11 @@ void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const d
                       hipStream_t s);
 // y = x / sqrt(nrm2) (zero when it is zero) with nrm2 = dots[row], and the Gram
 // row of y: G[row][i] = G[i][row] = dots[i] / sqrt(nrm2) (i < row, when
-// have_dots), G[row][row] = 1; *nrm2_out = nrm2.  Batch: x at wcol, y at vcol, dots at
-// rcol, G at gcol, nrm2_out at hcol
+// have_dots), G[row][row] = 1; host[0..2 row) = col[0..2 row), host[2 row] =
+// nrm2 (host: pinned memory).  Batch: x at wcol, y at vcol, dots at rcol, G at
+// gcol, col and host at hcol
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s,
+                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s,
                            const BatchCols& bc = BatchCols());
 void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                         RedWork& rw, double* result, hipStream_t s);

@@ -348,12 +348,14 @@ void launch_scale(const double* x, double a, double* y, int64_t n, hipStream_t s
 // row `row` (and its mirror column) for the new vector y: block 0 stores
 // G[row][i] = (V[i] . x) / ||x|| for i < row from the products dots[0..row)
 // taken while x was formed (unless have_dots is 0: the next projection takes
-// them), and G[row][row] = 1; nrm2 = dots[row] goes to *nrm2_out.  Column
-// blockIdx.y of a batch.
+// them), and G[row][row] = 1.  The step's column goes to the host from here
+// as well: host[0 .. 2 row) = col[0 .. 2 row) and host[2 row] = nrm2 =
+// dots[row] (a copy of its own cost 3 us a step).  Column blockIdx.y of a
+// batch.
 __global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
                                  const double* __restrict__ dots, int have_dots, double* __restrict__ gram,
-                                 size_t ldg, double* __restrict__ nrm2_out, size_t xcol, size_t ycol, size_t dcol, size_t gcol,
-                                 size_t rcol) {
+                                 size_t ldg, const double* __restrict__ col, double* __restrict__ host, size_t xcol,
+                                 size_t ycol, size_t dcol, size_t gcol, size_t rcol) {
   x += blockIdx.y * xcol;
   y += blockIdx.y * ycol;
   dots += blockIdx.y * dcol;
@@ -369,20 +371,24 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
       gram[(size_t)row * ldg + i] = gv;
       gram[(size_t)i * ldg + row] = gv;
     }
+    col += blockIdx.y * rcol;
+    host += blockIdx.y * rcol;
+    for (int i = threadIdx.x; i < 2 * row; i += blockDim.x) host[i] = col[i];
     if (threadIdx.x == 0) {
       gram[(size_t)row * ldg + row] = 1.0;
-      nrm2_out[blockIdx.y * rcol] = nv;
+      host[2 * row] = nv;
     }
   }
 }
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, double* nrm2_out, hipStream_t s, const BatchCols& bc) {
+                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s,
+                           const BatchCols& bc) {
   if (n <= 0) return;
   check_cols(bc);
   int64_t g = (n + 255) / 256;
   if (g > 8192 / bc.nb) g = 8192 / bc.nb;
   hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots,
-                     have_dots ? 1 : 0, gram, ldg, nrm2_out, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
+                     have_dots ? 1 : 0, gram, ldg, col, host, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
   HIPCK(hipGetLastError());
 }
 
