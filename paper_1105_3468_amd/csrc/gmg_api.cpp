@@ -1721,7 +1721,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
         launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, kc <= many_max(), S.gram.p, S.ldg, res,
-                              hp + (size_t)kPinCol * (1 + (j & 1)), s);
+                              hp + (size_t)kPinCol * (1 + (j & 1)), S.rw, s);
       }
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };
@@ -2138,7 +2138,7 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
       {
         Prof p(S, PC_VECTOR, (double)n * 16 * nb);
         launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, true, W.gram.p, kGramLd,
-                              res, hp + (size_t)kPinCol * (1 + (j & 1)), s, bg);
+                              res, hp + (size_t)kPinCol * (1 + (j & 1)), S.rw, s, bg);
       }
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };

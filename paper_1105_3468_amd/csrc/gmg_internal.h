@@ -328,6 +328,7 @@ void launch_jacobi(int n, const int* rp, const int* ci, const double* v, const d
 // Krylov kernels (k_krylov.hip)
 struct RedWork {  // scratch for deterministic two-level reductions
   DBuf<double> partial;
+  DBuf<double> dpart;    // block partials that the next kernel adds
   DBuf<double> mpart;    // block partials of the many-vector passes
   DBuf<unsigned> counter;
   DBuf<double> result;   // two coefficient blocks of up to 2048 values + norms
@@ -349,7 +350,7 @@ void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t
                      RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
 // c = (2I - G) h (d = c - h is stored), w -= V[0..k)^T c, then result[0..k) =
 // V^T w_new and result[k] = ||w_new||^2
-void launch_update_gram(const double* V, size_t ld, int k, const double* h, const double* gram, size_t ldg, double* d,
+void launch_update_gram(const double* V, size_t ld, int k, double* h, const double* gram, size_t ldg, double* d,
                         double* w, int64_t n, RedWork& rw, double* result, hipStream_t s,
                         const BatchCols& bc = BatchCols());
 // any k (<= 2048): w -= V^T h (h device); if want_norm, result[0] = ||w_new||^2
@@ -374,7 +375,7 @@ void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const d
 // nrm2 (host: pinned memory).  Batch: x at wcol, y at vcol, dots at rcol, G at
 // gcol, col and host at hcol
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s,
+                           double* gram, size_t ldg, const double* col, double* host, RedWork& rw, hipStream_t s,
                            const BatchCols& bc = BatchCols());
 void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                         RedWork& rw, double* result, hipStream_t s);

@@ -1,12 +1,14 @@
 // Krylov-subspace vector kernels of FGMRES: block multi-dot products, the
 // Gram-corrected projection (two reads of the basis per step), norms, scaling
-// and the solution update.  Reductions are deterministic: every block writes its partial sums
-// in a fixed order and the last block to finish adds the partials in block
-// order (no floating-point atomics), so repeated runs are bitwise identical.
-// The partials are published like the sweeps' results: relaxed agent-scope
-// stores into a buffer reset to a NaN sentinel, polled by the last block,
-// which resets them again.  No fence is needed; an agent-scope fence writes
-// the whole L2 back and cost ~40 us per launch here.
+// and the solution update.  Reductions are deterministic (no floating-point
+// atomics): every block writes its partial sums and they are added in block
+// order, so repeated runs are bitwise identical.  Up to KDEF blocks a column
+// the kernel that needs the sums adds the partials in each of its blocks;
+// beyond, the last block to finish adds them.  There the partials are
+// published like the sweeps' results: relaxed agent-scope stores into a buffer
+// reset to a NaN sentinel, polled by the last block, which resets them again.
+// No fence is needed; an agent-scope fence writes the whole L2 back and cost
+// ~40 us per launch here.
 #include <algorithm>
 
 #include "gmg_internal.h"
@@ -18,6 +20,13 @@ constexpr int KB = 256;          // threads per block
 constexpr int KGRID = 512;       // blocks of the reduction kernels
 constexpr int KMAX = 32;         // vectors per fused register-resident pass
 constexpr int KPART = KMAX + 1;  // partial sums per block: a product per vector and a norm
+// Up to KDEF blocks a column, the next kernel adds the partials: counting the
+// blocks, and the last one's reads, took more than the rest of a small
+// reduction (an FGMRES step of a short solve, with the exchanges of wave_sums:
+// 64^2 78 -> 70 us, 32^2 in 16 columns 99 -> 90 us).  With the line at 64
+// blocks the reads at the start of every block cost more: 512^2 in 16 columns
+// (64 blocks each) 685 -> 701 us a step, 160^2 (50 blocks) 128 -> 130.
+constexpr int KDEF = 32;
 constexpr int KLDS = 2048;       // vectors per LDS-staged pass (longest basis)
 // many-vector passes (a basis longer than KMAX)
 constexpr int MKB = 512;          // threads per block
@@ -35,27 +44,81 @@ constexpr int MSTR = MMAX + 8;    // stride of a block's row of partials (one ex
 // K basis loads of an element and waits for each in turn.
 #define ALL_LOADS_ISSUED() __builtin_amdgcn_sched_barrier(0)
 
+// Sums of the M values a[0 .. M) over the wave's lanes, each added in the order
+// of a tree over lane distances 32, 16, .., 1.  At every distance a lane keeps
+// half of its values and gives the other half to its partner, so M values
+// cost about M + 6 exchanges instead of 6 M (a tree per value spent more on
+// LDS permutes than a small reduction on its loads).  Afterwards a lane with
+// cnt > 0 holds the sum of value `base` in a[0].
+__device__ __forceinline__ double lane_swap(double lo, double hi, int off, bool up) {
+  if (off == 32 || off == 16) {
+    // lanes without bit `off` take lo + their partner's lo, the others hi
+    const uint64_t x = __builtin_bit_cast(uint64_t, lo), y = __builtin_bit_cast(uint64_t, hi);
+    uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32), yl = (uint32_t)y, yh = (uint32_t)(y >> 32);
+    if (off == 32) {
+      const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+      xl = l[0], yl = l[1], xh = h[0], yh = h[1];
+    } else {
+      const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+      xl = l[0], yl = l[1], xh = h[0], yh = h[1];
+    }
+    return __builtin_bit_cast(double, (uint64_t)xh << 32 | xl) + __builtin_bit_cast(double, (uint64_t)yh << 32 | yl);
+  }
+  return (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, 64);
+}
+template <int M, int OFF, int K>
+__device__ __forceinline__ void wave_sums(double (&a)[K], int lane, int& base, int& cnt) {
+  if constexpr (OFF > 0) {
+    constexpr int H = (M + 1) / 2;
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) a[i] = lane_swap(a[i], i + H < M ? a[i + H < M ? i + H : i] : 0.0, OFF, up);
+    base += up ? H : 0;
+    cnt = up ? cnt - H : (cnt < H ? cnt : H);
+    wave_sums<H, OFF / 2, K>(a, lane, base, cnt);
+  }
+}
+
+// sum of the partials p[b * KPART], b < nblk, in block order
+__device__ __forceinline__ double sum_parts(const double* __restrict__ p, int nblk) {
+  double s = 0.0;
+  for (int b0 = 0; b0 < nblk; b0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = b0 + u < nblk ? p[(size_t)(b0 + u) * KPART] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  return s;
+}
+
+// dpart: the blocks' sums are left there, plain stores, for the next kernel
+// to add (a reduction of few blocks: counting the blocks and the last one's
+// reading cost more than every block of the next kernel adding them).
 template <int K>
 __device__ __forceinline__ void block_reduce_store(double (&acc)[K], int kcount, double* partial,
-                                                   unsigned* counter, double* result) {
+                                                   unsigned* counter, double* result, double* dpart = nullptr) {
   __shared__ double sh[KB / 64][K];
   __shared__ bool last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double v = acc[k];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) sh[wave][k] = v;
-  }
+  int base = 0, cnt = K;
+  wave_sums<K, 32, K>(acc, lane, base, cnt);
+  if (cnt > 0) sh[wave][base] = acc[0];
   __syncthreads();
   if (threadIdx.x < kcount) {
     double s = 0.0;
 #pragma unroll
     for (int w = 0; w < KB / 64; ++w) s += sh[w][threadIdx.x];
-    if (is_sentinel(s)) s = __builtin_nan("");
-    st_agent(&partial[(size_t)blockIdx.x * KPART + threadIdx.x], s);
+    if (dpart) {
+      dpart[(size_t)blockIdx.x * KPART + threadIdx.x] = s;
+    } else {
+      if (is_sentinel(s)) s = __builtin_nan("");
+      st_agent(&partial[(size_t)blockIdx.x * KPART + threadIdx.x], s);
+    }
   }
+  if (dpart) return;
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned t = atomicAdd(counter, 1u);
@@ -140,9 +203,10 @@ __device__ __forceinline__ double uniform(double v) {
 template <int K>
 __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, size_t ld,
                                                  const double* __restrict__ w, int64_t n, double* partial,
-                                                 unsigned* counter, double* result, size_t vcol, size_t wcol,
-                                                 size_t rcol) {
+                                                 unsigned* counter, double* result, double* dpart, size_t vcol,
+                                                 size_t wcol, size_t rcol) {
   KRYLOV_COLUMN();
+  if (dpart) dpart += blockIdx.y * (size_t)KDEF * KPART;
   double acc[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) acc[k] = 0.0;
@@ -160,33 +224,45 @@ __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, s
       for (int k = 0; k < K; ++k) acc[k] += v[k].x * wi.x;
     }
   }
-  block_reduce_store<K>(acc, K, partial, counter, result);
+  block_reduce_store<K>(acc, K, partial, counter, result, dpart);
 }
 
 // w <- w - sum_k c[k] V[k]; result[k] = V[k] . w_new, result[K] = ||w_new||^2.
 // c = h + d, d_i = -sum_{l != i} G[i][l] h[l] with the basis' Gram matrix G
 // (k_gram_coef says why); every block forms it for itself, block 0 stores d.
+// hpart: h is the sum of the gridDim.x partials k_multidot left there, which
+// every block adds; block 0 stores it.
 // The products with w_new are the Gram row of the next basis vector, so a
 // step reads the basis twice.  A second Gram-Schmidt pass in its place read
 // it a third time: 27 vectors of 16 columns of 262k rows took 201 + 194 + 181
 // us in three passes.
 template <int K>
 __global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V, size_t ld,
-                                                    const double* __restrict__ h, const double* __restrict__ gram,
-                                                    size_t ldg, double* __restrict__ d, double* __restrict__ w,
-                                                    int64_t n, double* partial, unsigned* counter, double* result,
-                                                    size_t vcol, size_t wcol, size_t rcol, size_t hcol, size_t gcol) {
+                                                    double* h, const double* __restrict__ gram, size_t ldg,
+                                                    double* __restrict__ d, double* __restrict__ w, int64_t n,
+                                                    double* partial, unsigned* counter, double* result,
+                                                    const double* __restrict__ hpart, double* dpart, size_t vcol, size_t wcol, size_t rcol, size_t hcol, size_t gcol) {
   KRYLOV_COLUMN();
   h += blockIdx.y * hcol;
   d += blockIdx.y * hcol;
   gram += blockIdx.y * gcol;
   __shared__ double hs[K], cs[K];
-  if (threadIdx.x < K) hs[threadIdx.x] = h[threadIdx.x];
-  __syncthreads();
+  double g[K];
   if (threadIdx.x < K) {
-    double g[K], t = 0.0;
 #pragma unroll
     for (int l = 0; l < K; ++l) g[l] = gram[(size_t)l * ldg + threadIdx.x];  // symmetric
+    if (hpart) {
+      const double t = sum_parts(hpart + blockIdx.y * (size_t)KDEF * KPART + threadIdx.x, gridDim.x);
+      hs[threadIdx.x] = t;
+      if (blockIdx.x == 0) h[threadIdx.x] = t;
+    } else {
+      hs[threadIdx.x] = h[threadIdx.x];
+    }
+  }
+  if (dpart) dpart += blockIdx.y * (size_t)KDEF * KPART;
+  __syncthreads();
+  if (threadIdx.x < K) {
+    double t = 0.0;
 #pragma unroll
     for (int l = 0; l < K; ++l)
       if (l != (int)threadIdx.x) t += g[l] * hs[l];
@@ -221,13 +297,14 @@ __global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V
       acc[K] += s.x * s.x;
     }
   }
-  block_reduce_store<K + 1>(acc, K + 1, partial, counter, result);
+  block_reduce_store<K + 1>(acc, K + 1, partial, counter, result, dpart);
 }
 
 void red_init(RedWork& rw, hipStream_t s) {
   rw.blocks = KGRID;
   rw.partial.alloc((size_t)KGRID * KPART * KCOLS);
   rw.counter.alloc(KCOLS);
+  rw.dpart.alloc((size_t)2 * KDEF * KPART * KCOLS);
   rw.result.alloc(2 * KLDS + 8);
   rw.mpart.alloc((size_t)2 * MGRID * MSTR);
   launch_fill_u32(rw.counter.p, 0u, KCOLS, s);
@@ -254,6 +331,12 @@ static unsigned red_grid(int64_t n, int nb = 1) {
   return (unsigned)g;
 }
 
+// The partials of k_multidot (which 0) and k_update_gram (which 1) where the
+// next kernel adds them: up to KDEF blocks a column.
+static double* deferred(RedWork& rw, int64_t n, int nb, int which) {
+  return red_grid(n, nb) <= KDEF ? rw.dpart.p + (size_t)which * KDEF * KPART * KCOLS : nullptr;
+}
+
 // launch KERNEL<kc> for 1 <= kc <= 32
 #define GMG_K4(KERNEL, B, ...)                                           \
   case B + 1: hipLaunchKernelGGL(KERNEL<B + 1>, __VA_ARGS__); break;    \
@@ -278,15 +361,16 @@ void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t
   if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "multidot: bad vector count");
   check_cols(bc);
   GMG_DISPATCH_K(k, k_multidot, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, w, n, rw.partial.p,
-                 rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol);
+                 rw.counter.p, result, deferred(rw, n, bc.nb, 0), bc.vcol, bc.wcol, bc.rcol);
   HIPCK(hipGetLastError());
 }
-void launch_update_gram(const double* V, size_t ld, int k, const double* h, const double* gram, size_t ldg, double* d,
+void launch_update_gram(const double* V, size_t ld, int k, double* h, const double* gram, size_t ldg, double* d,
                         double* w, int64_t n, RedWork& rw, double* result, hipStream_t s, const BatchCols& bc) {
   if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update_gram: bad vector count");
   check_cols(bc);
   GMG_DISPATCH_K(k, k_update_gram, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, h, gram, ldg, d, w, n,
-                 rw.partial.p, rw.counter.p, result, bc.vcol, bc.wcol, bc.rcol, bc.hcol, bc.gcol);
+                 rw.partial.p, rw.counter.p, result, deferred(rw, n, bc.nb, 0), deferred(rw, n, bc.nb, 1), bc.vcol,
+                 bc.wcol, bc.rcol, bc.hcol, bc.gcol);
   HIPCK(hipGetLastError());
 }
 
@@ -350,24 +434,26 @@ void launch_scale(const double* x, double a, double* y, int64_t n, hipStream_t s
 // taken while x was formed (unless have_dots is 0: the next projection takes
 // them), and G[row][row] = 1.  The step's column goes to the host from here
 // as well: host[0 .. 2 row) = col[0 .. 2 row) and host[2 row] = nrm2 =
-// dots[row] (a copy of its own cost 3 us a step).  Column blockIdx.y of a
-// batch.
+// dots[row] (a copy of its own cost 3 us a step).  parts: dots is the sum of
+// the nparts partials k_update_gram left there.  Column blockIdx.y of a batch.
 __global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
                                  const double* __restrict__ dots, int have_dots, double* __restrict__ gram,
-                                 size_t ldg, const double* __restrict__ col, double* __restrict__ host, size_t xcol,
-                                 size_t ycol, size_t dcol, size_t gcol, size_t rcol) {
+                                 size_t ldg, const double* __restrict__ col, double* __restrict__ host,
+                                 const double* __restrict__ parts, int nparts, size_t xcol, size_t ycol, size_t dcol,
+                                 size_t gcol, size_t rcol) {
   x += blockIdx.y * xcol;
   y += blockIdx.y * ycol;
   dots += blockIdx.y * dcol;
   gram += blockIdx.y * gcol;
-  const double nv = dots[row];
+  if (parts) parts += blockIdx.y * (size_t)KDEF * KPART;
+  const double nv = parts ? sum_parts(parts + row, nparts) : dots[row];
   const double hn = sqrt(nv);
   const double a = hn != 0.0 ? 1.0 / hn : 0.0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = a * x[i];
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < row && have_dots; i += blockDim.x) {
-      const double gv = dots[i] * a;
+      const double gv = (parts ? sum_parts(parts + i, nparts) : dots[i]) * a;
       gram[(size_t)row * ldg + i] = gv;
       gram[(size_t)i * ldg + row] = gv;
     }
@@ -381,14 +467,15 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
   }
 }
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s,
+                           double* gram, size_t ldg, const double* col, double* host, RedWork& rw, hipStream_t s,
                            const BatchCols& bc) {
   if (n <= 0) return;
   check_cols(bc);
+  const double* parts = row <= KMAX ? deferred(rw, n, bc.nb, 1) : nullptr;
   int64_t g = (n + 255) / 256;
   if (g > 8192 / bc.nb) g = 8192 / bc.nb;
   hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots,
-                     have_dots ? 1 : 0, gram, ldg, col, host, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
+                     have_dots ? 1 : 0, gram, ldg, col, host, parts, parts ? (int)red_grid(n, bc.nb) : 0, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
   HIPCK(hipGetLastError());
 }
 

@@ -55,3 +55,20 @@ def test_batched_iterates_match_the_oracle(nrhs, restart):
         xo, _ = O.solve(B[:, c], tol=1e-30, restart=restart, maxit=restart + 2)
         d = A @ (X[:, c].cpu().numpy() - xo)
         assert np.linalg.norm(d) <= 1e-10 * np.linalg.norm(B[:, c])
+
+
+# 32 workgroups a column, whose sums the next kernel adds, and 33, whose last
+# workgroup adds them
+@pytest.mark.parametrize("n", [16384, 16385])
+def test_iterates_where_the_reduction_changes(n):
+    A = _chain(n)
+    rp, ci, v = A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data
+    B = np.random.default_rng(4).uniform(-1, 1, (n, 2))
+    opts = dict(ilut_tau=1e-1)
+    S, O = Solver(rp, ci, v, **opts), oracle.Oracle(rp, ci, v, **opts)
+    X = S.solve(B, tol=1e-30, restart=5, maxit=7)[0].cpu().numpy()
+    for c in range(2):
+        x1 = S.solve(B[:, c].copy(), tol=1e-30, restart=5, maxit=7)[0].cpu().numpy()
+        xo, _ = O.solve(B[:, c], tol=1e-30, restart=5, maxit=7)
+        for x in (X[:, c], x1):
+            assert np.linalg.norm(A @ (x - xo)) <= 1e-10 * np.linalg.norm(B[:, c])
