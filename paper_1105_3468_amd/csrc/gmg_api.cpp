@@ -1087,7 +1087,7 @@ static void smooth_apply(Solver& S, const double* z, T* t) {
   const size_t sz = sizeof(T);
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, sweep_bytes(S.L0, sz, 8, false) + sweep_bytes(S.U0, sz, sz, true));
-    launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, true, F32 ? (T*)S.wz32.p : (T*)S.wz.p, F32 ? (T*)S.wy32.p : (T*)S.wy.p,
+    launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, F32 ? (T*)S.wz32.p : (T*)S.wz.p, F32 ? (T*)S.wy32.p : (T*)S.wy.p,
                         F32 ? (T*)S.wt32.p : (T*)S.wt.p, t, S.abort_flag.p, s);
   } else if (S.fine_nd) {
     // t = Q^T U0^{-1} L0^{-1} Q z
@@ -1528,7 +1528,7 @@ static void smooth_adjoint(Solver& S, const double* sv, double* t) {
   hipStream_t s = S.s;
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, sweep_bytes(S.U0t, 8, 8, false) + sweep_bytes(S.L0t, 8, 8, true));
-    launch_wave_pair<double>(S.wg, S.wU0t, S.wL0t, sv, true, S.wz.p, S.wy.p, S.wt.p, t, S.abort_flag.p, s);
+    launch_wave_pair<double>(S.wg, S.wU0t, S.wL0t, sv, S.wz.p, S.wy.p, S.wt.p, t, S.abort_flag.p, s);
   } else if (S.fine_nd) {
     Prof p(S, PC_SWEEP_FINE, sweep_bytes(S.U0t, 8, 8, false) + sweep_bytes(S.L0t, 8, 8, true) + (double)S.n * 40);
     launch_perm_gather<double>(S.n, S.fperm.p, sv, S.fzp.p, s);
@@ -1833,7 +1833,7 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
     launch_fill_f64_bits(B.text.p, kSent64, ncv, s);
     if (S.wave) {
       const size_t nw = (size_t)S.wg.total * B.cap;
-      B.wz.alloc(nw);
+      if (S.wg.nz > 0) B.wz.alloc(nw);
       B.wy.alloc(nw);
       B.wt.alloc(nw);
       launch_fill_f64_bits(B.wy.p, kSent64, nw, s);
@@ -1866,7 +1866,7 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
     launch_fill_f32_bits(B.text32.p, kSent32, ncv, s);
     if (S.wave) {
       const size_t nw = (size_t)S.wg.total * B.cap;
-      B.wz32.alloc(nw);
+      if (S.wg.nz > 0) B.wz32.alloc(nw);
       B.wy32.alloc(nw);
       B.wt32.alloc(nw);
       launch_fill_f32_bits(B.wy32.p, kSent32, nw, s);
@@ -1930,7 +1930,7 @@ static void vcycle_batch(Solver& S, const double* z, size_t ldz, double* q, size
   const CoarseCols lc = coarse_cols(tree, ldc, nb);
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.L0, sz, 8, false) + sweep_bytes(S.U0, sz, sz, true)));
-    launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, true, F32 ? (T*)B.wz32.p : (T*)B.wz.p, F32 ? (T*)B.wy32.p : (T*)B.wy.p,
+    launch_wave_pair<T>(S.wg, S.wL0, S.wU0, z, F32 ? (T*)B.wz32.p : (T*)B.wz.p, F32 ? (T*)B.wy32.p : (T*)B.wy.p,
                         F32 ? (T*)B.wt32.p : (T*)B.wt.p, t, S.abort_flag.p, s, nb, ldz, ld);
   } else if (S.fine_nd) {
     for (int c = 0; c < nb; ++c) smooth_apply<T>(S, z + c * ldz, t + c * ld);
@@ -2006,7 +2006,7 @@ static void vcycle_adjoint_batch(Solver& S, const double* z, size_t ldz, double*
   }
   if (S.wave) {
     Prof p(S, PC_SWEEP_FINE, nb * (sweep_bytes(S.U0t, 8, 8, false) + sweep_bytes(S.L0t, 8, 8, true)));
-    launch_wave_pair<double>(S.wg, S.wU0t, S.wL0t, B.as.p, true, B.wz.p, B.wy.p, B.wt.p, B.at.p, S.abort_flag.p, s, nb,
+    launch_wave_pair<double>(S.wg, S.wU0t, S.wL0t, B.as.p, B.wz.p, B.wy.p, B.wt.p, B.at.p, S.abort_flag.p, s, nb,
                              ld, ld);
   } else if (S.fine_nd) {
     for (int c = 0; c < nb; ++c) smooth_adjoint(S, B.as.p + c * ld, B.at.p + c * ld);
@@ -2777,8 +2777,8 @@ static void setup_impl(Solver& S, int64_t n64, int64_t nnz64, const int32_t* row
       g.total = (int64_t)g.W * g.S * 64;
       build_wave(S.wL0, g, l_rp, l_ci, l_src, true, S.ilu.p, nnz64, nullptr, n, s);
       build_wave(S.wU0, g, u_rp, u_ci, u_src, false, S.ilu.p, nnz64, S.u0dinv.p, n, s);
-      S.wz.alloc(g.total); S.wy.alloc(g.total); S.wt.alloc(g.total);
-      S.wz32.alloc(g.total); S.wy32.alloc(g.total); S.wt32.alloc(g.total);
+      S.wy.alloc(g.total); S.wt.alloc(g.total);
+      S.wy32.alloc(g.total); S.wt32.alloc(g.total);
       S.wave = true;
       // sizes and depths of the factors (profiling byte counts, info)
       S.L0.n = S.U0.n = n;

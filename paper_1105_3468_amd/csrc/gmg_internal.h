@@ -166,11 +166,12 @@ struct WaveSweep {
   DBuf<double> coef, dinv;
   DBuf<float> coef32, dinv32;
 };
-// z (natural order, FP64 if z_f64) -> lower sweep -> upper sweep -> t
-// (natural order); zs, ys, ts are layout-ordered work vectors, ys and ts
-// all-sentinel on entry and left so.
+// z (natural order, FP64) -> lower sweep -> upper sweep -> t (natural order);
+// zs (3D only), ys, ts are layout-ordered work vectors, ys and ts
+// all-sentinel before the first pair of sweeps (2D: lane 63 of every step is
+// enough, and is what is left so) and after one.
 template <class T>
-void launch_wave_pair(const WaveGrid& g, const WaveSweep& lo, const WaveSweep& up, const void* z, bool z_f64, T* zs,
+void launch_wave_pair(const WaveGrid& g, const WaveSweep& lo, const WaveSweep& up, const double* z, T* zs,
                       T* ys, T* ts, T* t, int* abort_flag, hipStream_t s, int nb = 1, size_t ldz = 0,
                       size_t ldt = 0);
 

@@ -82,8 +82,15 @@ struct Pair<float> { using type = float2; };
 // one step's operands of one lane in the LDS ring: the two coefficients, the
 // right-hand side and the reciprocal diagonal (two 16-byte LDS reads for FP64)
 template <class T>
-struct alignas(4 * sizeof(T)) WaveOp {
+struct alignas(16) WaveOp {
   T cb, cl, b, d;  // coefficient of the neighbour below, of the left one
+};
+// one step's operands; 16 bytes of padding spread a producer's stores of eight
+// steps of a lane over the banks
+template <class T>
+struct alignas(16) WaveRow {
+  WaveOp<T> op[64];
+  char pad[16];
 };
 
 // Bounded wait on an LDS progress counter (relaxed loads); false when the
@@ -137,18 +144,22 @@ __device__ __forceinline__ void lds_acquire() { __builtin_amdgcn_fence(__ATOMIC_
 // (lower factors), else the left one (upper factors).  REV: the right-hand
 // side is read at total - 1 - p.
 //
+// Lower sweeps (!REV) take the right-hand side in cell order: a launch that
+// laid it out first took 3.4 us at 64^2, 8 us at 1024^2 and 19 us for 16
+// columns of 512^2, the sweep reading it itself 0, 8 and 3 us more.
+//
 // nb > 1 sweeps nb right-hand sides in one launch: workgroup w * nb + r runs
-// band w of column r, whose right-hand side and output are the position
-// layouts at rhs + r * total and out + r * total.  A band waits only on the
+// band w of column r, whose right-hand side is at rhs + r * ldr (REV: the
+// position layout) and whose output is the position layout at out + r * total.  A band waits only on the
 // band before it in the same column, which has the lower workgroup index, so
 // the launch drains as with one column.
-template <class T, bool DIAG, bool UP_FIRST, bool REV>
-__global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int64_t total,
+template <class T, class TR, bool DIAG, bool UP_FIRST, bool REV>
+__global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int ny, int64_t total,
                                                        const typename Pair<T>::type* __restrict__ coef,
-                                                       const T* __restrict__ dinv, const T* __restrict__ rhs, T* out,
-                                                       int* abort_flag, uint64_t limit, int nb) {
+                                                       const T* __restrict__ dinv, const TR* __restrict__ rhs,
+                                                       size_t ldr, T* out, int* abort_flag, uint64_t limit, int nb) {
   using P2 = typename Pair<T>::type;
-  __shared__ WaveOp<T> r_op[WAVE_RING][64];
+  __shared__ WaveRow<T> r_op[WAVE_RING];
   __shared__ T r_x[WAVE_XRING];      // previous band's boundary values
   __shared__ int ready[WAVE_SLOTS];  // chunk c + 1 once chunk c is in its slot c % WAVE_SLOTS
   __shared__ int xready;             // boundary values in r_x
@@ -158,7 +169,7 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int64_t to
   const int w = blockIdx.x / nb, l = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   {
     const int col = blockIdx.x - w * nb;
-    rhs += (int64_t)col * total;
+    rhs += (int64_t)col * ldr;
     out += (int64_t)col * total;
   }
   const int64_t p0 = (int64_t)w * S * 64 + l;
@@ -212,13 +223,26 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int64_t to
     // ---------------------------------------------------------- producer
     const int k = role - 1;
     P2 rc[WAVE_D][WAVE_CH];
-    T rb[WAVE_D][WAVE_CH], rd[WAVE_D][WAVE_CH];
+    TR rb[WAVE_D][WAVE_CH];
+    T rd[WAVE_D][WAVE_CH];
+    // !REV: load u of a chunk takes column 8 c + (l & 7) - r of grid rows
+    // r = 8 u + (l >> 3) of the band, 64 contiguous bytes of each of eight rows
+    // (a lane taking its own row's value of one step reads a line per lane, and
+    // on rows of a power of two the lines evict each other before the next
+    // step: 1024^2 lower sweep 162 us)
+    const int gk = l % WAVE_CH, gr = l / WAVE_CH;
+    auto cell_row = [&](int u) { return (64 / WAVE_CH) * u + gr; };
     auto issue = [&](int c, int slot) {
 #pragma unroll
       for (int u = 0; u < WAVE_CH; ++u) {
         const int64_t p = p0 + (int64_t)(c * WAVE_CH + u) * 64;
         rc[slot][u] = coef[p];
-        rb[slot][u] = REV ? rhs[total - 1 - p] : rhs[p];
+        if (REV) {
+          rb[slot][u] = rhs[total - 1 - p];
+        } else {
+          const int r = cell_row(u), i = c * WAVE_CH + gk - r, j = 64 * w + r;
+          rb[slot][u] = rhs[(int64_t)std::min(j, ny - 1) * nx + std::max(0, std::min(i, nx - 1))];
+        }
         if (DIAG) rd[slot][u] = dinv[p];
       }
     };
@@ -239,12 +263,21 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int64_t to
         const int rb0 = (c % WAVE_SLOTS) * WAVE_CH;
 #pragma unroll
         for (int u = 0; u < WAVE_CH; ++u) {
-          WaveOp<T> op;
-          op.cb = rc[dd][u].x;
-          op.cl = rc[dd][u].y;
-          op.b = is_sentinel(rb[dd][u]) ? (T)__builtin_nan("") : rb[dd][u];
-          op.d = DIAG ? rd[dd][u] : (T)1;
-          r_op[rb0 + u][l] = op;
+          WaveOp<T>& op = r_op[rb0 + u].op[l];
+          T v = (T)rb[dd][u];
+          if (!REV) {
+            const int r = cell_row(u), i = c * WAVE_CH + gk - r;
+            if (64 * w + r >= ny || i < 0 || i >= nx) v = (T)0;
+          }
+          if (is_sentinel(v)) v = (T)__builtin_nan("");
+          if (REV) {
+            op = WaveOp<T>{rc[dd][u].x, rc[dd][u].y, v, DIAG ? rd[dd][u] : (T)1};
+          } else {
+            op.cb = rc[dd][u].x;
+            op.cl = rc[dd][u].y;
+            if (DIAG) op.d = rd[dd][u];
+            r_op[rb0 + gk].op[cell_row(u)].b = v;
+          }
         }
         lds_release();
         if (l == 0) __hip_atomic_store(&ready[c % WAVE_SLOTS], c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -296,7 +329,7 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int64_t to
     const T* rx = r_x + s0 % WAVE_XRING;
 #pragma unroll
     for (int u = 0; u < WAVE_CH; ++u) {
-      op[u] = r_op[r0 + u][l];
+      op[u] = r_op[r0 + u].op[l];
       xv[u] = rx[u];
     }
   };
@@ -599,35 +632,32 @@ __global__ __launch_bounds__(W3_THREADS) void k_wave3(int S, int TY, int64_t tot
   }
 }
 
-// positions of the lower layout -> cell (or -1 outside the grid)
+// 3D: positions of the lower layout -> cell (or -1 outside the grid)
 struct WaveDims {
-  int S, nx, ny, nz, TY;  // nz == 0: 2D grid
+  int S, nx, ny, nz, TY;
 };
 __device__ __forceinline__ int wave_cell(int64_t q, const WaveDims& g) {
   const int l = (int)(q & 63);
   const int64_t ws = q >> 6;
   const int w = (int)(ws / g.S), s = (int)(ws - (int64_t)w * g.S);
-  if (g.nz == 0) {
-    const int j = 64 * w + l, i = s - l;
-    return (i >= 0 && i < g.nx && j < g.ny) ? j * g.nx + i : -1;
-  }
   const int yy = l & 7, zz = l >> 3, ty = w % g.TY, tz = w / g.TY;
   const int x = s - yy - zz, y = 8 * ty + yy, z = 8 * tz + zz;
   return (x >= 0 && x < g.nx && y < g.ny && z < g.nz) ? (z * g.ny + y) * g.nx + x : -1;
 }
 
-// The gather takes the positions in tiles of 16 steps of one wave (or 3D
-// tile): a lane's 16 cells of a tile are consecutive in x, at most two
-// 128-byte lines of the cell-ordered vector, so a line is read by one or two
-// workgroups (positions in plain grid-stride order spread a line's 16 values
-// over four or five workgroups, usually on different XCDs and their L2s).
+// The 3D gather takes the positions in tiles of 16 steps of one tile of grid
+// lines: a lane's 16 cells are consecutive in x, at most two 128-byte lines of
+// the cell-ordered vector, so a line is read by one or two workgroups
+// (positions in plain grid-stride order spread a line's 16 values over four or
+// five workgroups, usually on different XCDs and their L2s).  2D sweeps read
+// the cell-ordered vector themselves.
 constexpr int WAVE_COPY_THREADS = 256;
 constexpr int WAVE_COPY_TILE = 16 * 64;  // positions per tile
 
 // column blockIdx.y: z + col * ldz (cell order) -> zs + col * total
-template <class T, class TR>
+template <class T>
 __global__ __launch_bounds__(WAVE_COPY_THREADS) void k_wave_gather(int64_t total, WaveDims g,
-                                                                   const TR* __restrict__ z, T* __restrict__ zs,
+                                                                   const double* __restrict__ z, T* __restrict__ zs,
                                                                    size_t ldz) {
   z += blockIdx.y * ldz;
   zs += blockIdx.y * total;
@@ -648,9 +678,45 @@ __global__ __launch_bounds__(WAVE_COPY_THREADS) void k_wave_gather(int64_t total
 }
 
 // out[cell] = ts[p] for the upper layout (cell of lower position total-1-p);
-// ts and the lower sweep's output ys are reset to the sentinel for the next
-// pair of sweeps.  Plain grid-stride order: its three streams of stores keep
-// more workgroups busy than the tiled order (measured faster on 1024^2).
+// what the next pair of sweeps polls is reset to the sentinel.  2D: a workgroup
+// turns a tile of 16 steps of one band round in LDS, so that a grid row's 16
+// values are stored together (8-byte stores a row apart, and resets of all of
+// ts and ys, took 33 us for 16 columns of 512^2); only lane 63 of a band is
+// polled.
+template <class T>
+__global__ __launch_bounds__(WAVE_COPY_THREADS) void k_wave_scatter2(WaveDims g, int64_t total, T* __restrict__ ts,
+                                                                     T* __restrict__ ys, T* __restrict__ t,
+                                                                     size_t ldt) {
+  __shared__ T sh[16][65];
+  ts += blockIdx.y * total;
+  ys += blockIdx.y * total;
+  t += blockIdx.y * ldt;
+  const int64_t q0 = blockIdx.x * (int64_t)WAVE_COPY_TILE;  // lower positions
+  const int l = threadIdx.x & 63;
+  T v[WAVE_COPY_TILE / WAVE_COPY_THREADS];
+#pragma unroll
+  for (int k = 0; k < WAVE_COPY_TILE / WAVE_COPY_THREADS; ++k)
+    v[k] = ts[total - 1 - (q0 + k * WAVE_COPY_THREADS + threadIdx.x)];
+#pragma unroll
+  for (int k = 0; k < WAVE_COPY_TILE / WAVE_COPY_THREADS; ++k) {
+    const int64_t q = q0 + k * WAVE_COPY_THREADS + threadIdx.x;
+    sh[(k * WAVE_COPY_THREADS + threadIdx.x) >> 6][l] = v[k];
+    if (l == 0) ts[total - 1 - q] = sentinel_of<T>(0);
+    if (l == 63) ys[q] = sentinel_of<T>(0);
+  }
+  __syncthreads();
+  const int64_t ws = q0 >> 6;
+  const int w = (int)(ws / g.S), s0 = (int)(ws - (int64_t)w * g.S), k = threadIdx.x & 15;
+#pragma unroll
+  for (int u = 0; u < WAVE_COPY_TILE / WAVE_COPY_THREADS; ++u) {
+    const int r = u * (WAVE_COPY_THREADS / 16) + (threadIdx.x >> 4), i = s0 + k - r, j = 64 * w + r;
+    if (i >= 0 && i < g.nx && j < g.ny) t[(int64_t)j * g.nx + i] = sh[k][r];
+  }
+}
+
+// 3D: plain grid-stride order; all of ts and the lower sweep's output ys are
+// reset (the faces that are polled touch every line).  Its three streams of
+// stores keep more workgroups busy than the tiled order.
 template <class T>
 __global__ __launch_bounds__(WAVE_COPY_THREADS) void k_wave_scatter(int64_t total, WaveDims g, T* __restrict__ ts,
                                                                     T* __restrict__ ys, T* __restrict__ t,
@@ -681,27 +747,24 @@ static uint64_t wave_limit_ticks() {
 }
 
 template <class T>
-void launch_wave_pair(const WaveGrid& g, const WaveSweep& lo, const WaveSweep& up, const void* z, bool z_f64, T* zs,
+void launch_wave_pair(const WaveGrid& g, const WaveSweep& lo, const WaveSweep& up, const double* z, T* zs,
                       T* ys, T* ts, T* t, int* abort_flag, hipStream_t s, int nb, size_t ldz, size_t ldt) {
   constexpr bool F32 = sizeof(T) == 4;
   using P2 = typename Pair<T>::type;
   const bool three = g.nz > 0;
   if (g.S % (2 * (three ? W3_CH : WAVE_CH)) != 0)
     fail(GMG_ERR_INVALID_ARG, "wavefront layout: steps not a multiple of two chunks");
+  if (!three && (g.S % 16 != 0 || (int64_t)g.W * g.S * 64 != g.total))
+    fail(GMG_ERR_INVALID_ARG, "wavefront layout: inconsistent 2D layout");
   if (three && (g.TY < 1 || (int64_t)g.W * g.S * 64 != g.total || g.S < 8))
     fail(GMG_ERR_INVALID_ARG, "wavefront layout: inconsistent 3D tiling");
   if (nb < 1 || nb > 65535 || (int64_t)g.W * nb > INT32_MAX) fail(GMG_ERR_INVALID_ARG, "wavefront sweep: bad column count");
-  const WaveDims dims{g.S, g.nx, g.ny, three ? g.nz : 0, three ? g.TY : 1};
-  const unsigned gb = (unsigned)std::min<int64_t>(4096, (g.total + WAVE_COPY_TILE - 1) / WAVE_COPY_TILE);
-  if (z_f64)
-    hipLaunchKernelGGL((k_wave_gather<T, double>), dim3(gb, nb), dim3(WAVE_COPY_THREADS), 0, s, g.total, dims,
-                       (const double*)z, zs, ldz);
-  else
-    hipLaunchKernelGGL((k_wave_gather<T, T>), dim3(gb, nb), dim3(WAVE_COPY_THREADS), 0, s, g.total, dims, (const T*)z,
-                       zs, ldz);
+  const WaveDims dims{g.S, g.nx, g.ny, g.nz, g.TY};
   const uint64_t lim = wave_limit_ticks();
   const dim3 grid((unsigned)(g.W * nb));
   if (three) {
+    const unsigned gb = (unsigned)std::min<int64_t>(4096, (g.total + WAVE_COPY_TILE - 1) / WAVE_COPY_TILE);
+    hipLaunchKernelGGL((k_wave_gather<T>), dim3(gb, nb), dim3(WAVE_COPY_THREADS), 0, s, g.total, dims, z, zs, ldz);
     // coefficient quads (z, y, x neighbours, reciprocal diagonal)
     auto co = [&](const WaveSweep& f) { return F32 ? (const Quad<T>*)f.coef32.p : (const Quad<T>*)f.coef.p; };
     const dim3 blk(W3_THREADS);
@@ -723,26 +786,32 @@ void launch_wave_pair(const WaveGrid& g, const WaveSweep& lo, const WaveSweep& u
     // lower factor: neighbour below first; upper factor: left neighbour first,
     // right-hand side = the lower sweep's output read backwards
     const dim3 blk(WAVE_THREADS);
-    if (lo.has_diag)
-      hipLaunchKernelGGL((k_wave<T, true, true, false>), grid, blk, 0, s, g.S, g.nx, g.total, co(lo), di(lo), zs,
-                         ys, abort_flag, lim, nb);
-    else
-      hipLaunchKernelGGL((k_wave<T, false, true, false>), grid, blk, 0, s, g.S, g.nx, g.total, co(lo), di(lo), zs,
-                         ys, abort_flag, lim, nb);
-    if (up.has_diag)
-      hipLaunchKernelGGL((k_wave<T, true, false, true>), grid, blk, 0, s, g.S, g.nx, g.total, co(up), di(up), ys,
-                         ts, abort_flag, lim, nb);
-    else
-      hipLaunchKernelGGL((k_wave<T, false, false, true>), grid, blk, 0, s, g.S, g.nx, g.total, co(up), di(up), ys,
-                         ts, abort_flag, lim, nb);
+    auto lower = [&](auto diag) {
+      hipLaunchKernelGGL((k_wave<T, double, decltype(diag)::value, true, false>), grid, blk, 0, s, g.S, g.nx, g.ny,
+                         g.total, co(lo), di(lo), z, ldz, ys, abort_flag, lim, nb);
+    };
+    if (lo.has_diag) lower(std::true_type());
+    else lower(std::false_type());
+    auto upper = [&](auto diag) {
+      hipLaunchKernelGGL((k_wave<T, T, decltype(diag)::value, false, true>), grid, blk, 0, s, g.S, g.nx, g.ny, g.total,
+                         co(up), di(up), ys, (size_t)g.total, ts, abort_flag, lim, nb);
+    };
+    if (up.has_diag) upper(std::true_type());
+    else upper(std::false_type());
   }
-  const unsigned gs = (unsigned)std::min<int64_t>(4096, (g.total + WAVE_COPY_THREADS - 1) / WAVE_COPY_THREADS);
-  hipLaunchKernelGGL((k_wave_scatter<T>), dim3(gs, nb), dim3(WAVE_COPY_THREADS), 0, s, g.total, dims, ts, ys, t, ldt);
+  if (three) {
+    const unsigned gs = (unsigned)std::min<int64_t>(4096, (g.total + WAVE_COPY_THREADS - 1) / WAVE_COPY_THREADS);
+    hipLaunchKernelGGL((k_wave_scatter<T>), dim3(gs, nb), dim3(WAVE_COPY_THREADS), 0, s, g.total, dims, ts, ys, t, ldt);
+  } else {
+    // S is a multiple of 16 steps (checked above): tiles do not cross bands
+    hipLaunchKernelGGL((k_wave_scatter2<T>), dim3((unsigned)(g.total / WAVE_COPY_TILE), nb), dim3(WAVE_COPY_THREADS), 0,
+                       s, dims, g.total, ts, ys, t, ldt);
+  }
   HIPCK(hipGetLastError());
 }
-template void launch_wave_pair<double>(const WaveGrid&, const WaveSweep&, const WaveSweep&, const void*, bool,
+template void launch_wave_pair<double>(const WaveGrid&, const WaveSweep&, const WaveSweep&, const double*,
                                        double*, double*, double*, double*, int*, hipStream_t, int, size_t, size_t);
-template void launch_wave_pair<float>(const WaveGrid&, const WaveSweep&, const WaveSweep&, const void*, bool,
+template void launch_wave_pair<float>(const WaveGrid&, const WaveSweep&, const WaveSweep&, const double*,
                                       float*, float*, float*, float*, int*, hipStream_t, int, size_t, size_t);
 
 }  // namespace gmg
