@@ -11,6 +11,7 @@
 //   k_cols_from_rows / k_rows_from_cols: between the caller's (N, nrhs)
 //                    row-major arrays and the column-major batch
 #include <algorithm>
+#include <type_traits>
 
 #include "gmg_internal.h"
 #include "kcommon.h"
@@ -20,25 +21,34 @@ namespace gmg {
 constexpr int BROWS = 256;    // rows per workgroup of the sparse products
 constexpr int BCAP = 3072;    // (column, value) pairs of a tile staged in LDS
 
+constexpr int SPMM_LOADS = 16;  // loads of x a lane has in flight
+
 // One workgroup owns BROWS consecutive rows.  When the tile's entries fit in
 // LDS they are first staged there with coalesced loads; then each lane runs
 // its own row, reading the entry once and the nb columns' values of x at that
 // entry (consecutive lanes hold consecutive rows, so for fixed column and
-// entry position the gathers are nearly contiguous).
+// entry position the gathers are nearly contiguous).  Column group blockIdx.y
+// of CB columns.
 // MODE 0: y = A x; 1: y = b - A x; 2: y = b - A (P e), x indexed through agg
 // and rsx apart from row to row.
-template <class T, class TB, int MODE>
+template <class T, class TB, int MODE, int CB>
 __global__ __launch_bounds__(BROWS) void k_spmm(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const T* __restrict__ v, const int* __restrict__ agg,
                                                 const T* __restrict__ x, size_t ldx, size_t rsx,
                                                 const TB* __restrict__ b, size_t ldb, T* __restrict__ y, size_t ldy,
                                                 int nb) {
+  constexpr int U = SPMM_LOADS / CB;  // entries of a row in flight
   __shared__ int sc[BCAP];
   __shared__ T sv[BCAP];
   const int r0 = blockIdx.x * BROWS;
   const int r1 = min(r0 + BROWS, n);
   const int e0 = rp[r0], e1 = rp[r1];
   const int row = r0 + threadIdx.x;
+  const int c0 = blockIdx.y * CB;
+  nb = min(CB, nb - c0);
+  x += c0 * ldx;
+  y += c0 * ldy;
+  if (MODE != 0) b += c0 * ldb;
   const bool staged = e1 - e0 <= BCAP;
   if (staged) {
     for (int e = e0 + threadIdx.x; e < e1; e += BROWS) {
@@ -48,30 +58,41 @@ __global__ __launch_bounds__(BROWS) void k_spmm(int n, const int* __restrict__ r
     __syncthreads();
   }
   if (row >= r1) return;
-  T acc[BATCH_MAX];
+  TB bv[CB];
+  T acc[CB];
 #pragma unroll
-  for (int c = 0; c < BATCH_MAX; ++c) acc[c] = (T)0;
+  for (int c = 0; c < CB; ++c) {
+    acc[c] = (T)0;
+    if (MODE != 0) bv[c] = c < nb ? b[c * ldb + row] : (TB)0;
+  }
   const int p0 = rp[row], p1 = rp[row + 1];
-  for (int p = p0; p < p1; ++p) {
-    int j;
-    T a;
-    if (staged) {
-      j = sc[p - e0];
-      a = sv[p - e0];
-    } else {
-      j = ci[p];
-      a = v[p];
+  for (int p = p0; p < p1; p += U) {
+    int j[U];
+    T a[U], xv[U][CB];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = min(p + u, p1 - 1);
+      j[u] = staged ? sc[q - e0] : ci[q];
+      a[u] = staged ? sv[q - e0] : v[q];
     }
-    if (MODE == 2) j = agg[j];
-    T xv[BATCH_MAX];
+    if (MODE == 2) {
 #pragma unroll
-    for (int c = 0; c < BATCH_MAX; ++c) xv[c] = c < nb ? x[c * ldx + (MODE == 2 ? j * rsx : j)] : (T)0;
+      for (int u = 0; u < U; ++u) j[u] = agg[j[u]];
+    }
 #pragma unroll
-    for (int c = 0; c < BATCH_MAX; ++c) acc[c] += a * xv[c];
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < CB; ++c) xv[u][c] = c < nb ? x[c * ldx + (MODE == 2 ? j[u] * rsx : j[u])] : (T)0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (p + u < p1) {
+#pragma unroll
+        for (int c = 0; c < CB; ++c) acc[c] += a[u] * xv[u][c];
+      }
   }
 #pragma unroll
-  for (int c = 0; c < BATCH_MAX; ++c)
-    if (c < nb) y[c * ldy + row] = MODE == 0 ? acc[c] : (T)b[c * ldb + row] - acc[c];
+  for (int c = 0; c < CB; ++c)
+    if (c < nb) y[c * ldy + row] = MODE == 0 ? acc[c] : (T)bv[c] - acc[c];
 }
 
 template <class T, class TB, int MODE>
@@ -79,8 +100,21 @@ static void spmm_launch(int n, const int* rp, const int* ci, const T* v, const i
                         size_t rsx, const TB* b, size_t ldb, T* y, size_t ldy, int nb, hipStream_t s) {
   if (n <= 0) return;
   if (nb < 1 || nb > BATCH_MAX) fail(GMG_ERR_INVALID_ARG, "spmm: bad column count");
-  hipLaunchKernelGGL((k_spmm<T, TB, MODE>), dim3((n + BROWS - 1) / BROWS), dim3(BROWS), 0, s, n, rp, ci, v, agg, x,
-                     ldx, rsx, b, ldb, y, ldy, nb);
+  const int blocks = (n + BROWS - 1) / BROWS;
+  auto go = [&](auto cb) {
+    constexpr int CB = decltype(cb)::value;
+    hipLaunchKernelGGL((k_spmm<T, TB, MODE, CB>), dim3(blocks, (nb + CB - 1) / CB), dim3(BROWS), 0, s, n, rp, ci, v,
+                       agg, x, ldx, rsx, b, ldb, y, ldy, nb);
+  };
+  // All columns in one workgroup read the matrix once; with few workgroups a
+  // product is a row's chain of loads, one trip to L2 per entry, and columns
+  // go to more workgroups with several entries in flight instead (us, product
+  // / fine residual of 16 columns, with 16, 4 and 2 columns a workgroup:
+  // 32^2 7.5 / 8.1, 5.6 / 5.2, 4.7 / 5.3; 160^2 9.5 / 13.3, 7.8 / 10.1, 8.1 /
+  // 10.3; 512^2, 4 and 8: 37, 29 against 28).
+  if (blocks <= 64) go(std::integral_constant<int, 2>());
+  else if (blocks < 256) go(std::integral_constant<int, 4>());
+  else go(std::integral_constant<int, BATCH_MAX>());
   HIPCK(hipGetLastError());
 }
 
