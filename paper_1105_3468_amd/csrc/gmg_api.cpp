@@ -1970,8 +1970,9 @@ static void vcycle_batch(Solver& S, const double* z, size_t ldz, double* q, size
     for (int c = 0; c < nb; ++c) coarse_apply<T>(S, rc + c * ldc, ec + c * ldc);
   }
   {
-    Prof p(S, PC_PROLONG, nb * ((double)S.n * (4 + 2 * sz + 8) + (double)S.nc * sz));
-    launch_prolong_cols<T>(S.n, S.agg.p, t, ld, ec, lc, q, ldq, nb, s);
+    const bool reset_t = !S.wave && !S.fine_nd;  // as in the single cycle
+    Prof p(S, PC_PROLONG, nb * ((double)S.n * (4 + (reset_t ? 2 : 1) * sz + 8) + (double)S.nc * sz));
+    launch_prolong_cols<T>(S.n, S.agg.p, t, ld, ec, lc, q, ldq, nb, reset_t, s);
   }
 }
 
@@ -2021,8 +2022,9 @@ static void vcycle_adjoint_batch(Solver& S, const double* z, size_t ldz, double*
     }
   }
   {
-    Prof p(S, PC_PROLONG, nb * ((double)S.n * 28 + (double)S.nc * 8));
-    launch_prolong_cols<double>(S.n, S.agg.p, B.at.p, ld, B.aec.p, lc, q, ldq, nb, s);
+    const bool reset_t = !S.wave && !S.fine_nd;
+    Prof p(S, PC_PROLONG, nb * ((double)S.n * (reset_t ? 28 : 20) + (double)S.nc * 8));
+    launch_prolong_cols<double>(S.n, S.agg.p, B.at.p, ld, B.aec.p, lc, q, ldq, nb, reset_t, s);
   }
 }
 

@@ -425,7 +425,7 @@ void launch_restrict_cols(int nc, const int* aptr, const int* amem, const T* z, 
 // q_c = t_c + P ec_c (widened to FP64); t_c <- sentinel
 template <class T>
 void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, CoarseCols lc, double* q, size_t ldq,
-                         int nb, hipStream_t s);
+                         int nb, bool reset_t, hipStream_t s);
 // out_c[i] = X[i * nrhs + c0 + c] (c < nb), and the reverse
 void launch_cols_from_rows(const double* X, int nrhs, int c0, double* out, size_t ld, int64_t n, int nb,
                            hipStream_t s);

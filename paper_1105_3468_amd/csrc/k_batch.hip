@@ -237,17 +237,19 @@ template void launch_restrict_cols<double>(int, const int*, const int*, const do
 template void launch_restrict_cols<float>(int, const int*, const int*, const float*, size_t, float*, float*,
                                           CoarseCols, int, hipStream_t);
 
-// q_c[k] = t_c[k] + ec_c[agg[k]] (in T, widened); t_c[k] <- sentinel
+// q_c[k] = t_c[k] + ec_c[agg[k]] (in T, widened); t_c[k] <- sentinel if
+// reset_t (t was polled)
 template <class T>
 __global__ void k_prolong_cols(int n, const int* __restrict__ agg, T* __restrict__ t, size_t ldt,
-                               const T* __restrict__ ec, size_t ldc, double* __restrict__ q, size_t ldq) {
+                               const T* __restrict__ ec, size_t ldc, double* __restrict__ q, size_t ldq,
+                               int reset_t) {
   t += blockIdx.y * ldt;
   ec += blockIdx.y * ldc;
   q += blockIdx.y * ldq;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
     const T val = t[k] + ec[agg[k]];
     q[k] = (double)val;
-    t[k] = sentinel_of<T>(0);
+    if (reset_t) t[k] = sentinel_of<T>(0);
   }
 }
 // The same from rows of CW coarse columns: a lane reads its aggregate's row
@@ -255,7 +257,7 @@ __global__ void k_prolong_cols(int n, const int* __restrict__ agg, T* __restrict
 template <class T, int CW>
 __global__ __launch_bounds__(256) void k_prolong_rows(int n, const int* __restrict__ agg, T* __restrict__ t,
                                                       size_t ldt, const T* __restrict__ ec, double* __restrict__ q,
-                                                      size_t ldq, int nb) {
+                                                      size_t ldq, int nb, int reset_t) {
   constexpr int V = 16 / sizeof(T);
   typedef T vec __attribute__((ext_vector_type(V)));
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
@@ -271,30 +273,30 @@ __global__ __launch_bounds__(256) void k_prolong_rows(int n, const int* __restri
       if (c < nb) {
         const T val = tv[c] + e[c / V][c % V];
         q[c * ldq + k] = (double)val;
-        t[c * ldt + k] = sentinel_of<T>(0);
+        if (reset_t) t[c * ldt + k] = sentinel_of<T>(0);
       }
   }
 }
 template <class T>
 void launch_prolong_cols(int n, const int* agg, T* t, size_t ldt, const T* ec, CoarseCols lc, double* q, size_t ldq,
-                         int nb, hipStream_t s) {
+                         int nb, bool reset_t, hipStream_t s) {
   if (n <= 0) return;
   if (lc.col == 1) {
     const unsigned g = (unsigned)std::min<int64_t>(4096, ((int64_t)n + 255) / 256);
 #define GMG_PROLONG(CW_) \
-  hipLaunchKernelGGL((k_prolong_rows<T, CW_>), dim3(g), dim3(256), 0, s, n, agg, t, ldt, ec, q, ldq, nb)
+  hipLaunchKernelGGL((k_prolong_rows<T, CW_>), dim3(g), dim3(256), 0, s, n, agg, t, ldt, ec, q, ldq, nb, reset_t ? 1 : 0)
     GMG_COLS_WIDTH(lc.width, GMG_PROLONG);
 #undef GMG_PROLONG
   } else {
     const unsigned g = (unsigned)std::min<int64_t>(1024, ((int64_t)n + 255) / 256);
-    hipLaunchKernelGGL(k_prolong_cols<T>, dim3(g, nb), dim3(256), 0, s, n, agg, t, ldt, ec, lc.col, q, ldq);
+    hipLaunchKernelGGL(k_prolong_cols<T>, dim3(g, nb), dim3(256), 0, s, n, agg, t, ldt, ec, lc.col, q, ldq, reset_t ? 1 : 0);
   }
   HIPCK(hipGetLastError());
 }
 template void launch_prolong_cols<double>(int, const int*, double*, size_t, const double*, CoarseCols, double*, size_t,
-                                          int, hipStream_t);
+                                          int, bool, hipStream_t);
 template void launch_prolong_cols<float>(int, const int*, float*, size_t, const float*, CoarseCols, double*, size_t,
-                                         int, hipStream_t);
+                                         int, bool, hipStream_t);
 
 // out_c[i] = X[i * nrhs + c0 + c] for c < nb (column blockIdx.y), and back
 __global__ void k_cols_from_rows(const double* __restrict__ X, int nrhs, int c0, double* __restrict__ out, size_t ld,
