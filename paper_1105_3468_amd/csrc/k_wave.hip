@@ -39,7 +39,7 @@ namespace gmg {
 // stream the operands of chunks of WAVE_CH steps into an LDS ring of
 // WAVE_SLOTS chunks (producer k takes chunks k, k + P, k + 2P, ..., each
 // keeping WAVE_D chunks of loads in flight) and flag each chunk ready; the
-// last wave polls the previous band's boundary values into a second ring of
+// last waves poll the previous band's boundary values into a second ring of
 // WAVE_XRING steps.  The computing wave thus issues no global loads: its
 // stores, which share the in-order memory counter with loads, never hold it
 // up.  Its step is a handful of instructions (a wave issues at most one per
@@ -53,9 +53,18 @@ constexpr int WAVE_D = 2;
 constexpr int WAVE_SLOTS = 6;
 constexpr int WAVE_RING = WAVE_CH * WAVE_SLOTS;
 constexpr int WAVE_PRODUCERS = 4;
+// A poll's trip through memory takes about 1.2 us.  Two pollers of 8 steps each
+// look twice as often as one, with an eighth of the lines of one of 64 steps
+// (as many as are published handed over each time): pair on 1024^2 301 -> 279
+// us; 3 pollers of 8 steps 285, 2 of 16 298, 3 of 4 320, 1 of 8 387 (too few
+// steps a trip).  More than eight waves would halve the registers of a SIMD's
+// waves (4 pollers: one band 106 -> 140 us).
+constexpr int WAVE_POLLERS = 2;
+constexpr int WAVE_XG = 8;  // boundary values a poller takes at a time
 constexpr int WAVE_XRING = 256;
-constexpr int WAVE_THREADS = 64 * (2 + WAVE_PRODUCERS);
-static_assert(WAVE_XRING % WAVE_CH == 0, "a chunk's boundary values must not wrap around the ring");
+constexpr int WAVE_THREADS = 64 * (1 + WAVE_PRODUCERS + WAVE_POLLERS);
+static_assert(WAVE_XRING % WAVE_XG == 0 && WAVE_XG <= 64 && WAVE_XRING % WAVE_CH == 0,
+              "boundary values must not wrap around the ring");
 
 // Lane l receives lane l - 1's value v; lane 0 keeps lane0 (DPP wave_shr:1
 // without bound control leaves the destination of a lane with no source).
@@ -185,28 +194,23 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int ny, in
   // boundary values exist for steps s < xn (the previous band's lane 63 at
   // step s + 63); later steps are padding
   const int xn = S - 63;
-  if (role == 1 + WAVE_PRODUCERS) {
+  if (role > WAVE_PRODUCERS) {
     // ------------------------------------------- previous band's boundary
+    // poller k takes groups k, k + WAVE_POLLERS, .. of WAVE_XG steps and hands
+    // each over after the group before it
     if (w == 0) return;
     const T* prev = out + ((int64_t)(w - 1) * S + 63) * 64 + 63;
-    int next = 0;
     const uint64_t t0 = wall_clock64();
     unsigned it = 0;
 #pragma clang loop unroll(disable)
-    while (next < xn) {
-      // ring space: slots of steps next .. next + 63 were used WAVE_XRING steps earlier
-      if (!wait_lds_at_least<4>(&consumed, next + 64 - WAVE_XRING, abort_flag, limit)) return;
-      const int s = next + l;
-      const T v = s < xn ? ld_agent(prev + (int64_t)s * 64) : (T)0;
-      const uint64_t pend = __ballot(s < xn && is_sentinel(v));
-      const int k = pend ? (int)__builtin_ctzll(pend) : 64;  // leading published steps
-      if (k > 0) {
-        if (l < k) r_x[s % WAVE_XRING] = v;
-        lds_release();
-        next = std::min(next + k, xn);
-        if (l == 0) __hip_atomic_store(&xready, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        __builtin_amdgcn_s_sleep(1);
+    for (int s0 = (role - 1 - WAVE_PRODUCERS) * WAVE_XG; s0 < xn; s0 += WAVE_POLLERS * WAVE_XG) {
+      // ring space: these slots were used WAVE_XRING steps earlier
+      if (!wait_lds_at_least<4>(&consumed, s0 + WAVE_XG - WAVE_XRING, abort_flag, limit)) return;
+      const int s = s0 + l;
+      const bool mine = l < WAVE_XG && s < xn;
+      T v = mine ? ld_agent(prev + (int64_t)s * 64) : (T)0;
+#pragma clang loop unroll(disable)
+      while (__ballot(is_sentinel(v))) {
         if ((++it & 63u) == 0) {
           if (ld_agent(abort_flag)) return;
           if (wall_clock64() - t0 > limit) {
@@ -214,7 +218,14 @@ __global__ __launch_bounds__(WAVE_THREADS) void k_wave(int S, int nx, int ny, in
             return;
           }
         }
+        v = mine ? ld_agent(prev + (int64_t)s * 64) : (T)0;
       }
+      if (mine) r_x[s % WAVE_XRING] = v;
+      if (!wait_lds_at_least<0>(&xready, s0, abort_flag, limit)) return;
+      lds_acquire();
+      lds_release();
+      if (l == 0)
+        __hip_atomic_store(&xready, std::min(s0 + WAVE_XG, xn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     return;
   }

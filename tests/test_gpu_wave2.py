@@ -28,7 +28,7 @@ def _grid5(nx, ny, seed):
     return a.indptr.astype(np.int32), a.indices.astype(np.int32), a.data
 
 
-@pytest.mark.parametrize("nx,ny", [(3, 200), (17, 63), (16, 64), (33, 65), (65, 128), (1, 70), (128, 129), (200, 3)])
+@pytest.mark.parametrize("nx,ny", [(3, 200), (17, 63), (16, 64), (33, 65), (65, 128), (300, 130), (1, 70), (128, 129), (200, 3)])
 def test_wave2_bitwise_equal_to_level_sweeps(nx, ny):
     A = _grid5(nx, ny, nx)
     n = nx * ny
