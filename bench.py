@@ -107,9 +107,8 @@ def copy_calibration():
 def _alg_bytes_doc():
     return ("spmv 12*nnz+20*N (FP64 CSR, int32 indices); sweep: 12 per dependency entry + "
             "(8 + rhs + 2*val [+ diag] [+ reset]) per row; resid_restrict 12*nnz + 40*N + 20*N_c; "
-            "ortho 8*N*(2k+3)+8*k^2 for k basis vectors from 33 to 384 (one Gram-corrected projection), "
-            "8*N*(3k+6) up to 32 (two classical Gram-Schmidt passes), "
-            "8*N*(3k-k_last+4*blocks)+8*k^2 beyond 384 (the projection over blocks of 384)")
+            "ortho 8*N*(2k+3)+8*k^2 for k basis vectors up to 384 (one Gram-corrected projection), "
+            "8*N*(2k+2*blocks+2)+8*k^2 beyond (the first read over blocks of at most 384 vectors)")
 
 
 def run_cpu_baseline(p):

@@ -1609,12 +1609,12 @@ struct OneResult {
 
 // Flexible GMRES(m) with right preconditioning (Algorithm 1's accelerator with
 // z_j = B~^{-1} v_j kept), Givens rotations on the host (O(m) scalars per
-// step).  Orthogonalisation: classical Gram-Schmidt applied twice while the
-// basis is short (up to 32 vectors); beyond, one projection whose coefficients
-// are corrected with the basis' Gram matrix G = V^T V, c = (2I - G) V^T w
-// (equal to the second pass's V^T (w - V h) = h - G h), where each new row of
-// G comes from the products V^T w_new taken in the same read of V that forms
-// w_new: two reads of V per step instead of three.
+// step).  Orthogonalisation: one projection whose coefficients are corrected
+// with the basis' Gram matrix G = V^T V, c = (2I - G) V^T w (equal to a second
+// Gram-Schmidt pass's V^T (w - V h) = h - G h), two reads of V per step.  Each
+// new row of G comes from the products V^T w_new taken in the read of V that
+// forms w_new; beyond many_max() vectors, from a second product in the next
+// projection's first read.
 static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b, double* x, double tol,
                         int maxit, int m, bool x0_given) {
   hipStream_t s = S.s;

@@ -346,7 +346,10 @@ struct BatchCols {
   int nb = 1;
   size_t vcol = 0, wcol = 0, rcol = 0, hcol = 0, gcol = 0;
 };
-// result[0..k) = V[0..k)^T w   (V rows with stride ld)
+// k <= 32: result[0..k) = V[0..k)^T w (V rows with stride ld).  When the
+// reduction is small, this and launch_update_gram leave their sums as partials
+// in rw and the next of multidot, update_gram, normalize_gram adds them:
+// update_gram then stores h, and its own products stay in rw.
 void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t n,
                      RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
 // c = (2I - G) h (d = c - h is stored), w -= V[0..k)^T c, then result[0..k) =

@@ -410,8 +410,13 @@ constexpr int W3_SLOTS = 10;
 constexpr int W3_RING = W3_CH * W3_SLOTS;
 constexpr int W3_PRODUCERS = 4;
 constexpr int W3_XRING = 128;
-constexpr int W3_THREADS = 64 * (2 + W3_PRODUCERS);
-static_assert(W3_XRING % 8 == 0 && W3_XRING % W3_CH == 0, "ring rows must not wrap within a poll or a chunk");
+// As in 2D (pair with its copies, us, FP64, 20^3 / 64^3 / 128^3: one poller of
+// 8 steps 41.3 / 111 / 271, two of 4 39.6 / 107 / 265, two of 8 42.3 / 119 /
+// 293, three of 4 41.3 / 108 / 273, three of 2 40.5 / 110 / 288).
+constexpr int W3_POLLERS = 2;
+constexpr int W3_XG = 4;  // steps of the faces a poller takes at a time
+constexpr int W3_THREADS = 64 * (1 + W3_PRODUCERS + W3_POLLERS);
+static_assert(W3_XRING % W3_XG == 0 && W3_XG <= 8 && W3_XRING % W3_CH == 0, "ring rows must not wrap within a poll or a chunk");
 
 // coefficients of one position of a 3D layout: z - 1, y - 1, x - 1
 // neighbours (z + 1, y + 1, x + 1 for upper factors) and the reciprocal
@@ -439,7 +444,7 @@ __device__ __forceinline__ double lane_up8(int addr, double v) {
 }
 
 // One workgroup per tile: wave 0 computes, waves 1 .. W3_PRODUCERS stream
-// the operands into an LDS ring as in the 2D kernel, the last wave polls the
+// the operands into an LDS ring as in the 2D kernel, the last ones poll the
 // two neighbouring tiles' faces.  LOWER: terms in the order z, y, x (the
 // ascending column order of a lower factor), else x, y, z.  nb columns as in
 // the 2D kernel: workgroup w * nb + r runs tile w of column r.
@@ -477,39 +482,31 @@ __global__ __launch_bounds__(W3_THREADS) void k_wave3(int S, int TY, int64_t tot
   // steps only meet zero coefficients
   const int xn = S - 7;
   const bool hy = ty > 0, hz = tz > 0;
-  if (role == 1 + W3_PRODUCERS) {
+  if (role > W3_PRODUCERS) {
     // ------------------------------------------- the neighbouring faces
     if (!hy && !hz) return;
-    // lane l polls step next + l / 8: face y - 1 at zz = l % 8 (the y
-    // neighbour's lane 8 zz + 7) and face z - 1 at yy = l % 8 (the z
-    // neighbour's lane 56 + yy)
+    // poller k takes groups k, k + W3_POLLERS, .. of W3_XG steps and hands
+    // each over after the group before it.  Lane l polls step s0 + l / 8: face
+    // y - 1 at zz = l % 8 (the y neighbour's lane 8 zz + 7) and face z - 1 at
+    // yy = l % 8 (the z neighbour's lane 56 + yy)
     const int j = l & 7, sl = l >> 3;
     const T* py = out + ((int64_t)(w - (hy ? 1 : 0)) * S + 7) * 64 + 8 * j + 7;
     const T* pz = out + ((int64_t)(w - (hz ? TY : 0)) * S + 7) * 64 + 56 + j;
-    int next = 0;
     const uint64_t t0 = wall_clock64();
     unsigned it = 0;
 #pragma clang loop unroll(disable)
-    while (next < xn) {
-      if (!wait_lds_at_least<4>(&consumed, next + 8 - W3_XRING, abort_flag, limit)) return;
-      const int s = next + sl;
+    for (int s0 = (role - 1 - W3_PRODUCERS) * W3_XG; s0 < xn; s0 += W3_POLLERS * W3_XG) {
+      if (!wait_lds_at_least<4>(&consumed, s0 + W3_XG - W3_XRING, abort_flag, limit)) return;
+      const int s = s0 + sl;
+      const bool mine = sl < W3_XG && s < xn;
       T vy = (T)0, vz = (T)0;
-      if (s < xn) {
-        if (hy) vy = ld_agent(py + (int64_t)s * 64);
-        if (hz) vz = ld_agent(pz + (int64_t)s * 64);
-      }
-      const uint64_t pend = __ballot(s < xn && (is_sentinel(vy) || is_sentinel(vz)));
-      const int k = pend ? (int)(__builtin_ctzll(pend) >> 3) : 8;  // leading complete steps
-      if (k > 0) {
-        if (sl < k) {
-          r_by[s % W3_XRING][j] = vy;
-          r_bz[s % W3_XRING][j] = vz;
-        }
-        lds_release();
-        next = std::min(next + k, xn);
-        if (l == 0) __hip_atomic_store(&xready, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        __builtin_amdgcn_s_sleep(1);
+      auto look = [&] {
+        if (mine && hy) vy = ld_agent(py + (int64_t)s * 64);
+        if (mine && hz) vz = ld_agent(pz + (int64_t)s * 64);
+      };
+      look();
+#pragma clang loop unroll(disable)
+      while (__ballot(is_sentinel(vy) || is_sentinel(vz))) {
         if ((++it & 63u) == 0) {
           if (ld_agent(abort_flag)) return;
           if (wall_clock64() - t0 > limit) {
@@ -517,7 +514,17 @@ __global__ __launch_bounds__(W3_THREADS) void k_wave3(int S, int TY, int64_t tot
             return;
           }
         }
+        look();
       }
+      if (mine) {
+        r_by[s % W3_XRING][j] = vy;
+        r_bz[s % W3_XRING][j] = vz;
+      }
+      if (!wait_lds_at_least<0>(&xready, s0, abort_flag, limit)) return;
+      lds_acquire();
+      lds_release();
+      if (l == 0)
+        __hip_atomic_store(&xready, std::min(s0 + W3_XG, xn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     return;
   }
