@@ -129,7 +129,7 @@ struct Solver {
   BatchWork bw;                // multi-right-hand-side solve (allocated on first use)
   DBuf<int> abort_flag;
   double* hpin = nullptr;      // pinned host scalars, then two Hessenberg columns (kPinCol each)
-  hipEvent_t colev[2] = {nullptr, nullptr};  // a column's copy into hpin finished
+  hipEvent_t colev[2] = {nullptr, nullptr};  // a step's column is in hpin
   gmg_info info{};
   int log_every = 0;           // GMG_LOG=k prints the residual estimate every k steps
   std::vector<double> hist;    // FGMRES residual estimates of the last solve, per step
