@@ -78,7 +78,8 @@ typedef struct {
   int precond_fp32;     /* 1: the whole preconditioner runs in FP32 on FP32 copies of
                            A and of the factors; the Krylov part stays FP64          */
   int x0_given;         /* 1: x holds the initial guess on entry, else x0 = 0         */
-  int sweep_waves;      /* resident waves of the triangular sweeps (0: auto)          */
+  int sweep_waves;      /* waves that run a device-wide level sweep, rounded up to
+                           a multiple of four per column of a batch (0: auto)         */
   int coarse_order;     /* numbering of the aggregates, hence of A_c and its ILUT
                            factors: 0 by smallest fine index; 1 nested dissection
                            of A_c's graph (default)                                   */

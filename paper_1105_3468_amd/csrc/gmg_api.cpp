@@ -901,6 +901,8 @@ static void build_sweep(Sweep& sw, int n, const std::vector<int>& dep_rp, const 
     else d2d(sw.dinv.p, dev_dinv, n, s);
     launch_cast_f32(sw.dinv.p, sw.dinv32.p, n, s);
   }
+  sw.ticket.alloc(kSweepCols * kTicketStride);
+  launch_fill_u32(sw.ticket.p, 0u, sw.ticket.n, s);
   {
     // a few levels of look-ahead: more resident waves would only poll
     const double per_level = levels > 0 ? (double)sw.nchunks / levels : 1.0;
@@ -1033,7 +1035,11 @@ static void run_tri(Solver& S, Sweep& sw, const void* rhs, bool rhs_f64, T* out,
                            nb, ldr, ldo);
     return;
   }
-  const int waves = S.opt.sweep_waves > 0 ? S.opt.sweep_waves : sw.waves;
+  // more than kSweepWaves waves over all columns only poll (16 columns of a
+  // 50k-row graph, us a sweep: 103 with 2048 waves, 137 with 16 times one
+  // column's; 3 columns of 200k rows 89, 102; of 500k rows 181, 255)
+  constexpr int kSweepWaves = 2048;
+  const int waves = S.opt.sweep_waves > 0 ? S.opt.sweep_waves : std::min(kSweepWaves, sw.waves * nb);
   launch_sweep<T>(sw, F32 ? (const T*)sw.dval32.p : (const T*)sw.dval.p, di, rhs, rhs_f64, out, reset, waves,
                   S.opt.sweep_kernel == 1, S.abort_flag.p, S.s, nb, ldr, ldo);
 }

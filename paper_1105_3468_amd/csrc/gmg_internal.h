@@ -118,6 +118,7 @@ struct CuSweep {
   DBuf<float> wval32, dinv_e32;
 };
 
+constexpr int kSweepCols = 16, kTicketStride = 64;  // columns of a sweep at most; counters a line apart
 // A triangular factor prepared for the synchronisation-free sweep: row rows[e]
 // (entries e in schedule order: by dependency level, ascending row inside a
 // level) has dependency entries dcol[dp[e] .. dp[e+1]) with values dval.
@@ -132,6 +133,7 @@ struct Sweep {
   DBuf<int> chunk, rows, dp, dcol;
   DBuf<double> dval, dinv;
   DBuf<float> dval32, dinv32;
+  DBuf<unsigned> ticket;     // a counter per column of the groups of chunks drawn, zero between sweeps
   bool has_diag = false;
   int waves = 0;             // resident waves (a few dependency levels of look-ahead)
   // consecutive level ranges, one launch each: chunks [seg_c0[g], seg_c1[g])

@@ -7,10 +7,11 @@
 // a wave never holds two rows where one depends on the other.  A chunk gives
 // each of its rows G lanes (G a power of two chosen per level from the
 // longest row, so that a lane reads at most one batch of entries); the lanes'
-// partial sums meet in a shuffle reduction.  Chunk t belongs to wave t of the
-// launch and workgroups start in order, so every row a wave waits for belongs
-// to a chunk that an already-running wave holds: the sweep always makes
-// progress.  A result is published with one relaxed agent-scope store
+// partial sums meet in a shuffle reduction.  Workgroups draw their chunks from
+// a global counter in schedule order, so every row a wave waits for belongs to
+// a chunk that an already-running wave holds: the sweep makes progress however
+// its workgroups are started, whatever else runs on the device.  A result is
+// published with one relaxed agent-scope store
 // and doubles as its own ready flag: consumers poll with relaxed agent-scope
 // loads until the value differs from the NaN sentinel the buffer was reset to.
 // Every wait is bounded by a wall-clock limit; a timeout raises a device flag
@@ -210,33 +211,53 @@ __device__ __forceinline__ bool chunk_rows(const Src& src, const int* __restrict
   return true;
 }
 
-// A wave per chunk, in schedule order.  500k-row graph, 24 levels, 15.6k
-// chunks: 80 us a sweep, against 190 us when persistent waves drew their
-// chunks from one counter (12 ns a ticket, all of them in turn).
+// A few workgroups draw groups of SWEEP_WAVES consecutive chunks from a
+// counter, a chunk per wave, until none are left.  The lowest unfinished chunk
+// thus always belongs to a running workgroup, to a wave that waits for nothing
+// but finished chunks.  (Chunks given to waves by their workgroup's index would
+// need the workgroups to start in order, which holds per XCD only: beside
+// another kernel that polls, each can fill the XCD that the other's next
+// workgroup waits for.  It took 80 us a sweep of a 500k-row graph, 24 levels,
+// 15.6k chunks, against 87 us so.)  Tickets of one counter are served one after
+// another, 12 ns each: a ticket per chunk took 190 us.  Groups of more chunks
+// than waves, or drawn a round ahead, leave chunks waiting for a busy wave
+// while others look on (two chunks a wave 165 us, a round ahead 98 us).
 //
-// nb > 1 sweeps nb right-hand sides in one launch: workgroup g * nb + c runs
-// chunks 4 g .. 4 g + 3 for column c (rhs + c * ldr, out + c * ldo; reset_rhs
-// like rhs).
+// nb > 1 sweeps nb right-hand sides in one launch, each by workgroups of its
+// own with a counter of its own: workgroup b works on column b % nb (rhs + col *
+// ldr, out + col * ldo; reset_rhs like rhs).  The workgroup that draws the last
+// ticket of a column sets its counter back to zero.
+constexpr int SWEEP_WAVES = 4;
 template <class T, class TR, bool DIAG>
-__global__ __launch_bounds__(256) void k_sweep(const int* __restrict__ chunk, const int* __restrict__ rows,
-                                               const int* __restrict__ dp, const int* __restrict__ dcol,
-                                               const T* __restrict__ dval, const T* __restrict__ dinv,
-                                               const TR* rhs, T* out, TR* reset_rhs, unsigned nchunks, int nb,
-                                               size_t ldr, size_t ldo, int* abort_flag, uint64_t limit) {
-  const unsigned g = blockIdx.x / nb, col = blockIdx.x - g * nb;
-  const unsigned t = g * 4u + (threadIdx.x >> 6);
-  if (t >= nchunks) return;
+__global__ __launch_bounds__(64 * SWEEP_WAVES) void k_sweep(
+    const int* __restrict__ chunk, const int* __restrict__ rows, const int* __restrict__ dp,
+    const int* __restrict__ dcol, const T* __restrict__ dval, const T* __restrict__ dinv, const TR* rhs, T* out,
+    TR* reset_rhs, unsigned nchunks, int nb, size_t ldr, size_t ldo, unsigned* ticket, int* abort_flag,
+    uint64_t limit) {
+  __shared__ unsigned drawn[2];  // in turn, so that one barrier a round is enough
+  const unsigned col = blockIdx.x % nb, groups = (nchunks + SWEEP_WAVES - 1) / SWEEP_WAVES;
+  ticket += col * kTicketStride;
   rhs += col * ldr;
   out += col * ldo;
   if (reset_rhs) reset_rhs += col * ldr;
   const GlobalSrc<T> src{out};
-  int e, r;
-  T y;
-  if (chunk_rows<T, TR, DIAG>(src, chunk, t, rows, dp, dcol, dval, dinv, rhs, abort_flag, limit, e, r, y)) {
-    st_agent(out + r, y);
-    // rhs and reset_rhs may be the same buffer: the row read it already
-    if (reset_rhs) reset_rhs[r] = sentinel_of<TR>(0);
+  unsigned g;
+  for (unsigned round = 0;; ++round) {
+    if (threadIdx.x == 0) drawn[round & 1u] = atomicAdd(ticket, 1u);
+    __syncthreads();
+    g = drawn[round & 1u];
+    if (g >= groups) break;
+    const unsigned t = g * SWEEP_WAVES + (threadIdx.x >> 6);
+    if (t >= nchunks) continue;
+    int e, r;
+    T y;
+    if (chunk_rows<T, TR, DIAG>(src, chunk, t, rows, dp, dcol, dval, dinv, rhs, abort_flag, limit, e, r, y)) {
+      st_agent(out + r, y);
+      // rhs and reset_rhs may be the same buffer: the row read it already
+      if (reset_rhs) reset_rhs[r] = sentinel_of<TR>(0);
+    }
   }
+  if (threadIdx.x == 0 && g == groups + gridDim.x / nb - 1) st_agent(ticket, 0u);
 }
 
 // The chunks of one dependency level, a wave per chunk: every dependency
@@ -348,7 +369,7 @@ void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool
                   T* reset_rhs, int waves, bool whole, int* abort_flag, hipStream_t s, int nb, size_t ldr,
                   size_t ldo) {
   if (sw.nchunks == 0) return;
-  if (nb < 1 || ((int64_t)sw.nchunks / 4 + 1) * nb > 0x7fffffff) fail(GMG_ERR_INVALID_ARG, "sweep: bad column count");
+  if (nb < 1 || nb > kSweepCols || waves < 1) fail(GMG_ERR_INVALID_ARG, "sweep: bad column count");
   const uint64_t lim = wall_limit_ticks();
   // whole: every level device-wide in one launch; else the level ranges
   // chosen at setup
@@ -384,25 +405,14 @@ void launch_sweep(Sweep& sw, const T* dval, const T* dinv, const void* rhs, bool
       HIPCK(hipGetLastError());
       continue;
     }
-    const unsigned blocks = (nchunks + 3) / 4 * (unsigned)nb;
-    // Idle LDS holds the resident waves near `waves` a column: a few levels of
-    // look-ahead.  More only poll (200k-row graph, FP64: 49 us with 1024
-    // waves, 65 us with all 8192; 500k rows: 80 us with 2048, 86 us with
-    // 1024 or 8192; 16 columns of 200k rows: 390 us with 1024, 313 us with all)
-    size_t hold = 0;
-    const int64_t per_cu = std::max<int64_t>(1, ((int64_t)waves * nb + 4 * 256 - 1) / (4 * 256));
-    if (per_cu < 8) hold = (size_t)(160 * 1024) / per_cu - 1024;
-#define GMG_SW(TR_, DG_, RHS_, RESET_)                                                                        \
-  do {                                                                                                        \
-    static bool attr = false;                                                                                 \
-    if (!attr) {                                                                                              \
-      HIPCK(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep<T, TR_, DG_>),                         \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));                      \
-      attr = true;                                                                                            \
-    }                                                                                                         \
-    hipLaunchKernelGGL((k_sweep<T, TR_, DG_>), dim3(blocks), dim3(256), hold, s, ch, sw.rows.p, sw.dp.p,       \
-                       sw.dcol.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, nb, ldr, ldo, abort_flag, lim); \
-  } while (0)
+    // workgroups a column: `waves` waves over all columns.  Those beyond the
+    // device's residency start late and find nothing to draw
+    const unsigned w = std::min(nchunks, std::max(1u, (unsigned)waves / (unsigned)nb));
+    const unsigned blocks = std::min(8192u, (w + SWEEP_WAVES - 1) / SWEEP_WAVES) * (unsigned)nb;
+#define GMG_SW(TR_, DG_, RHS_, RESET_)                                                                           \
+  hipLaunchKernelGGL((k_sweep<T, TR_, DG_>), dim3(blocks), dim3(64 * SWEEP_WAVES), 0, s, ch, sw.rows.p, sw.dp.p, \
+                     sw.dcol.p, dval, dinv, (const TR_*)RHS_, out, RESET_, nchunks, nb, ldr, ldo, sw.ticket.p,   \
+                     abort_flag, lim)
     if (rhs_is_f64 && sizeof(T) == 4) {
       // FP32 sweep with an FP64 right-hand side (first sweep of the FP32 cycle)
       if (sw.has_diag) GMG_SW(double, true, rhs, (double*)nullptr);
