@@ -107,7 +107,8 @@ def copy_calibration():
 def _alg_bytes_doc():
     return ("spmv 12*nnz+20*N (FP64 CSR, int32 indices); sweep: 12 per dependency entry + "
             "(8 + rhs + 2*val [+ diag] [+ reset]) per row; resid_restrict 12*nnz + 40*N + 20*N_c; "
-            "ortho 8*N*(2k+3)+8*k^2 for k basis vectors up to 384 (one Gram-corrected projection), "
+            "ortho 8*N*(2k+4) for k basis vectors up to 32 (two projections, one of them of the vector "
+            "before), 8*N*(2k+3)+8*k^2 up to 384 (one Gram-corrected projection), "
             "8*N*(2k+2*blocks+2)+8*k^2 beyond (the first read over blocks of at most 384 vectors)")
 
 

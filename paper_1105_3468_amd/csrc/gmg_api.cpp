@@ -59,7 +59,7 @@ struct BatchWork {
   DBuf<double> abc, auc, aec, as, at;                              // adjoint cycle
   DBuf<double> r;                                                  // fine residuals before the restriction
   DBuf<float> r32;
-  DBuf<double> V, Z, w, x, b, coef, gram, gdots;                   // Krylov
+  DBuf<double> V, Z, w, x, b, coef, gfix, gdots;                   // Krylov
 };
 
 struct Solver {
@@ -124,6 +124,7 @@ struct Solver {
   size_t ld = 0;
   DBuf<double> V, Z, w, xcol, bcol, coef;
   size_t ldg = 0;
+  DBuf<double> gfix;           // second projection of the newest vector (bases up to kFused)
   DBuf<double> gram, gcoef, gdots;  // the basis' Gram matrix (ldg x ldg), corrected coefficients, V^T w_new
   RedWork rw;
   BatchWork bw;                // multi-right-hand-side solve (allocated on first use)
@@ -1604,6 +1605,7 @@ static void ensure_krylov(Solver& S, int m) {
   S.gram.alloc(S.ldg * S.ldg);
   S.gcoef.alloc((size_t)m + 8);
   S.gdots.alloc((size_t)m + 8);
+  S.gfix.alloc(kFused + 1);
 }
 
 // ------------------------------------------------------------------ FGMRES
@@ -1615,12 +1617,14 @@ struct OneResult {
 
 // Flexible GMRES(m) with right preconditioning (Algorithm 1's accelerator with
 // z_j = B~^{-1} v_j kept), Givens rotations on the host (O(m) scalars per
-// step).  Orthogonalisation: one projection whose coefficients are corrected
-// with the basis' Gram matrix G = V^T V, c = (2I - G) V^T w (equal to a second
-// Gram-Schmidt pass's V^T (w - V h) = h - G h), two reads of V per step.  Each
-// new row of G comes from the products V^T w_new taken in the read of V that
-// forms w_new; beyond many_max() vectors, from a second product in the next
-// projection's first read.
+// step).  Orthogonalisation: classical Gram-Schmidt twice for up to kFused
+// vectors, a vector's second projection taken in the read that projects the
+// next one the first time; beyond, one projection whose coefficients are
+// corrected with the basis' Gram matrix G = V^T V, c = (2I - G) V^T w (in exact
+// arithmetic a second pass's V^T (w - V h) = h - G h; the rounding of w - V c
+// stays).  Each new row of G comes from the products V^T w_new taken in the
+// read of V that forms w_new; beyond many_max() vectors, from a second product
+// in the next projection's first read.  Two reads of V per step throughout.
 static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b, double* x, double tol,
                         int maxit, int m, bool x0_given) {
   hipStream_t s = S.s;
@@ -1696,16 +1700,27 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       else vcycle<double>(S, vj, zj);
       apply_op(S, adjoint, zj, w);
       const int kc = j + 1;
+      double* col = hp + (size_t)kPinCol * (1 + (j & 1));
+      if (kc <= kFused) {
+        // v_j's second projection, h = V^T w, w <- w - V h with V^T w and ||w||^2
+        {
+          Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 4));
+          launch_multidot(V, ld, kc, S.gfix.p, w, n, S.rw, res, s);
+          launch_update(V, ld, kc, res, w, n, S.rw, S.gdots.p, s);
+        }
+        Prof p(S, PC_VECTOR, (double)n * 16);
+        launch_normalize(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, S.gfix.p, S.gram.p, S.ldg, res, col, S.rw,
+                         s);
+        HIPCK(hipEventRecord(S.colev[j & 1], s));
+        return;
+      }
       // h1 = V^T w; c = (2I - G) h1 (its correction d = c - h1 into h2's slot,
       // where the host adds it); w <- w - V c with V^T w (the next Gram row)
       // and ||w||^2 in the same read of V
       double* h1 = res;
       double* h2 = res + kc;
-      if (kc <= kFused) {
-        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
-        launch_multidot(V, ld, kc, w, n, S.rw, h1, s);
-        launch_update_gram(V, ld, kc, h1, S.gram.p, S.ldg, h2, w, n, S.rw, S.gdots.p, s);
-      } else if (kc <= many_max()) {
+      if (kc == kFused + 1) launch_again(V, ld, kFused, S.gfix.p, n, s);
+      if (kc <= many_max()) {
         Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot_many(V, ld, kc, w, n, S.rw, h1, s);
         launch_gram_coef(kc, h1, S.gram.p, S.ldg, nullptr, h2, S.gcoef.p, s);
@@ -1727,7 +1742,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
         launch_normalize_gram(w, V + (size_t)(j + 1) * ld, n, j + 1, S.gdots.p, kc <= many_max(), S.gram.p, S.ldg, res,
-                              hp + (size_t)kPinCol * (1 + (j & 1)), S.rw, s);
+                              col, s);
       }
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };
@@ -1813,8 +1828,8 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
 // cost about what one column costs), the matrix, the aggregates and the
 // factors are read once per step for all columns, and the Krylov kernels run
 // one recurrence per column of their grid.
-constexpr int kBatchRS = 2 * kFused + 8;  // result doubles per column: h1, d, ||w||^2
-constexpr int kGramLd = kFused + 1;       // rows of a column's Gram matrix
+constexpr int kBatchRS = 2 * kFused + 8;  // doubles per column of the host's block: h, V^T w, ||w||^2
+constexpr int kBatchDots = kFused + 1;    // V^T w and ||w||^2 of a column
 
 static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
   BatchWork& B = S.bw;
@@ -1855,8 +1870,8 @@ static void ensure_batch(Solver& S, int nb, int m, bool f32, bool adjoint) {
     B.x.alloc(nf);
     B.b.alloc(nf);
     B.coef.alloc((size_t)B.cap * (B.m + 1));
-    B.gram.alloc((size_t)B.cap * kGramLd * kGramLd);
-    B.gdots.alloc((size_t)B.cap * kGramLd);
+    B.gfix.alloc((size_t)B.cap * kBatchDots);
+    B.gdots.alloc((size_t)B.cap * kBatchDots);
   }
   if (f32 && !B.f32) {
     const size_t nf = B.ld * B.cap, ncv = B.ldc * B.cap;
@@ -2058,8 +2073,8 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
   double* hp = S.hpin;
   BatchResult out;
   // coefficients and norms per column in res, products with w_new in gdots
-  const BatchCols bh{nb, ld, ld, (size_t)kBatchRS, 0, 0};
-  const BatchCols bg{nb, ld, ld, (size_t)kGramLd, (size_t)kBatchRS, (size_t)kGramLd * kGramLd};
+  const BatchCols bh{nb, ld, ld, (size_t)kBatchRS, 0, (size_t)kBatchDots};
+  const BatchCols bg{nb, ld, ld, (size_t)kBatchDots, (size_t)kBatchRS, (size_t)kBatchDots};
   const DCsr& M = adjoint ? S.AT : S.A;
   launch_cols_from_rows(Bu, nrhs, c0, W.b.p, ld, n, nb, s);
   if (x0_given) launch_cols_from_rows(Xu, nrhs, c0, W.x.p, ld, n, nb, s);
@@ -2137,16 +2152,15 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
       }
       const int kc = j + 1;
       {
-        // the Gram-corrected projection of the single solve, every column in
-        // each launch
-        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) * nb);
-        launch_multidot(W.V.p, cap * ld, kc, W.w.p, n, S.rw, res, s, bh);
-        launch_update_gram(W.V.p, cap * ld, kc, res, W.gram.p, kGramLd, res + kc, W.w.p, n, S.rw, W.gdots.p, s, bg);
+        // the projection of the single solve, every column in each launch
+        Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 4) * nb);
+        launch_multidot(W.V.p, cap * ld, kc, W.gfix.p, W.w.p, n, S.rw, res, s, bh);
+        launch_update(W.V.p, cap * ld, kc, res, W.w.p, n, S.rw, W.gdots.p, s, bg);
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16 * nb);
-        launch_normalize_gram(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, true, W.gram.p, kGramLd,
-                              res, hp + (size_t)kPinCol * (1 + (j & 1)), S.rw, s, bg);
+        launch_normalize(W.w.p, W.V.p + (size_t)(j + 1) * cap * ld, n, kc, W.gdots.p, W.gfix.p, nullptr, 0, res,
+                         hp + (size_t)kPinCol * (1 + (j & 1)), S.rw, s, bg);
       }
       HIPCK(hipEventRecord(S.colev[j & 1], s));
     };

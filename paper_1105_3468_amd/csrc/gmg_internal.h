@@ -341,24 +341,25 @@ void red_init(RedWork& rw, hipStream_t s);
 void red_reset(RedWork& rw, hipStream_t s);
 // Independent recurrences batched in one launch of the k <= 32 Krylov
 // kernels: column c (c < nb) works on V + c * vcol, w + c * wcol, the
-// coefficients h + c * hcol, the Gram matrix at c * gcol and writes
+// coefficients h (and the host's column) + c * hcol, fix + c * fcol and writes
 // result + c * rcol.
 constexpr int KCOLS = 16;
 struct BatchCols {
   int nb = 1;
-  size_t vcol = 0, wcol = 0, rcol = 0, hcol = 0, gcol = 0;
+  size_t vcol = 0, wcol = 0, rcol = 0, hcol = 0, fcol = 0;
 };
-// k <= 32: result[0..k) = V[0..k)^T w (V rows with stride ld).  When the
-// reduction is small, this and launch_update_gram leave their sums as partials
-// in rw and the next of multidot, update_gram, normalize_gram adds them:
-// update_gram then stores h, and its own products stay in rw.
-void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t n,
-                     RedWork& rw, double* result, hipStream_t s, const BatchCols& bc = BatchCols());
-// c = (2I - G) h (d = c - h is stored), w -= V[0..k)^T c, then result[0..k) =
-// V^T w_new and result[k] = ||w_new||^2
-void launch_update_gram(const double* V, size_t ld, int k, double* h, const double* gram, size_t ldg, double* d,
-                        double* w, int64_t n, RedWork& rw, double* result, hipStream_t s,
-                        const BatchCols& bc = BatchCols());
+// k <= 32 (V rows with stride ld): V[k-1] is projected on the earlier vectors
+// and scaled by fix[0..k) (launch_normalize's, k > 1), then result[0..k) =
+// V^T w.  When the reduction is small, this and launch_update leave their sums
+// as partials in rw and the next of multidot, update, normalize adds them:
+// update then stores h, and its own products stay in rw.
+void launch_multidot(double* V, size_t ld, int k, const double* fix, const double* w, int64_t n, RedWork& rw,
+                     double* result, hipStream_t s, const BatchCols& bc = BatchCols());
+// w -= V[0..k)^T h, then result[0..k) = V^T w and result[k] = ||w||^2
+void launch_update(const double* V, size_t ld, int k, double* h, double* w, int64_t n, RedWork& rw, double* result,
+                   hipStream_t s, const BatchCols& bc = BatchCols());
+// V[row] <- (V[row] - V[0..row) fix) fix[row]
+void launch_again(double* V, size_t ld, int row, const double* fix, int64_t n, hipStream_t s);
 // any k (<= 2048): w -= V^T h (h device); if want_norm, result[0] = ||w_new||^2
 // Many-vector passes (up to many_max() vectors): result[0..k) = V^T w, and
 // w <- w - V h with result[0..k) = V^T w_new (and result[k] = ||w_new||^2
@@ -375,14 +376,20 @@ void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, 
 // stored there
 void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const double* fresh, double* d, double* c,
                       hipStream_t s);
-// y = x / sqrt(nrm2) (zero when it is zero) with nrm2 = dots[row], and the Gram
-// row of y: G[row][i] = G[i][row] = dots[i] / sqrt(nrm2) (i < row, when
-// have_dots), G[row][row] = 1; host[0..2 row) = col[0..2 row), host[2 row] =
-// nrm2 (host: pinned memory).  Batch: x at wcol, y at vcol, dots at rcol, G at
-// gcol, col and host at hcol
+// row <= 32: y = x / ||x|| (zero when it is zero) from dots[row] = ||x||^2, and
+// fix[0..row] for its second projection from dots[0..row) = V^T x; host[0..row) =
+// h, host[row..2 row) = dots, host[2 row] = the squared norm after that
+// projection (host: pinned memory); gram (may be null): y's row of an
+// orthonormal basis.  Batch: x at wcol, y at vcol, dots at rcol, fix at fcol, h
+// and host at hcol
+void launch_normalize(const double* x, double* y, int64_t n, int row, const double* dots, double* fix, double* gram,
+                      size_t ldg, const double* h, double* host, RedWork& rw, hipStream_t s,
+                      const BatchCols& bc = BatchCols());
+// row > 32: y = x / ||x||, and the Gram row of y: G[row][i] = G[i][row] = dots[i]
+// / ||x|| (i < row, when have_dots), G[row][row] = 1; host[0..2 row) =
+// col[0..2 row), host[2 row] = dots[row] = ||x||^2
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, const double* col, double* host, RedWork& rw, hipStream_t s,
-                           const BatchCols& bc = BatchCols());
+                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s);
 void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
                         RedWork& rw, double* result, hipStream_t s);
 // result[0] = ||x||^2

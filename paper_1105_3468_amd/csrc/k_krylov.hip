@@ -1,6 +1,6 @@
 // Krylov-subspace vector kernels of FGMRES: block multi-dot products, the
-// Gram-corrected projection (two reads of the basis per step), norms, scaling
-// and the solution update.  Reductions are deterministic (no floating-point
+// projections (two reads of the basis per step), norms, scaling and the
+// solution update.  Reductions are deterministic (no floating-point
 // atomics): every block writes its partial sums and they are added in block
 // order, so repeated runs are bitwise identical.  Up to KDEF blocks a column
 // the kernel that needs the sums adds the partials in each of its blocks;
@@ -200,13 +200,36 @@ __device__ __forceinline__ double uniform(double v) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
+// The projection of up to KMAX vectors is classical Gram-Schmidt twice, the
+// second pass of a vector taken together with the first pass of the next one:
+// - k_multidot: the newest vector V[K - 1], projected once and normalised, is
+//   projected again, v <- (v - sum_k fix[k] V[k]) fix[K - 1], and written back;
+//   in the same read h = V^T w with it.
+// - k_update: w <- w - V h, and s = V^T w and ||w||^2 in the same read.
+// - k_normalize: y = w / ||w||, and the next k_multidot's coefficients
+//   fix = s / ||w|| and scale 1 / sqrt(1 - |fix|^2).
+// The Hessenberg column is h + s over ||w|| sqrt(1 - |fix|^2), as after a second
+// pass.  The preconditioner sees the vector projected once, which a flexible
+// method allows: z_j is any vector, and only V has to be orthonormal.  Two
+// reads of the basis and one vector written a step; a second pass of its own
+// reads it a third time (27 vectors of 16 columns of 262k rows: 201 + 194 +
+// 181 us).  Correcting the coefficients with the basis' Gram matrix instead,
+// c = (2I - G) h, also takes two reads, but leaves the rounding of w - V c in
+// the basis: max |V^T V - I| of 2e-14 where two passes give 7e-16, and 1e-10
+// where a step cancels by 1e5.
 template <int K>
 __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, size_t ld,
+                                                 const double* __restrict__ fix, double* __restrict__ last,
                                                  const double* __restrict__ w, int64_t n, double* partial,
                                                  unsigned* counter, double* result, double* dpart, size_t vcol,
-                                                 size_t wcol, size_t rcol) {
+                                                 size_t wcol, size_t rcol, size_t fcol) {
   KRYLOV_COLUMN();
+  last += blockIdx.y * vcol;
   if (dpart) dpart += blockIdx.y * (size_t)KDEF * KPART;
+  fix += blockIdx.y * fcol;
+  double f[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) f[k] = K > 1 ? uniform(fix[k]) : 0.0;
   double acc[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) acc[k] = 0.0;
@@ -214,12 +237,25 @@ __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, s
     const double2 wi = ld2(w + i);
     double2 v[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = ld2(V + k * ld + i);
+    for (int k = 0; k < K - 1; ++k) v[k] = ld2(V + k * ld + i);
+    double2 u = ld2(last + i);
     ALL_LOADS_ISSUED();
+    if constexpr (K > 1) {
+#pragma unroll
+      for (int k = 0; k < K - 1; ++k) {
+        u.x -= f[k] * v[k].x;
+        u.y -= f[k] * v[k].y;
+      }
+      u.x *= f[K - 1];
+      u.y *= f[K - 1];
+    }
+    v[K - 1] = u;
     if (i + 1 < n) {
+      if constexpr (K > 1) *reinterpret_cast<double2*>(last + i) = u;
 #pragma unroll
       for (int k = 0; k < K; ++k) acc[k] += v[k].x * wi.x + v[k].y * wi.y;
     } else {
+      if constexpr (K > 1) last[i] = u.x;
 #pragma unroll
       for (int k = 0; k < K; ++k) acc[k] += v[k].x * wi.x;
     }
@@ -227,30 +263,18 @@ __global__ __launch_bounds__(KB) void k_multidot(const double* __restrict__ V, s
   block_reduce_store<K>(acc, K, partial, counter, result, dpart);
 }
 
-// w <- w - sum_k c[k] V[k]; result[k] = V[k] . w_new, result[K] = ||w_new||^2.
-// c = h + d, d_i = -sum_{l != i} G[i][l] h[l] with the basis' Gram matrix G
-// (k_gram_coef says why); every block forms it for itself, block 0 stores d.
 // hpart: h is the sum of the gridDim.x partials k_multidot left there, which
 // every block adds; block 0 stores it.
-// The products with w_new are the Gram row of the next basis vector, so a
-// step reads the basis twice.  A second Gram-Schmidt pass in its place read
-// it a third time: 27 vectors of 16 columns of 262k rows took 201 + 194 + 181
-// us in three passes.
 template <int K>
-__global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V, size_t ld,
-                                                    double* h, const double* __restrict__ gram, size_t ldg,
-                                                    double* __restrict__ d, double* __restrict__ w, int64_t n,
-                                                    double* partial, unsigned* counter, double* result,
-                                                    const double* __restrict__ hpart, double* dpart, size_t vcol, size_t wcol, size_t rcol, size_t hcol, size_t gcol) {
+__global__ __launch_bounds__(KB) void k_update(const double* __restrict__ V, size_t ld, double* h,
+                                               double* __restrict__ w, int64_t n, double* partial, unsigned* counter,
+                                               double* result, const double* __restrict__ hpart, double* dpart,
+                                               size_t vcol, size_t wcol, size_t rcol, size_t hcol) {
   KRYLOV_COLUMN();
   h += blockIdx.y * hcol;
-  d += blockIdx.y * hcol;
-  gram += blockIdx.y * gcol;
-  __shared__ double hs[K], cs[K];
-  double g[K];
+  if (dpart) dpart += blockIdx.y * (size_t)KDEF * KPART;
+  __shared__ double hs[K];
   if (threadIdx.x < K) {
-#pragma unroll
-    for (int l = 0; l < K; ++l) g[l] = gram[(size_t)l * ldg + threadIdx.x];  // symmetric
     if (hpart) {
       const double t = sum_parts(hpart + blockIdx.y * (size_t)KDEF * KPART + threadIdx.x, gridDim.x);
       hs[threadIdx.x] = t;
@@ -259,20 +283,10 @@ __global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V
       hs[threadIdx.x] = h[threadIdx.x];
     }
   }
-  if (dpart) dpart += blockIdx.y * (size_t)KDEF * KPART;
   __syncthreads();
-  if (threadIdx.x < K) {
-    double t = 0.0;
+  double acc[K + 1], hk[K];
 #pragma unroll
-    for (int l = 0; l < K; ++l)
-      if (l != (int)threadIdx.x) t += g[l] * hs[l];
-    cs[threadIdx.x] = hs[threadIdx.x] + (-t);
-    if (blockIdx.x == 0) d[threadIdx.x] = -t;
-  }
-  __syncthreads();
-  double acc[K + 1], ck[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) { acc[k] = 0.0; ck[k] = uniform(cs[k]); }
+  for (int k = 0; k < K; ++k) { acc[k] = 0.0; hk[k] = uniform(hs[k]); }
   acc[K] = 0.0;
   for (int64_t i = 2 * (blockIdx.x * (int64_t)KB + threadIdx.x); i < n; i += 2 * (int64_t)gridDim.x * KB) {
     double2 v[K];
@@ -282,8 +296,8 @@ __global__ __launch_bounds__(KB) void k_update_gram(const double* __restrict__ V
     ALL_LOADS_ISSUED();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      s.x -= ck[k] * v[k].x;
-      s.y -= ck[k] * v[k].y;
+      s.x -= hk[k] * v[k].x;
+      s.y -= hk[k] * v[k].y;
     }
     if (i + 1 < n) {
       *reinterpret_cast<double2*>(w + i) = s;
@@ -331,7 +345,7 @@ static unsigned red_grid(int64_t n, int nb = 1) {
   return (unsigned)g;
 }
 
-// The partials of k_multidot (which 0) and k_update_gram (which 1) where the
+// The partials of k_multidot (which 0) and k_update (which 1) where the
 // next kernel adds them: up to KDEF blocks a column.
 static double* deferred(RedWork& rw, int64_t n, int nb, int which) {
   return red_grid(n, nb) <= KDEF ? rw.dpart.p + (size_t)which * KDEF * KPART * KCOLS : nullptr;
@@ -356,21 +370,40 @@ static double* deferred(RedWork& rw, int64_t n, int nb, int which) {
 static void check_cols(const BatchCols& bc) {
   if (bc.nb < 1 || bc.nb > KCOLS) fail(GMG_ERR_INVALID_ARG, "Krylov kernels: bad column count");
 }
-void launch_multidot(const double* V, size_t ld, int k, const double* w, int64_t n, RedWork& rw,
+void launch_multidot(double* V, size_t ld, int k, const double* fix, const double* w, int64_t n, RedWork& rw,
                      double* result, hipStream_t s, const BatchCols& bc) {
   if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "multidot: bad vector count");
   check_cols(bc);
-  GMG_DISPATCH_K(k, k_multidot, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, w, n, rw.partial.p,
-                 rw.counter.p, result, deferred(rw, n, bc.nb, 0), bc.vcol, bc.wcol, bc.rcol);
+  GMG_DISPATCH_K(k, k_multidot, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, fix, V + (size_t)(k - 1) * ld,
+                 w, n, rw.partial.p, rw.counter.p, result, deferred(rw, n, bc.nb, 0), bc.vcol, bc.wcol, bc.rcol,
+                 bc.fcol);
   HIPCK(hipGetLastError());
 }
-void launch_update_gram(const double* V, size_t ld, int k, double* h, const double* gram, size_t ldg, double* d,
-                        double* w, int64_t n, RedWork& rw, double* result, hipStream_t s, const BatchCols& bc) {
-  if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update_gram: bad vector count");
+void launch_update(const double* V, size_t ld, int k, double* h, double* w, int64_t n, RedWork& rw, double* result,
+                   hipStream_t s, const BatchCols& bc) {
+  if (k < 1 || k > KMAX) fail(GMG_ERR_INVALID_ARG, "update: bad vector count");
   check_cols(bc);
-  GMG_DISPATCH_K(k, k_update_gram, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, h, gram, ldg, d, w, n,
-                 rw.partial.p, rw.counter.p, result, deferred(rw, n, bc.nb, 0), deferred(rw, n, bc.nb, 1), bc.vcol,
-                 bc.wcol, bc.rcol, bc.hcol, bc.gcol);
+  GMG_DISPATCH_K(k, k_update, dim3(red_grid(n, bc.nb), bc.nb), dim3(KB), 0, s, V, ld, h, w, n, rw.partial.p,
+                 rw.counter.p, result, deferred(rw, n, bc.nb, 0), deferred(rw, n, bc.nb, 1), bc.vcol, bc.wcol, bc.rcol,
+                 bc.hcol);
+  HIPCK(hipGetLastError());
+}
+
+// v <- (v - sum_{k < row} fix[k] V[k]) fix[row], the newest vector V[row] = v
+// projected again, where no k_multidot does it (KMAX vectors before it)
+__global__ __launch_bounds__(KB) void k_again(double* V, size_t ld, int row, const double* __restrict__ fix,
+                                              int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)KB + threadIdx.x; i < n; i += (int64_t)gridDim.x * KB) {
+    double u = V[(size_t)row * ld + i];
+#pragma unroll 16
+    for (int k = 0; k < row; ++k) u -= fix[k] * V[(size_t)k * ld + i];
+    V[(size_t)row * ld + i] = u * fix[row];
+  }
+}
+void launch_again(double* V, size_t ld, int row, const double* fix, int64_t n, hipStream_t s) {
+  if (n <= 0) return;
+  const unsigned g = (unsigned)std::min<int64_t>(8192, (n + KB - 1) / KB);
+  hipLaunchKernelGGL(k_again, dim3(g), dim3(KB), 0, s, V, ld, row, fix, n);
   HIPCK(hipGetLastError());
 }
 
@@ -428,23 +461,22 @@ void launch_scale(const double* x, double a, double* y, int64_t n, hipStream_t s
   HIPCK(hipGetLastError());
 }
 
-// y = x / sqrt(nrm2) (zero when the norm is zero), and the basis' Gram matrix
-// row `row` (and its mirror column) for the new vector y: block 0 stores
-// G[row][i] = (V[i] . x) / ||x|| for i < row from the products dots[0..row)
-// taken while x was formed (unless have_dots is 0: the next projection takes
-// them), and G[row][row] = 1.  The step's column goes to the host from here
-// as well: host[0 .. 2 row) = col[0 .. 2 row) and host[2 row] = nrm2 =
-// dots[row] (a copy of its own cost 3 us a step).  parts: dots is the sum of
-// the nparts partials k_update_gram left there.  Column blockIdx.y of a batch.
-__global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
-                                 const double* __restrict__ dots, int have_dots, double* __restrict__ gram,
-                                 size_t ldg, const double* __restrict__ col, double* __restrict__ host,
-                                 const double* __restrict__ parts, int nparts, size_t xcol, size_t ycol, size_t dcol,
-                                 size_t gcol, size_t rcol) {
+// y = x / ||x|| (zero when the norm is zero) and the coefficients of its second
+// projection, from dots[0..row) = V^T x and dots[row] = ||x||^2: fix[i] = dots[i] /
+// ||x||, fix[row] = 1 / sqrt(1 - |fix|^2) (zero when x lies in the basis).  The
+// step's column goes to the host from here as well (a copy of its own cost 3 us
+// a step): host[0..row) = h, host[row..2 row) = dots and host[2 row] =
+// ||x||^2 (1 - |fix|^2).  parts: dots is the sum of the nparts partials k_update
+// left there.  gram (may be null): y's row of the basis' Gram matrix, whose
+// vectors up to here are orthonormal.  Column blockIdx.y of a batch.
+__global__ void k_normalize(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
+                            const double* __restrict__ dots, double* __restrict__ fix, double* __restrict__ gram,
+                            size_t ldg, const double* __restrict__ h, double* __restrict__ host,
+                            const double* __restrict__ parts, int nparts, size_t xcol, size_t ycol, size_t dcol,
+                            size_t fcol, size_t hcol) {
   x += blockIdx.y * xcol;
   y += blockIdx.y * ycol;
   dots += blockIdx.y * dcol;
-  gram += blockIdx.y * gcol;
   if (parts) parts += blockIdx.y * (size_t)KDEF * KPART;
   const double nv = parts ? sum_parts(parts + row, nparts) : dots[row];
   const double hn = sqrt(nv);
@@ -452,13 +484,64 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = a * x[i];
   if (blockIdx.x == 0) {
+    __shared__ double sq[KMAX];
+    fix += blockIdx.y * fcol;
+    h += blockIdx.y * hcol;
+    host += blockIdx.y * hcol;
+    const int i = threadIdx.x;
+    if (i < row) {
+      const double d = parts ? sum_parts(parts + i, nparts) : dots[i];
+      const double f = d * a;
+      fix[i] = f;
+      sq[i] = f * f;
+      host[i] = h[i];
+      host[row + i] = d;
+      if (gram) {
+        gram[(size_t)row * ldg + i] = 0.0;
+        gram[(size_t)i * ldg + row] = 0.0;
+      }
+    }
+    __syncthreads();
+    if (i == 0) {
+      double rest = 1.0;
+      for (int k = 0; k < row; ++k) rest -= sq[k];
+      if (rest < 0.0) rest = 0.0;
+      fix[row] = rest > 0.0 ? 1.0 / sqrt(rest) : 0.0;
+      host[2 * row] = nv * rest;
+      if (gram) gram[(size_t)row * ldg + row] = 1.0;
+    }
+  }
+}
+void launch_normalize(const double* x, double* y, int64_t n, int row, const double* dots, double* fix, double* gram,
+                      size_t ldg, const double* h, double* host, RedWork& rw, hipStream_t s, const BatchCols& bc) {
+  if (n <= 0) return;
+  if (row < 1 || row > KMAX) fail(GMG_ERR_INVALID_ARG, "normalize: bad vector count");
+  check_cols(bc);
+  const double* parts = deferred(rw, n, bc.nb, 1);
+  const int64_t g = std::min<int64_t>((n + 255) / 256, 8192 / bc.nb);
+  hipLaunchKernelGGL(k_normalize, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots, fix, gram, ldg, h,
+                     host, parts, parts ? (int)red_grid(n, bc.nb) : 0, bc.wcol, bc.vcol, bc.rcol, bc.fcol, bc.hcol);
+  HIPCK(hipGetLastError());
+}
+
+// The same for a basis of more than KMAX vectors: y's Gram row, G[row][i] =
+// G[i][row] = dots[i] / ||x|| (i < row, when have_dots: else the next projection
+// takes it), takes the place of a second projection, and the column is
+// host[0 .. 2 row) = col[0 .. 2 row), host[2 row] = ||x||^2.
+__global__ void k_normalize_gram(const double* __restrict__ x, double* __restrict__ y, int64_t n, int row,
+                                 const double* __restrict__ dots, int have_dots, double* __restrict__ gram,
+                                 size_t ldg, const double* __restrict__ col, double* __restrict__ host) {
+  const double nv = dots[row];
+  const double hn = sqrt(nv);
+  const double a = hn != 0.0 ? 1.0 / hn : 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    y[i] = a * x[i];
+  if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < row && have_dots; i += blockDim.x) {
-      const double gv = (parts ? sum_parts(parts + i, nparts) : dots[i]) * a;
+      const double gv = dots[i] * a;
       gram[(size_t)row * ldg + i] = gv;
       gram[(size_t)i * ldg + row] = gv;
     }
-    col += blockIdx.y * rcol;
-    host += blockIdx.y * rcol;
     for (int i = threadIdx.x; i < 2 * row; i += blockDim.x) host[i] = col[i];
     if (threadIdx.x == 0) {
       gram[(size_t)row * ldg + row] = 1.0;
@@ -467,15 +550,11 @@ __global__ void k_normalize_gram(const double* __restrict__ x, double* __restric
   }
 }
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
-                           double* gram, size_t ldg, const double* col, double* host, RedWork& rw, hipStream_t s,
-                           const BatchCols& bc) {
+                           double* gram, size_t ldg, const double* col, double* host, hipStream_t s) {
   if (n <= 0) return;
-  check_cols(bc);
-  const double* parts = row <= KMAX ? deferred(rw, n, bc.nb, 1) : nullptr;
-  int64_t g = (n + 255) / 256;
-  if (g > 8192 / bc.nb) g = 8192 / bc.nb;
-  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g, bc.nb), dim3(256), 0, s, x, y, n, row, dots,
-                     have_dots ? 1 : 0, gram, ldg, col, host, parts, parts ? (int)red_grid(n, bc.nb) : 0, bc.wcol, bc.vcol, bc.rcol, bc.gcol, bc.hcol);
+  const int64_t g = std::min<int64_t>((n + 255) / 256, 8192);
+  hipLaunchKernelGGL(k_normalize_gram, dim3((unsigned)g), dim3(256), 0, s, x, y, n, row, dots, have_dots ? 1 : 0,
+                     gram, ldg, col, host);
   HIPCK(hipGetLastError());
 }
 
