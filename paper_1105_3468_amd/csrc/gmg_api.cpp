@@ -735,23 +735,21 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
   ts.eval32.alloc(ne > 0 ? ne : 1);
   ts.boff.alloc(nn);
   ts.ncount.alloc(nn);
+  // holds the diagonal blocks themselves (column-major; no longer than the
+  // packed inverses) until those are ready
   ts.inv.alloc(packed > 0 ? packed : 1);
-  ts.inv32.alloc(packed > 0 ? packed : 1);
   h2d(ts.task.p, task.data(), task.size(), s);
   h2d(ts.erp.p, erp.data(), n + 1, s);
   h2d(ts.boff.p, boff.data(), nn, s);
   HIPCK(hipMemsetAsync(ts.ncount.p, 0, sizeof(int) * nn, s));
+  HIPCK(hipMemsetAsync(ts.inv.p, 0, sizeof(double) * (total > 0 ? total : 1), s));
+  DBuf<int64_t> dwoff;
+  dwoff.alloc(nn);
+  h2d(dwoff.p, woff.data(), nn, s);
   {
     // the factor's rows on the device, values in entry order
     DBuf<int> drp, dci, dnode, dlo, dsz;
-    DBuf<double> dv, dblk, ddinv, work;
-    DBuf<int> dit[2], dpt;
-    DBuf<int64_t> dwoff;
-    dwoff.alloc(nn);
-    h2d(dwoff.p, woff.data(), nn, s);
-    dpt.alloc(ptask.size());
-    h2d(dpt.p, ptask.data(), ptask.size(), s);
-    work.alloc(total > 0 ? total : 1);
+    DBuf<double> dv;
     drp.alloc(n + 1);
     dci.alloc(nent > 0 ? nent : 1);
     dv.alloc(nent > 0 ? nent : 1);
@@ -773,10 +771,16 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     h2d(dnode.p, node_of.data(), n, s);
     h2d(dlo.p, nlo.data(), nn, s);
     h2d(dsz.p, nsz.data(), nn, s);
-    dblk.alloc(total > 0 ? total : 1);
-    HIPCK(hipMemsetAsync(dblk.p, 0, sizeof(double) * (total > 0 ? total : 1), s));
-    launch_tree_fill(n, drp.p, dci.p, dv.p, skip, dnode.p, dlo.p, dsz.p, dwoff.p, ts.erp.p, dblk.p, ts.ecol.p,
+    launch_tree_fill(n, drp.p, dci.p, dv.p, skip, dnode.p, dlo.p, dsz.p, dwoff.p, ts.erp.p, ts.inv.p, ts.ecol.p,
                      ts.eval.p, s);
+  }
+  {
+    DBuf<double> ddinv, work;
+    DBuf<int> dit[2], dpt;
+    work.alloc(total > 0 ? total : 1);
+    ts.inv32.alloc(packed > 0 ? packed : 1);
+    dpt.alloc(ptask.size());
+    h2d(dpt.p, ptask.data(), ptask.size(), s);
     if (dinv) {
       ddinv.alloc(n);
       h2d(ddinv.p, dinv->data(), n, s);
@@ -787,7 +791,7 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
       dit[c].alloc(itask[c].size());
       h2d(dit[c].p, itask[c].data(), itask[c].size(), s);
     }
-    launch_tree_invert(lower, dwoff.p, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, dblk.p,
+    launch_tree_invert(lower, dwoff.p, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, ts.inv.p,
                        dinv ? ddinv.p : nullptr, work.p, s);
     launch_tree_pack(dpt.p, (int)ptask.size() / 8, dwoff.p, ts.boff.p, work.p, ts.inv.p, ts.inv32.p, s);
     launch_cast_f32(ts.eval.p, ts.eval32.p, ne, s);
