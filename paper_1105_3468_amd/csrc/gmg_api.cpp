@@ -1425,37 +1425,54 @@ static void adjoint_ilut(Solver& S, bool threads) {
 // Transposed factors, built at the first adjoint call.  The coarse ones run on
 // a second host thread beside the fine ones; both queue work on the solver's
 // stream, on disjoint buffers.  First adjoint application on 128^3: 680 -> 211
-// ms; small factors stay on one thread (50k-row graph: 1 ms less a training
-// step; the threads' blocks come from the runtime, not the cache).
+// ms; below kThreadEntries entries (50k-row graph: 1 ms less a training step;
+// the threads' blocks come from the runtime, not the cache) only L0^T's level
+// layout has a thread of its own.
+static void adjoint_threads(Solver& S) {
+  std::exception_ptr err;
+  int dev = 0;
+  HIPCK(hipGetDevice(&dev));
+  std::thread ct([&] {
+    try {
+      HIPCK(hipSetDevice(dev));
+      PoolStream scope(S.s);
+      adjoint_ilut(S, true);
+    } catch (...) {
+      err = std::current_exception();
+    }
+  });
+  try {
+    adjoint_fine(S);
+  } catch (...) {
+    ct.join();
+    throw;
+  }
+  ct.join();
+  if (err) std::rethrow_exception(err);
+}
+
 static void ensure_adjoint(Solver& S) {
   if (S.adj_ready) return;
   hipStream_t s = S.s;
   const int nc = S.nc;
   const gmg_options& o = S.opt;
   constexpr int64_t kThreadEntries = 2000000;
-  const bool threads = S.nnz + (int64_t)S.hLc.ci.size() + (int64_t)S.hUc.ci.size() >= kThreadEntries;
-  if (o.coarse_mode == 0 && threads) {
-    std::exception_ptr err;
-    int dev = 0;
-    HIPCK(hipGetDevice(&dev));
-    std::thread ct([&] {
-      try {
-        HIPCK(hipSetDevice(dev));
-        PoolStream scope(s);
-        adjoint_ilut(S, true);
-      } catch (...) {
-        err = std::current_exception();
-      }
-    });
+  bool done = false;
+  if (o.coarse_mode == 0 && S.nnz + (int64_t)S.hLc.ci.size() + (int64_t)S.hUc.ci.size() >= kThreadEntries) {
     try {
-      adjoint_fine(S);
-    } catch (...) {
-      ct.join();
-      throw;
+      adjoint_threads(S);
+      done = true;
+    } catch (const Error& e) {
+      // the layouts' work arrays did not fit side by side: one after another
+      if (e.code != GMG_ERR_OOM) throw;
+      HIPCK(hipStreamSynchronize(s));
+      S.tU0t = TreeSolve();
+      S.tL0t = TreeSolve();
+      S.tUct = TreeSolve();
+      S.tLct = TreeSolve();
     }
-    ct.join();
-    if (err) std::rethrow_exception(err);
-  } else {
+  }
+  if (!done) {
     adjoint_fine(S);
     if (o.coarse_mode == 0) adjoint_ilut(S, false);
   }
