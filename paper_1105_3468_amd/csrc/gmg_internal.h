@@ -296,6 +296,8 @@ void launch_perm_gather(int n, const int* perm, const double* z, T* zp, hipStrea
 template <class T>
 void launch_perm_scatter(int n, const int* perm, T* tp, T* t, hipStream_t s);
 void launch_exclusive_scan_int(const int* in, int* out, int n, hipStream_t s, DBuf<int>& tmp);
+// threads of a launch, along x, at most
+constexpr int64_t kMaxThreads = (1LL << 32) - 1;
 // message returned by gmg_last_error() on this thread
 void set_error_message(const std::string& msg);
 

@@ -185,10 +185,12 @@ __global__ __launch_bounds__(256) void k_pattern_grad(int n, const int* __restri
 }
 
 // lanes per cell or row for nrhs right-hand sides: the largest power of two
-// that keeps them all busy, at most 16 (a 128-byte line of values)
+// that keeps them all busy, at most 16 (a 128-byte line of values), and fewer
+// where a launch cannot have that many threads
 #define GMG_FV_LANES(nrhs, KERNEL, items, ...)                                                                  \
   do {                                                                                                          \
-    const int lg_ = (nrhs) >= 16 ? 4 : (nrhs) >= 8 ? 3 : (nrhs) >= 4 ? 2 : (nrhs) >= 2 ? 1 : 0;                 \
+    int lg_ = (nrhs) >= 16 ? 4 : (nrhs) >= 8 ? 3 : (nrhs) >= 4 ? 2 : (nrhs) >= 2 ? 1 : 0;                       \
+    while (lg_ > 0 && ((int64_t)(items) << lg_) > kMaxThreads - 255) --lg_;                                     \
     const dim3 grid_((unsigned)((((int64_t)(items) << lg_) + 255) / 256));                                      \
     if (lg_ == 0) hipLaunchKernelGGL(KERNEL<0>, grid_, dim3(256), 0, s, __VA_ARGS__);                           \
     else if (lg_ == 1) hipLaunchKernelGGL(KERNEL<1>, grid_, dim3(256), 0, s, __VA_ARGS__);                      \

@@ -335,17 +335,18 @@ __global__ void k_agg_fill(int nc, const int* __restrict__ aptr, const int* __re
   dcnt[I] = o - s;
 }
 
-// 16 lanes per aggregate copy its list
+// 16 lanes per aggregate copy its list (in turns when there are more aggregates
+// than a launch has threads)
 __global__ void k_compact(int nc, const int* __restrict__ off, const int* __restrict__ dst_rp,
                           const int* __restrict__ rj, const double* __restrict__ rv, int* __restrict__ cj,
                           double* __restrict__ cv) {
   const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t I = t0 >> 4;
-  if (I >= nc) return;
-  const int s = off[I], d = dst_rp[I], c = dst_rp[I + 1] - d;
-  for (int t = (int)(t0 & 15); t < c; t += 16) {
-    cj[d + t] = rj[s + t];
-    cv[d + t] = rv[s + t];
+  for (int64_t I = t0 >> 4; I < nc; I += gridDim.x * (int64_t)blockDim.x >> 4) {
+    const int s = off[I], d = dst_rp[I], c = dst_rp[I + 1] - d;
+    for (int t = (int)(t0 & 15); t < c; t += 16) {
+      cj[d + t] = rj[s + t];
+      cv[d + t] = rv[s + t];
+    }
   }
 }
 
@@ -372,7 +373,8 @@ static void aggregate_csr(int nc, const int* aptr, const int* amem, const int* r
   const int raw = tail[0];
   rj.alloc(raw > 0 ? raw : 1);
   rv.alloc(raw > 0 ? raw : 1);
-  if (tail[1])
+  // a wave per aggregate, where a launch has the threads
+  if (tail[1] || (int64_t)nc * 64 > kMaxThreads - 255)
     hipLaunchKernelGGL(k_agg_fill<UPPER_ONLY>, dim3(g1(nc, 128)), dim3(128), 0, s, nc, aptr, amem, rp, ci, v, agg,
                        off.p, rj.p, rv.p, dcnt.p);
   else
@@ -385,7 +387,7 @@ static void aggregate_csr(int nc, const int* aptr, const int* amem, const int* r
   HIPCK(hipStreamSynchronize(s));
   oci.alloc(nnz > 0 ? nnz : 1);
   ov.alloc(nnz > 0 ? nnz : 1);
-  hipLaunchKernelGGL(k_compact, dim3(g1((int64_t)nc * 16)), dim3(256), 0, s, nc, off.p, orp.p, rj.p, rv.p, oci.p, ov.p);
+  hipLaunchKernelGGL(k_compact, dim3(g1(std::min<int64_t>((int64_t)nc * 16, 1LL << 31))), dim3(256), 0, s, nc, off.p, orp.p, rj.p, rv.p, oci.p, ov.p);
   HIPCK(hipGetLastError());
   HIPCK(hipStreamSynchronize(s));
   *onnz = nnz;

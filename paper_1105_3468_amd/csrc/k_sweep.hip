@@ -856,7 +856,7 @@ void launch_ilu0_grid(int n, int nx, const int* rp, const int* ci, const int* dp
 void launch_ilu0_level(const int* rows, int count, const int* rp, const int* ci, const int* dpos, double* a,
                        int* bad, hipStream_t s, int longest) {
   if (count <= 0) return;
-  if (longest <= ILU_ROW) {
+  if (longest <= ILU_ROW && (int64_t)count * ILU_G <= kMaxThreads - 255) {
     hipLaunchKernelGGL(k_ilu0_rows, dim3((unsigned)(((int64_t)count * ILU_G + 255) / 256)), dim3(256), 0, s, rows,
                        count, rp, ci, dpos, a, bad);
     HIPCK(hipGetLastError());

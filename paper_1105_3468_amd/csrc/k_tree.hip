@@ -711,7 +711,7 @@ __global__ __launch_bounds__(256) void k_tree_fill(int n, const int* __restrict_
                                                    const int* __restrict__ nsz, const int64_t* __restrict__ boff,
                                                    const int* __restrict__ erp, double* __restrict__ blk,
                                                    int* __restrict__ ecol, double* __restrict__ eval) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t t = (blockIdx.y * (int64_t)gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
   const bool in = t / FILL_G < n;  // whole groups; idle ones take part in the ballots
   const int r = in ? (int)(t / FILL_G) : n - 1, sub = (int)(t % FILL_G);
   const int a = node_of[r], lo = nlo[a], sz = nsz[a];
@@ -740,8 +740,9 @@ void launch_tree_fill(int n, const int* rp, const int* ci, const double* v, int 
                       const int* nlo, const int* nsz, const int64_t* boff, const int* erp, double* blk, int* ecol,
                       double* eval, hipStream_t s) {
   if (n <= 0) return;
-  const unsigned grid = (unsigned)(((int64_t)n * FILL_G + 255) / 256);
-  hipLaunchKernelGGL(k_tree_fill, dim3(grid), dim3(256), 0, s, n, rp, ci, v, skip, node_of, nlo, nsz, boff,
+  const int64_t blocks = ((int64_t)n * FILL_G + 255) / 256, most = 1 << 23;
+  const dim3 grid((unsigned)std::min(blocks, most), (unsigned)((blocks + most - 1) / most));
+  hipLaunchKernelGGL(k_tree_fill, grid, dim3(256), 0, s, n, rp, ci, v, skip, node_of, nlo, nsz, boff,
                      erp, blk, ecol, eval);
   HIPCK(hipGetLastError());
 }
