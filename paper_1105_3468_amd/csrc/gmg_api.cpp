@@ -136,6 +136,7 @@ struct Solver {
   std::vector<double> hist;    // FGMRES residual estimates of the last solve, per step
   bool force_column_loop = false;  // GMG_COLUMN_LOOP=1: solve several RHS one after another (timing reference)
   int spmv_cap = 4096;         // LDS products per SpMV tile (from A's largest 256-row tile)
+  int spmv_cap_at = 0;         // the same for A^T (0: not known yet)
   // profiling
   bool prof = false;
   unsigned prof_mask = 0;      // classes that record events (bit c: class c)
@@ -1580,6 +1581,13 @@ static void smooth_adjoint(Solver& S, const double* sv, double* t) {
   }
 }
 
+// LDS products per tile of the product with A or A^T
+static int op_cap(Solver& S, bool adjoint) {
+  if (!adjoint) return S.spmv_cap;
+  if (S.spmv_cap_at == 0) S.spmv_cap_at = spmv_cap_of(S.n, S.AT.rp.p, S.s);
+  return S.spmv_cap_at;
+}
+
 // q = B~^{-T} z (FP64), the transpose of Eq. (twogrid)'s operator:
 // ec = M~_c^{-T} P^T z; s = z - A^T P ec; t = S^{-T} s; q = P ec + t
 static void vcycle_adjoint(Solver& S, const double* z, double* q) {
@@ -1593,7 +1601,7 @@ static void vcycle_adjoint(Solver& S, const double* z, double* q) {
   {
     Prof p(S, PC_RESID_RESTRICT, (double)S.nnz * 12 + (double)S.n * 24);
     launch_resid_adj(S.n, S.AT.rp.p, S.AT.ci.p, S.AT.v.p, S.agg.p, S.aec.p, z, S.as.p, s,
-                     S.spmv_cap);
+                     op_cap(S, true));
   }
   smooth_adjoint(S, S.as.p, S.at.p);
   {
@@ -1607,7 +1615,7 @@ static void vcycle_adjoint(Solver& S, const double* z, double* q) {
 static void apply_op(Solver& S, bool adjoint, const double* x, double* y) {
   Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)S.n * 20);
   const DCsr& M = adjoint ? S.AT : S.A;
-  launch_spmv<double>(S.n, M.rp.p, M.ci.p, M.v.p, x, y, S.s, S.spmv_cap);
+  launch_spmv<double>(S.n, M.rp.p, M.ci.p, M.v.p, x, y, S.s, op_cap(S, adjoint));
 }
 
 static void ensure_krylov(Solver& S, int m) {
@@ -1684,7 +1692,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
       {
         Prof p(S, PC_SPMV, (double)S.nnz * 12 + (double)n * 28);
         const DCsr& M = adjoint ? S.AT : S.A;
-        launch_residual(S.n, M.rp.p, M.ci.p, M.v.p, x, b, w, s, S.spmv_cap);
+        launch_residual(S.n, M.rp.p, M.ci.p, M.v.p, x, b, w, s, op_cap(S, adjoint));
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 8);

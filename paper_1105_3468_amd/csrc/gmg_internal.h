@@ -261,6 +261,8 @@ void launch_dense_transpose(int n, int np, const double* M, double* MT, hipStrea
 // staged in LDS (2048 or 4096; spmv_cap picks it from the largest tile, and
 // tiles beyond it are computed from global memory)
 int spmv_cap(int64_t max_tile_nnz);
+// the same for a matrix of n > 0 rows on the device (waits for the stream)
+int spmv_cap_of(int n, const int* rp, hipStream_t s);
 template <class T>
 void launch_spmv(int n, const int* rp, const int* ci, const T* v, const T* x, T* y,
                  hipStream_t s, int cap = 4096);

@@ -183,6 +183,23 @@ __global__ __launch_bounds__(256) void k_spmv(int n, const int* __restrict__ rp,
 // the CU's wave limit, so more loads in flight).
 int spmv_cap(int64_t max_tile_nnz) { return max_tile_nnz <= 2048 ? 2048 : 4096; }
 
+__global__ void k_tile_max(int n, const int* __restrict__ rp, int* __restrict__ most) {
+  const int64_t r0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * SPMV_ROWS;
+  if (r0 < n) atomicMax(most, rp[min(r0 + SPMV_ROWS, (int64_t)n)] - rp[r0]);
+}
+int spmv_cap_of(int n, const int* rp, hipStream_t s) {
+  DBuf<int> most;
+  most.alloc(1);
+  launch_fill_u32(reinterpret_cast<unsigned*>(most.p), 0u, 1, s);
+  const int tiles = (n + SPMV_ROWS - 1) / SPMV_ROWS;
+  hipLaunchKernelGGL(k_tile_max, dim3((tiles + 255) / 256), dim3(256), 0, s, n, rp, most.p);
+  HIPCK(hipGetLastError());
+  int m = 0;
+  d2h(&m, most.p, 1, s);
+  HIPCK(hipStreamSynchronize(s));
+  return spmv_cap(m);
+}
+
 template <class T, class TB, int MODE>
 static void spmv_dispatch(int n, const int* rp, const int* ci, const T* v, const int* agg, const T* x, const TB* b,
                           T* y, int cap, hipStream_t s) {
