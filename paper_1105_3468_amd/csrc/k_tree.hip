@@ -60,7 +60,7 @@ __device__ __forceinline__ T tree_poll(const T* p, int* abort_flag, uint64_t lim
 //                       none), so that a tree's many leaves fit the workgroups
 //                       resident at once
 template <class T, class TR, bool LOWER>
-__global__ __launch_bounds__(TREE_THREADS) void k_tree(const int* __restrict__ task, const int64_t* __restrict__ boff,
+__global__ __launch_bounds__(TREE_THREADS, 6) void k_tree(const int* __restrict__ task, const int64_t* __restrict__ boff,
                                                        const int* __restrict__ erp, const int* __restrict__ ecol,
                                                        const T* __restrict__ eval, const T* __restrict__ inv,
                                                        int* ncount, const TR* rhs, T* out, T* ext, TR* reset_rhs,
@@ -194,6 +194,15 @@ __global__ __launch_bounds__(TREE_THREADS) void k_tree(const int* __restrict__ t
   if (tid < R && a + tid < b) {
     T x = (T)0;
     for (int g = 0; g < G; ++g) x += part[g * R + tid];
+    if (!isfinite(x)) {
+      // a zero entry's term is no term, whatever the value beside it
+      const int k1 = LOWER ? a + tid + 1 : j1;
+      x = (T)0;
+      for (int k = LOWER ? j0 : a + tid; k < k1; ++k)
+        if (const T e = inv[boff[node] + (packed ? (int64_t)a * s + tid : (int64_t)(a + tid)) + (int64_t)k * cs];
+            e != (T)0)
+          x += e * y[k - j0];
+    }
     if (is_sentinel(x)) x = (T)__builtin_nan("");
     st_agent(out + lo + a + tid, x);
   }
@@ -456,6 +465,13 @@ __global__ __launch_bounds__(TREE_THREADS, 7) void k_tree_cols(const int* __rest
     T x = (T)0;
 #pragma unroll
     for (int w = 0; w < TREE_THREADS / 64; ++w) x += part[w][rr][c];
+    if (!isfinite(x)) {  // without the terms of zero entries, as in k_tree
+      const int i = a + rr, lgR = tk[6] >> 1, R = 1 << lgR, cs = s > kTreeLeaf ? R : s;
+      const T* col = M + (s > kTreeLeaf ? (int64_t)(i >> lgR) * R * s + (i & (R - 1)) : (int64_t)i);
+      x = (T)0;
+      for (int k = k0; k < k1; ++k)
+        if (const T e = col[(int64_t)k * cs]; e != (T)0) x += e * ld_agent(y + (size_t)k * CW + c);
+    }
     if (is_sentinel(x)) x = (T)__builtin_nan("");
     st_agent(out + (size_t)(lo + a) * CW + o, x);
   }
@@ -567,9 +583,27 @@ __global__ __launch_bounds__(INV_B) void k_tree_inv_diag(const int* __restrict__
       }
     }
   }
-  __syncthreads();
+  bool fin = true;
 #pragma unroll
-  for (int i = 0; i < INV_B; ++i) Tl[lane * (INV_B + 1) + i] = x[i];
+  for (int i = 0; i < INV_B; ++i) fin = fin && isfinite(x[i]);
+  const bool redo = __any(!fin);
+  __syncthreads();
+  double* X = Tl + lane * (INV_B + 1);  // column `lane` of the inverse
+  if (redo) {
+    // an entry overflowed: again, without the terms of zero entries
+    for (int i = 0; i < INV_B; ++i) X[i] = i == lane ? 1.0 : 0.0;
+    for (int step = 0; step < bs; ++step) {
+      const int k = LOWER ? step : bs - 1 - step;
+      double xk = X[k];
+      if (DIAG && xk != 0.0) X[k] = xk = xk * dl[k];
+      if (xk == 0.0) continue;
+      for (int i = LOWER ? k + 1 : 0; i < (LOWER ? bs : k); ++i)
+        if (const double e = Tb[(int64_t)k * s + i]; e != 0.0) X[i] -= e * xk;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < INV_B; ++i) X[i] = x[i];
+  }
   __syncthreads();
   if (lane < bs)
     for (int c = 0; c < bs; ++c) M[(int64_t)c * s + lane] = Tl[c * (INV_B + 1) + lane];
@@ -613,8 +647,21 @@ __global__ __launch_bounds__(256) void k_tree_inv_off(const int* __restrict__ it
 #pragma unroll
       for (int u = 0; u < KU; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
     }
+    // entries that overflowed: again without the terms of zero entries
+    auto again = [&](int i, int q0, int q1, const double* A, auto&& value) {
+      double t = 0.0;
+      for (int q = q0; q < q1; ++q)
+        if (const double e = A[(int64_t)q * s + i]; e != 0.0)
+          if (const double v = value(q); v != 0.0) t += e * v;
+      return t;
+    };
 #pragma unroll
-    for (int r = 0; r < 4; ++r) Ss[16 * wave + 4 * r + kq][l16] = acc[r];
+    for (int r = 0; r < 4; ++r) {
+      const int i = I * INV_B + 16 * wave + 4 * r + kq;
+      double v = acc[r];
+      if (!isfinite(v) && i < s && col) v = again(i, k0, k1, T, [&](int q) { return X[q]; });
+      Ss[16 * wave + 4 * r + kq][l16] = v;
+    }
     __syncthreads();
     f64x4 x = {0.0, 0.0, 0.0, 0.0};
     double a[INV_B / 4];
@@ -630,7 +677,10 @@ __global__ __launch_bounds__(256) void k_tree_inv_off(const int* __restrict__ it
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = I * INV_B + 16 * wave + 4 * r + kq;
-        if (i < s) M[(int64_t)c * s + i] = -x[r];
+        double v = x[r];
+        if (!isfinite(v) && i < s)
+          v = again(i, I * INV_B, min((I + 1) * INV_B, s), M, [&](int q) { return Ss[q - I * INV_B][l16]; });
+        if (i < s) M[(int64_t)c * s + i] = -v;
       }
     }
     __syncthreads();  // the next block reads these rows; Ss is free again
