@@ -517,10 +517,13 @@ static std::vector<NdNode> merge_tree(const std::vector<NdNode>& t, int rows) {
 // Microseconds a solve without and with merging, one column (16 columns):
 // N_c = 657 17.4, 7.3; 3087 26.1, 18.0 (33.2, 23.4); 7751 30.6, 25.5 (40.3,
 // 35.0); 14799 36.4, 33.0 (56.3, 52.6); in 3D 9788 42.7, 36.3 (63.3, 54.9).
-static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
+// merge: in, may merge; out, has merged.
+static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in, bool& merge) {
   constexpr double kLevelUs = 3.0, kBytesPerUs = 1.2e6;
   constexpr int kMergeRows = 1024;
   std::vector<NdNode> best = split_tree(tree_in, kTreeMaxRows);
+  if (!merge) return best;
+  merge = false;
   auto cost = [&](const std::vector<NdNode>& t) {
     double bytes = 0.0;
     int h = 0;
@@ -539,6 +542,7 @@ static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
     if (c < least) {
       least = c;
       best = std::move(t);
+      merge = true;
     }
   }
   return best;
@@ -547,8 +551,9 @@ static std::vector<NdNode> solve_tree(const std::vector<NdNode>& tree_in) {
 static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n, const std::vector<int>& rp,
                        const std::vector<int>& ci, const std::vector<int>* src, int skip,
                        const std::vector<double>& vals, bool lower, const std::vector<double>* dinv,
-                       hipStream_t s) {
-  const std::vector<NdNode> tree = solve_tree(tree_in);
+                       hipStream_t s, bool merge = true) {
+  const std::vector<NdNode> tree = solve_tree(tree_in, merge);
+  constexpr float kMergeGrowth = 8.0f;
   constexpr int kHelperEntries = 256, kHelperRows = 32;
   // helpers of the solve of several columns (of 4 or 8; of 16): entries and
   // rows at most, and the entries beyond which a row gets the whole workgroup
@@ -775,6 +780,7 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     launch_tree_fill(n, drp.p, dci.p, dv.p, skip, dnode.p, dlo.p, dsz.p, dwoff.p, ts.erp.p, ts.inv.p, ts.ecol.p,
                      ts.eval.p, s);
   }
+  bool merged_grows = false;
   {
     DBuf<double> ddinv, work;
     DBuf<int> dit[2], dpt;
@@ -794,9 +800,27 @@ static bool build_tree(TreeSolve& ts, const std::vector<NdNode>& tree_in, int n,
     }
     launch_tree_invert(lower, dwoff.p, dit[0].p, (int)itask[0].size() / 8, dit[1].p, (int)itask[1].size() / 8, ts.inv.p,
                        dinv ? ddinv.p : nullptr, work.p, s);
-    launch_tree_pack(dpt.p, (int)ptask.size() / 8, dwoff.p, ts.boff.p, work.p, ts.inv.p, ts.inv32.p, s);
+    DBuf<unsigned> dgrowth;
+    unsigned growth[2] = {0, 0};
+    if (merge) {
+      dgrowth.alloc(2);
+      launch_fill_u32(dgrowth.p, 0u, 2, s);
+    }
+    launch_tree_pack(dpt.p, (int)ptask.size() / 8, dwoff.p, ts.boff.p, work.p, ts.inv.p, ts.inv32.p, dgrowth.p, s);
     launch_cast_f32(ts.eval.p, ts.eval32.p, ne, s);
+    if (merge) d2h(growth, dgrowth.p, 2, s);
     HIPCK(hipStreamSynchronize(s));  // host vectors and staging buffers go out of scope
+    // A product with an explicit inverse is as accurate as a substitution while
+    // |T^-1||T| is small.  The factors of diagonally dominant M-matrices have
+    // entries of at most 1 here (2 on nonsymmetric graphs), by columns or by
+    // rows.  Where entries grow, small blocks keep the growth small.
+    float g[2];
+    std::memcpy(g, growth, sizeof g);
+    merged_grows = merge && !(std::min(g[0], g[1]) <= kMergeGrowth);
+  }
+  if (merged_grows) {
+    ts = TreeSolve();
+    return build_tree(ts, tree_in, n, rp, ci, src, skip, vals, lower, dinv, s, false);
   }
   return true;
 }

@@ -220,10 +220,12 @@ constexpr int kTreeInvBlock = 64, kTreeInvCols = 16;
 constexpr int kTreeLeaf = 64;
 // Setup: the inverses into the solves' layout; ptask: one of 8 ints per
 // kTreePackCols columns of a node (its rows, first column, columns, node, log2
-// of its slices' rows).
+// of its slices' rows).  growth (may be null; two values, zero beforehand): bits of
+// the largest entry of the inverses after scaling the columns, and the rows, of
+// every block to a unit diagonal.
 constexpr int kTreePackCols = 16;
 void launch_tree_pack(const int* ptask, int npack, const int64_t* woff, const int64_t* boff, const double* work,
-                      double* inv, float* inv32, hipStream_t s);
+                      double* inv, float* inv32, unsigned* growth, hipStream_t s);
 // Setup: dense diagonal blocks (zeroed beforehand) and outside-entry lists of
 // a factor whose row r holds entries [rp[r] + skip, rp[r+1]).
 void launch_tree_fill(int n, const int* rp, const int* ci, const double* v, int skip, const int* node_of,

@@ -693,16 +693,37 @@ __global__ __launch_bounds__(256) void k_tree_inv_off(const int* __restrict__ it
 // follow, so a slice's workgroup streams one contiguous piece.  (In column-
 // major order a slice of 8 rows read 64 bytes of every line, the other half
 // going to another slice's workgroup; 16 rows straddled lines.)
+// growth (may be null): the largest entry of the inverses with the block's
+// columns, and its rows, scaled to a unit diagonal (as float bits)
 // ptask[8t ..]: s, first column, columns, node, log2 R
 constexpr int PACK_COLS = 16;
 __global__ __launch_bounds__(256) void k_tree_pack(const int* __restrict__ ptask, const int64_t* __restrict__ woff,
                                                    const int64_t* __restrict__ boff, const double* __restrict__ work,
-                                                   double* __restrict__ inv, float* __restrict__ inv32) {
+                                                   double* __restrict__ inv, float* __restrict__ inv32,
+                                                   unsigned* growth) {
   const int* t = ptask + 8 * (size_t)blockIdx.x;
   const int s = t[0], j0 = t[1], nj = t[2], node = t[3], lgR = t[4], R = 1 << lgR;
   const double* W = work + woff[node];
   double* O = inv + boff[node];
   float* O32 = inv32 + boff[node];
+  if (growth) {
+    unsigned by_col = 0, by_row = 0;  // bits of non-negative floats order like the floats, NaN above them all
+    for (int e = threadIdx.x; e < nj * s; e += 256) {
+      const int j = j0 + e / s, i = e % s;
+      const double v = W[(int64_t)j * s + i];
+      if (v == 0.0) continue;
+      by_col = max(by_col, __float_as_uint((float)fabs(v / W[(int64_t)j * s + j])));
+      by_row = max(by_row, __float_as_uint((float)fabs(v / W[(int64_t)i * s + i])));
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      by_col = max(by_col, (unsigned)__shfl_xor((int)by_col, off, 64));
+      by_row = max(by_row, (unsigned)__shfl_xor((int)by_row, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      atomicMax(growth, by_col);
+      atomicMax(growth + 1, by_row);
+    }
+  }
   if (s <= kTreeLeaf) {
     for (int e = threadIdx.x; e < nj * s; e += 256) {
       const double v = W[(int64_t)j0 * s + e];
@@ -722,9 +743,9 @@ __global__ __launch_bounds__(256) void k_tree_pack(const int* __restrict__ ptask
 }
 
 void launch_tree_pack(const int* ptask, int npack, const int64_t* woff, const int64_t* boff, const double* work,
-                      double* inv, float* inv32, hipStream_t s) {
+                      double* inv, float* inv32, unsigned* growth, hipStream_t s) {
   if (npack == 0) return;
-  hipLaunchKernelGGL(k_tree_pack, dim3(npack), dim3(256), 0, s, ptask, woff, boff, work, inv, inv32);
+  hipLaunchKernelGGL(k_tree_pack, dim3(npack), dim3(256), 0, s, ptask, woff, boff, work, inv, inv32, growth);
   HIPCK(hipGetLastError());
 }
 static_assert(kTreePackCols == PACK_COLS, "packing tasks");
