@@ -284,7 +284,8 @@ gmg_status gmg_fv_assemble(int n, int dim, const double* kappa, const double* ve
  * HIP graph capture, serving loops that forbid hipMalloc): the same arguments,
  * layout and results (bitwise identical), with no hipMalloc, hipFree or other
  * allocation and no scratch memory.  Limit: n^dim <= GMG_FV_NOALLOC_MAX_CELLS
- * (GMG_FV_NOALLOC_SCRATCH_INTS - 1 blocks of 1024 row pointers), else
+ * (GMG_FV_NOALLOC_SCRATCH_INTS - 1 times 1024, less one: constants of the
+ * interface that no scratch stands behind any more), else
  * GMG_ERR_INVALID_ARG before any device work.  Unlike gmg_fv_assemble it does
  * not synchronise: the results are complete in the order of `stream`. */
 #define GMG_FV_NOALLOC_SCRATCH_INTS 32768

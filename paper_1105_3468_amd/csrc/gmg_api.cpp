@@ -48,8 +48,8 @@ struct ProfRec {
 };
 
 // Workspace of the multi-right-hand-side solve: up to BATCH_MAX columns,
-// column-major, fine vectors ld apart, coarse vectors ldc apart, Krylov bases
-// of m steps (step j of column c at V + (j * cap + c) * ld).
+// column-major, fine vectors ld apart, coarse vectors ldc apart (rows of columns
+// while the tree solves have them), Krylov bases of m steps (step j of column c at V + (j * cap + c) * ld).
 struct BatchWork {
   int cap = 0, m = 0;
   size_t ld = 0, ldc = 0;
@@ -1777,7 +1777,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
         Prof p(S, PC_ORTHO, 8.0 * n * (2 * kc + 3) + 8.0 * kc * kc);
         launch_multidot_many(V, ld, kc, w, n, S.rw, h1, s);
         launch_gram_coef(kc, h1, S.gram.p, S.ldg, nullptr, h2, S.gcoef.p, s);
-        launch_update_dot_many(V, ld, kc, S.gcoef.p, w, n, true, S.rw, S.gdots.p, s);
+        launch_update_dot_many(V, ld, kc, S.gcoef.p, w, n, S.rw, S.gdots.p, s);
       } else {
         // longer than the register-resident passes hold: h1 over equal blocks,
         // and in the same read the products of the newest basis vector (the
@@ -1790,7 +1790,7 @@ static OneResult fgmres(Solver& S, bool adjoint, int precision, const double* b,
           launch_multidot_many(V + (size_t)k0 * ld, ld, std::min(per, kc - k0), w, n, S.rw, h1 + k0, s, vlast,
                                S.gdots.p + k0);
         launch_gram_coef(kc, h1, S.gram.p, S.ldg, S.gdots.p, h2, S.gcoef.p, s);
-        launch_update_many(V, ld, kc, S.gcoef.p, w, n, true, S.rw, S.gdots.p + kc, s);
+        launch_update_many(V, ld, kc, S.gcoef.p, w, n, S.rw, S.gdots.p + kc, s);
       }
       {
         Prof p(S, PC_VECTOR, (double)n * 16);
@@ -2117,7 +2117,7 @@ static BatchResult fgmres_batch(Solver& S, bool adjoint, int precision, const do
                                 int c0, int nb, double tol, int maxit, int m, bool x0_given) {
   hipStream_t s = S.s;
   const int64_t n = S.n;
-  if (adjoint) ensure_adjoint(S);   // the transposed factors, before their per-column counters
+  if (adjoint) ensure_adjoint(S);
   ensure_batch(S, nb, m, precision == 1, adjoint);
   reset_batch_buffers(S);
   BatchWork& W = S.bw;

@@ -366,18 +366,17 @@ void launch_update(const double* V, size_t ld, int k, double* h, double* w, int6
                    hipStream_t s, const BatchCols& bc = BatchCols());
 // V[row] <- (V[row] - V[0..row) fix) fix[row]
 void launch_again(double* V, size_t ld, int row, const double* fix, int64_t n, hipStream_t s);
-// any k (<= 2048): w -= V^T h (h device); if want_norm, result[0] = ||w_new||^2
 // Many-vector passes (up to many_max() vectors): result[0..k) = V^T w, and
-// w <- w - V h with result[0..k) = V^T w_new (and result[k] = ||w_new||^2
-// when want_norm), each reading V once.  w2: also result2[0..k) = V^T w2.
+// w <- w - V h with result[0..k) = V^T w_new and result[k] = ||w_new||^2, each
+// reading V once.  w2: also result2[0..k) = V^T w2.
 int many_max();
 void launch_multidot_many(const double* V, size_t ld, int k, const double* w, int64_t n, RedWork& rw, double* result,
                           hipStream_t s, const double* w2 = nullptr, double* result2 = nullptr);
-void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
-                            RedWork& rw, double* result, hipStream_t s);
+void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
+                            double* result, hipStream_t s);
 // c = (2I - G) h and d = c - h for the basis' Gram matrix G (row-major, ldg;
 // unit diagonal assumed): the coefficients of a projection corrected for the
-// basis' loss of orthogonality, as a second Gram-Schmidt pass would give
+// basis' loss of orthogonality
 // fresh (may be null): V^T v of the last vector v, used as its Gram row and
 // stored there
 void launch_gram_coef(int kc, const double* h, double* gram, size_t ldg, const double* fresh, double* d, double* c,
@@ -396,8 +395,9 @@ void launch_normalize(const double* x, double* y, int64_t n, int row, const doub
 // col[0..2 row), host[2 row] = dots[row] = ||x||^2
 void launch_normalize_gram(const double* x, double* y, int64_t n, int row, const double* dots, bool have_dots,
                            double* gram, size_t ldg, const double* col, double* host, hipStream_t s);
-void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
-                        RedWork& rw, double* result, hipStream_t s);
+// any k (<= 2048): w -= V^T h (h device), result[0] = ||w_new||^2
+void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
+                        double* result, hipStream_t s);
 // result[0] = ||x||^2
 void launch_norm2(const double* x, int64_t n, RedWork& rw, double* result, hipStream_t s, int nb = 1,
                   size_t xcol = 0, size_t rcol = 0);

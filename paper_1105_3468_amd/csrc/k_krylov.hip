@@ -579,15 +579,13 @@ __global__ void k_xupdate(double* __restrict__ x, const double* __restrict__ Z, 
   }
 }
 
-
-
 // Any number of vectors: w <- w - sum_k h[k] V[k] with the coefficients staged
-// in LDS; optionally result[0] = ||w_new||^2.  Used when the basis has more
-// vectors than one fused pass holds in registers.
+// in LDS, and result[0] = ||w_new||^2.  Used when the basis has more vectors
+// than one fused pass holds in registers.
 __global__ __launch_bounds__(KB) void k_update_many(const double* __restrict__ V, size_t ld, int kc,
                                                     const double* __restrict__ h, double* __restrict__ w,
-                                                    int64_t n, int want_norm, double* partial,
-                                                    unsigned* counter, double* result) {
+                                                    int64_t n, double* partial, unsigned* counter,
+                                                    double* result) {
   __shared__ double hs[KLDS];
   for (int k = threadIdx.x; k < kc; k += KB) hs[k] = h[k];
   __syncthreads();
@@ -607,14 +605,14 @@ __global__ __launch_bounds__(KB) void k_update_many(const double* __restrict__ V
     w[i] = s;
     acc[0] += s * s;
   }
-  if (want_norm) block_reduce_store<1>(acc, 1, partial, counter, result);
+  block_reduce_store<1>(acc, 1, partial, counter, result);
 }
 
-void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
-                        RedWork& rw, double* result, hipStream_t s) {
+void launch_update_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
+                        double* result, hipStream_t s) {
   if (k < 1 || k > KLDS) fail(GMG_ERR_INVALID_ARG, "update_many: bad vector count");
-  hipLaunchKernelGGL(k_update_many, dim3(red_grid(n)), dim3(KB), 0, s, V, ld, k, h, w, n, want_norm ? 1 : 0,
-                     rw.partial.p, rw.counter.p, result);
+  hipLaunchKernelGGL(k_update_many, dim3(red_grid(n)), dim3(KB), 0, s, V, ld, k, h, w, n, rw.partial.p,
+                     rw.counter.p, result);
   HIPCK(hipGetLastError());
 }
 
@@ -722,8 +720,8 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// w <- w - sum_k h[k] V[k]; block partials of V[k] . w_new, and with
-// want_norm of ||w_new||^2 (slot kc).  A chunk's new w needs every vector
+// w <- w - sum_k h[k] V[k]; block partials of V[k] . w_new and of ||w_new||^2
+// (slot kc).  A chunk's new w needs every vector
 // group's partial sum (two barriers per chunk), so the next chunk's basis
 // values (and w) are loaded before them.  The grid walks the rows from the
 // last chunk down to the first: the preceding multidot pass walked them
@@ -732,7 +730,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int PER>
 __global__ __launch_bounds__(MKB) void k_update_dot_many(const double* __restrict__ V, size_t ld, int kc,
                                                          const double* __restrict__ h, double* __restrict__ w,
-                                                         int64_t n, int want_norm, double* __restrict__ mpart) {
+                                                         int64_t n, double* __restrict__ mpart) {
   __shared__ double pr[MROWS][MG + 1];
   __shared__ double wn[MROWS];
   __shared__ double hs[MMAX];
@@ -799,7 +797,7 @@ __global__ __launch_bounds__(MKB) void k_update_dot_many(const double* __restric
   __syncthreads();
   many_block_sums<PER>(acc, kc, mpart);
   static_assert(MROWS == 64, "the norm is reduced within wave 0");
-  if (want_norm && threadIdx.x < MROWS) {
+  if (threadIdx.x < MROWS) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) nacc += __shfl_down(nacc, off, 64);
     if (threadIdx.x == 0) mpart[(size_t)blockIdx.x * MSTR + kc] = nacc;
@@ -876,21 +874,23 @@ void launch_multidot_many(const double* V, size_t ld, int k, const double* w, in
   HIPCK(hipGetLastError());
 }
 
-void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, bool want_norm,
-                            RedWork& rw, double* result, hipStream_t s) {
+void launch_update_dot_many(const double* V, size_t ld, int k, const double* h, double* w, int64_t n, RedWork& rw,
+                            double* result, hipStream_t s) {
   if (k < 1 || k > MMAX) fail(GMG_ERR_INVALID_ARG, "update_dot_many: bad vector count");
   const unsigned nb = many_grid(n);
-  const int wn = want_norm ? 1 : 0;
-  GMG_MANY(GMG_UPDATE, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, h, w, n, wn, rw.mpart.p);
-  colsum(rw.mpart.p, nb, k + wn, result, s);
+  GMG_MANY(GMG_UPDATE, k, dim3(nb), dim3(MKB), 0, s, V, ld, k, h, w, n, rw.mpart.p);
+  colsum(rw.mpart.p, nb, k + 1, result, s);
   HIPCK(hipGetLastError());
 }
 
 // Gram-corrected coefficients of one projection: with G = V^T V (unit
 // diagonal taken as exact), c = h + d, d_i = -sum_{l != i} G[i][l] h[l],
-// i.e. c = (2I - G) h, the first-order form of G^{-1} h: the same as a second
-// classical Gram-Schmidt pass, V^T (w - V h) = h - G h, without reading V
-// again.  One wave per coefficient, lanes over l, added in a fixed order.
+// i.e. c = (2I - G) h, the first-order form of G^{-1} h and, in exact
+// arithmetic, what a second classical Gram-Schmidt pass, V^T (w - V h) = h - G
+// h, adds.  It makes up for what the basis has lost, but the rounding of w - V c
+// itself, about eps ||w||, stays in the new vector, where a second pass removes
+// it: products with the basis are left at eps ||w|| / ||w - V c||, and enter G.
+// One wave per coefficient, lanes over l, added in a fixed order.
 // `fresh`: the products of the last vector with the basis, when its Gram row
 // was not taken as it was formed; used in the row's place and stored there.
 __global__ __launch_bounds__(64) void k_gram_coef(int kc, const double* __restrict__ h, double* gram, size_t ldg,

@@ -207,8 +207,9 @@ __global__ void k_agg_count(int nc, const int* __restrict__ aptr, const int* __r
 // entries in visiting order go to LDS, every lane ranks its pairs by (J,
 // position), a stable sort, and the lane that holds the first pair of a run
 // of equal J adds the run front to back.  The compacted list lands at the
-// segment start, as from k_agg_fill, bit for bit.  For aggregates of at most
-// 64 members and AGG_LIST entries.  A thread per aggregate sorting in global
+// segment start, as from k_agg_fill, bit for bit.  For matrices whose
+// aggregates all have at most 64 members and AGG_LIST entries (with one wider
+// aggregate k_agg_fill takes them all).  A thread per aggregate sorting in global
 // memory took 2.7 ms for A_c of a 500k-row graph (77k lists of about 70
 // pairs, every insertion step a load of its own).
 template <bool UPPER_ONLY>

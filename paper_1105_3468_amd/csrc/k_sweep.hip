@@ -638,7 +638,8 @@ __global__ void k_ilu0_level(const int* __restrict__ rows, int count, const int*
   else if (!isfinite(d)) atomicOr(bad, 2);
 }
 
-// The same by ILU_G lanes per row, for rows of at most ILU_ROW entries: a lane
+// The same by ILU_G lanes per row, for matrices whose rows all have at most
+// ILU_ROW entries (one longer row sends every level to k_ilu0_level): a lane
 // holds up to ILU_E entries of row i (column and value) in registers.  For
 // every lower entry (i, k) in turn, its owner forms l_ik; the lanes load row
 // k's upper entries side by side and hand them round, and the lane whose entry

@@ -8,9 +8,10 @@
 // node's diagonal block and the rows outside it that E refers to are final by
 // then.  The diagonal blocks of separators are nearly dense after fill, and a
 // substitution through one costs a dependent step per row; instead T^{-1} is
-// formed once at setup (dense, column-major, zeros in the other triangle) and
-// the solve applies it as a matrix-vector product, whose rows are independent
-// and are split over several workgroups.
+// formed once at setup (dense, zeros in the other triangle; column-major up to
+// 64 rows, packed by the slices that read it beyond) and the solve applies it as
+// a matrix-vector product, whose rows are independent and are split over several
+// workgroups.
 //
 // One launch runs a whole solve as a list of tasks in tree order (lower:
 // heights ascending; upper: descending).  For a node with terms outside it,
@@ -18,8 +19,11 @@
 // polling the published results of other nodes (value-as-flag, as in the
 // sweeps), and publish them to a staging vector that doubles as its own
 // ready flag; the node's slice tasks poll them, multiply, and publish their
-// rows.  Every task waits only on earlier tasks and workgroups start in
-// order, so the solve always makes progress; every wait is bounded.
+// rows.  Every task waits only on earlier tasks.  Workgroups start in order on
+// each XCD, so a solve that has the device, or shares it with kernels that do
+// not wait, makes progress; beside another kernel that polls, each could fill
+// the XCD that the other's next workgroup waits for.  Every wait is bounded: it
+// then ends with an error.
 #include <algorithm>
 
 #include "gmg_internal.h"
