@@ -49,7 +49,8 @@ struct ProfRec {
 
 // Workspace of the multi-right-hand-side solve: up to BATCH_MAX columns,
 // column-major, fine vectors ld apart, coarse vectors ldc apart (rows of columns
-// while the tree solves have them), Krylov bases of m steps (step j of column c at V + (j * cap + c) * ld).
+// while the tree solves have them), Krylov bases of m steps (step j of column c
+// at V + (j * cap + c) * ld).
 struct BatchWork {
   int cap = 0, m = 0;
   size_t ld = 0, ldc = 0;

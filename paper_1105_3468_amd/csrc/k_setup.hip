@@ -388,7 +388,8 @@ static void aggregate_csr(int nc, const int* aptr, const int* amem, const int* r
   HIPCK(hipStreamSynchronize(s));
   oci.alloc(nnz > 0 ? nnz : 1);
   ov.alloc(nnz > 0 ? nnz : 1);
-  hipLaunchKernelGGL(k_compact, dim3(g1(std::min<int64_t>((int64_t)nc * 16, 1LL << 31))), dim3(256), 0, s, nc, off.p, orp.p, rj.p, rv.p, oci.p, ov.p);
+  hipLaunchKernelGGL(k_compact, dim3(g1(std::min<int64_t>((int64_t)nc * 16, 1LL << 31))), dim3(256), 0, s, nc, off.p,
+                     orp.p, rj.p, rv.p, oci.p, ov.p);
   HIPCK(hipGetLastError());
   HIPCK(hipStreamSynchronize(s));
   *onnz = nnz;

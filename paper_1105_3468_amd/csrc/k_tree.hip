@@ -64,11 +64,12 @@ __device__ __forceinline__ T tree_poll(const T* p, int* abort_flag, uint64_t lim
 //                       none), so that a tree's many leaves fit the workgroups
 //                       resident at once
 template <class T, class TR, bool LOWER>
-__global__ __launch_bounds__(TREE_THREADS, 6) void k_tree(const int* __restrict__ task, const int64_t* __restrict__ boff,
-                                                       const int* __restrict__ erp, const int* __restrict__ ecol,
-                                                       const T* __restrict__ eval, const T* __restrict__ inv,
-                                                       int* ncount, const TR* rhs, T* out, T* ext, TR* reset_rhs,
-                                                       int* abort_flag, uint64_t limit) {
+__global__ __launch_bounds__(TREE_THREADS, 6) void k_tree(const int* __restrict__ task,
+                                                          const int64_t* __restrict__ boff,
+                                                          const int* __restrict__ erp, const int* __restrict__ ecol,
+                                                          const T* __restrict__ eval, const T* __restrict__ inv,
+                                                          int* ncount, const TR* rhs, T* out, T* ext, TR* reset_rhs,
+                                                          int* abort_flag, uint64_t limit) {
   extern __shared__ __align__(16) unsigned char tree_smem[];
   T* y = reinterpret_cast<T*>(tree_smem);
   const int* tk = task + 8 * (size_t)blockIdx.x;
